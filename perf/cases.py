@@ -188,6 +188,53 @@ def run(state):
     return state["outputs"]
 
 
+# --------------------------------------------------------------------------- the same products in float64
+def _exact_product(case, w, x, keep=None):
+    """x W^T in float64 with W pruned and quantised as the format defines it, a slab of rows at a time.  The saliency
+    of a group is the float64 sum of its squares in index order (the squares are exact), the quantiser's steps are
+    single fp32 operations: both are reproduced to the last bit, so the same groups are kept with the same codes.
+    (An fp32 quotient taken in float64 and rounded to fp32 is the fp32 quotient.)"""
+    group, levels = case["group"], float(2 ** case["bits"] - 1)
+    n, k = w.shape
+    columns = k // group
+    kept = torch.full((n,), columns - int(case["sparsity"] * columns + 0.5)) if keep is None else torch.as_tensor(np.asarray(keep))
+    dropped = (columns - kept).to(w.device)
+    y = torch.empty((x.shape[0], n), dtype=torch.float64, device=w.device)
+    slab = max(1, (1 << 24) // k)
+    for r in range(0, n, slab):
+        g = w[r:r + slab].view(-1, columns, group)
+        saliency = torch.zeros(g.shape[:2], dtype=torch.float64, device=w.device)
+        for j in range(group):
+            saliency += g[:, :, j].double().square()
+        order = torch.sort(saliency, dim=1, stable=True).indices        # of equal ones the lower column goes first
+        place = torch.empty_like(order).scatter_(1, order, torch.arange(columns, device=w.device).expand_as(order))
+        low = g.amin(dim=2, keepdim=True)
+        scale = ((g.amax(dim=2, keepdim=True) - low).double() / levels).float().half().double().clamp_(min=2.0 ** -14)
+        zero = torch.round((-low.double() / scale).float()).clamp_(-2048.0, 2048.0).double()
+        codes = (torch.round((g.double() / scale).float()).double() + zero).clamp_(0.0, levels)
+        weights = (codes - zero) * scale * (place >= dropped[r:r + slab, None])[:, :, None]
+        y[:, r:r + slab] = x.double() @ weights.view(-1, k).t()
+    return y
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in float64 with plain torch.  Packing is compared bit for bit and has none."""
+    if case["kind"] == "pack":
+        return None
+    gen = _generator(seed)
+    if case["kind"] == "call":
+        calls = [((case["n"],), case["k"])]
+    else:
+        hidden, kv, ffn = case["hidden"], case["kv"], case["ffn"]
+        calls = [((hidden, kv, kv), hidden), ((hidden,), hidden), ((ffn, ffn), hidden), ((hidden,), ffn)] * case["layers"]
+    results = []
+    for sizes, k in calls:
+        held = [_weights(n, k, gen) for n in sizes]      # drawn in the order in which prepare() draws them
+        x = _activations(case["batch"], k, gen)
+        results += [_exact_product(case, w, x, _keep_counts(case, seed)) for w in held]
+    return results
+
+
 # --------------------------------------------------------------------------- what a pass cannot do without
 def _matrices(case):
     """(rows, columns, stored groups) of every matrix of a pass, and (columns) of every input."""
