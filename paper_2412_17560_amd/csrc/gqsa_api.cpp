@@ -74,8 +74,8 @@ gqsa_status_t upload(gqsa_matrix* m)
 // panel image: its time hardly depends on the row count (16 rows' worth of products either way),
 // the wavefront kernel's grows with every row, and they cross between 4 and 5 rows on an MI355X
 // for K up to 8192 and between 2 and 3 rows beyond (4096x11008, 4096x14336: every workgroup of
-// the wavefront kernel stages all of x; group sizes other than 16: between 2 and 3 rows as well,
-// since that kernel takes them one row per launch).
+// the wavefront kernel stages all of x; group sizes other than 16: between 2 and 3 rows as well --
+// 4096x4096 at 2 / 3 rows, W4: G = 32 4.3 / 6.5 against 5.0 / 5.1 us, G = 64 4.5 / 6.8 against 4.7 / 4.8 us).
 constexpr int panel_min_batch(const gqsa_matrix* m) { return m->G == 16 && m->K <= 8192 ? 5 : 3; }
 
 }  // namespace

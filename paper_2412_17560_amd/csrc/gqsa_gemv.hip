@@ -32,9 +32,10 @@
 
 #include "gqsa_internal.hpp"
 
-// This file is compiled several times: once whole (GQSA_GEMV_PART 0: the kernels for the formats'
-// own tile sizes and all the host code) and once per further tile size (parts 1..4: tiles of 3, 4, 5 and -- 4-bit codes -- 6 and 8
-// blocks with a chosen count of lanes in use, group size 16), so that the kernels build side by side.
+// This file is compiled several times: once whole (GQSA_GEMV_PART 0: the kernels for group size 16 with the
+// formats' own tile sizes and all the host code), once per further tile size (parts 1..4: tiles of 3, 4, 5 and -- 4-bit codes -- 6 and 8
+// blocks with a chosen count of lanes in use, group size 16) and once per pair of the other group sizes
+// (parts 5..8), so that the kernels build side by side.
 #ifndef GQSA_GEMV_PART
 #define GQSA_GEMV_PART 0
 #endif
@@ -105,6 +106,12 @@ Variant tile_variant_part1(int bits, int u, int slots, int nb, int* kgp);
 Variant tile_variant_part2(int bits, int u, int slots, int nb, int* kgp);
 Variant tile_variant_part3(int bits, int u, int slots, int nb, int* kgp);
 Variant tile_variant_part4(int bits, int u, int slots, int nb, int* kgp);
+// The variants for group sizes other than 16 (m = 16-element chunks per group, 0: half a chunk) that the
+// other compilations hold.
+Variant group_variant_part5(int bits, int m, int slots, int nb, int* kgp);
+Variant group_variant_part6(int bits, int m, int slots, int nb, int* kgp);
+Variant group_variant_part7(int bits, int m, int slots, int nb, int* kgp);
+Variant group_variant_part8(int bits, int m, int slots, int nb, int* kgp);
 
 namespace {
 
@@ -174,8 +181,8 @@ struct Codes {
 };
 template <int BITS> struct CodeUnit;
 template <> struct CodeUnit<4> {
-    static constexpr float kInverse = 1048576.0f;            // 2^20
-    static constexpr uint32_t kPairOfUnits = 0x00100010u;    // the fp16 pair (2^-20, 2^-20)
+    [[maybe_unused]] static constexpr float kInverse = 1048576.0f;            // 2^20
+    [[maybe_unused]] static constexpr uint32_t kPairOfUnits = 0x00100010u;    // the fp16 pair (2^-20, 2^-20)
 };
 template <> struct CodeUnit<8> {            // (8-bit codes keep the unit 1, see decode_w8)
     [[maybe_unused]] static constexpr float kInverse = 1.0f;
@@ -611,6 +618,13 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                     const float d = __builtin_fmaf(-z, xs, dot16<F::BITS>(c, xl, xh));
                     dotz[b] = i == 0 ? d : dotz[b] + d;
                 }
+                // several rows of larger groups: a chunk's sums are finished before the next chunk's
+                // gathers begin -- left to itself the compiler issues the whole tile's gathers,
+                // moves the products to where the sums are used and spills (up to 2.4 KB a lane)
+                if constexpr (F::M > 1 && NB > 1) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(dotz[b])::"memory");
+                }
             }
             fold_in_loop(u, dotz);
         }
@@ -856,7 +870,7 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
     // registers.
     // (one slot per thread covers K up to 4096 with one activation row; with several rows, or larger K, two:
     // what is not requested here is requested behind the tile and arrives behind it)
-    constexpr int XPRE = (KGP >= 512 || NB == 2 || NB == 4 || (NB == 8 && F::BITS == 4)) ? 2 : 1;      // (8 rows of 8-bit codes: the registers are not there)
+    constexpr int XPRE = (KGP >= 512 || NB == 2 || NB == 4 || (NB == 8 && F::BITS == 4 && F::M != 2)) ? 2 : 1;      // (8 rows of 8-bit codes, or of groups of 32: the registers are not there)
     const int n_slots = NB * kg;
     uint4 xlo[XPRE], xhi[XPRE];
 #pragma unroll
@@ -1047,18 +1061,20 @@ Variant variant_if_it_fits()
     return v;
 }
 
-// Compiled variants.  Group size 16: 1, 2, 4 or 8 activation rows per launch (as far as NB
-// copies of x fit the 160 KB of LDS).  Larger groups: one activation row.
+// Compiled variants: 1, 2, 4 or 8 activation rows per launch, as far as NB copies of x fit the
+// 160 KB of LDS.
+// (Group sizes other than 16 had the kernel for one row only, so a batch read and decoded the matrix once
+// per row: 14336x4096 W4 at 2 / 4 / 16 rows, G = 8 15.0 / 28.3 / 108 -> 11.3 / 15.7 / 68 us, G = 32
+// 10.7 / 20.0 / 75 -> 8.1 / 13.9 / 56 us, G = 128 13.9 / 27.1 / 106 -> 12.1 / 22.1 / 89 us; with 8-bit codes
+// G = 8 19.5 / 37.8 / 148 -> 12.1 / 16.5 / 74 us, G = 64 13.2 / 24.3 / 91 -> 9.7 / 16.8 / 69 us.)
 template <typename F, int KGP>
 Variant pick_variant(int nb)
 {
-    if (nb == 1) return variant_if_it_fits<F, KGP, 1>();
-    if constexpr (F::M == 1) {
-        switch (nb) {
-            case 2: return variant_if_it_fits<F, KGP, 2>();
-            case 4: return variant_if_it_fits<F, KGP, 4>();
-            case 8: return variant_if_it_fits<F, KGP, 8>();
-        }
+    switch (nb) {
+        case 1: return variant_if_it_fits<F, KGP, 1>();
+        case 2: return variant_if_it_fits<F, KGP, 2>();
+        case 4: return variant_if_it_fits<F, KGP, 4>();
+        case 8: return variant_if_it_fits<F, KGP, 8>();
     }
     return Variant{};
 }
@@ -1076,7 +1092,36 @@ Variant pick_kernel(int slots, int nb, int* kgp)
     return Variant{};
 }
 
-#if GQSA_GEMV_PART != 0
+#if GQSA_GEMV_PART >= 5
+// The two (code width, chunks per group) pairs of this compilation.
+#if GQSA_GEMV_PART == 5
+#define GQSA_PART_NAME group_variant_part5
+#define GQSA_PART_PAIRS {4, 0}, {4, 2}
+#elif GQSA_GEMV_PART == 6
+#define GQSA_PART_NAME group_variant_part6
+#define GQSA_PART_PAIRS {4, 4}, {8, 0}
+#elif GQSA_GEMV_PART == 7
+#define GQSA_PART_NAME group_variant_part7
+#define GQSA_PART_PAIRS {4, 8}, {8, 2}
+#else
+#define GQSA_PART_NAME group_variant_part8
+#define GQSA_PART_PAIRS {8, 4}, {8, 4}
+#endif
+struct BitsAndChunks { int bits, m; };
+constexpr BitsAndChunks kPairs[2] = {GQSA_PART_PAIRS};
+
+}  // namespace
+
+Variant GQSA_PART_NAME(int bits, int m, int slots, int nb, int* kgp)
+{
+    if (bits == kPairs[0].bits && m == kPairs[0].m) return pick_kernel<Fmt<kPairs[0].bits, kPairs[0].m>>(slots, nb, kgp);
+    if (bits == kPairs[1].bits && m == kPairs[1].m) return pick_kernel<Fmt<kPairs[1].bits, kPairs[1].m>>(slots, nb, kgp);
+    return Variant{};
+}
+
+}  // namespace gqsa
+
+#elif GQSA_GEMV_PART != 0
 // The two (code width, blocks per tile) pairs of this compilation.
 #if GQSA_GEMV_PART == 1
 #define GQSA_PART_NAME tile_variant_part1
@@ -1119,22 +1164,12 @@ Variant pick(const gqsa_matrix* m, int nb, int* kgp)
             if (Variant v = part(m->bits, m->tile_blocks, slots, nb, kgp)) return v;
         return Variant{};
     }
-    if (m->bits == 4) {
-        switch (m->G) {
-            case 8: return pick_kernel<Fmt<4, 0>>(slots, nb, kgp);
-            case 16: return pick_kernel<Fmt<4, 1>>(slots, nb, kgp);
-            case 32: return pick_kernel<Fmt<4, 2>>(slots, nb, kgp);
-            case 64: return pick_kernel<Fmt<4, 4>>(slots, nb, kgp);
-            case 128: return pick_kernel<Fmt<4, 8>>(slots, nb, kgp);
-        }
-    } else if (m->bits == 8) {
-        switch (m->G) {
-            case 8: return pick_kernel<Fmt<8, 0>>(slots, nb, kgp);
-            case 16: return pick_kernel<Fmt<8, 1>>(slots, nb, kgp);
-            case 32: return pick_kernel<Fmt<8, 2>>(slots, nb, kgp);
-            case 64: return pick_kernel<Fmt<8, 4>>(slots, nb, kgp);
-        }
-    }
+    if (m->G == 16)
+        return m->bits == 4 ? pick_kernel<Fmt<4, 1>>(slots, nb, kgp) : pick_kernel<Fmt<8, 1>>(slots, nb, kgp);
+    Variant (*const parts[4])(int, int, int, int, int*) = {group_variant_part5, group_variant_part6, group_variant_part7,
+                                                           group_variant_part8};
+    for (auto part : parts)
+        if (Variant v = part(m->bits, m->G / 16, slots, nb, kgp)) return v;
     return Variant{};
 }
 

@@ -486,6 +486,33 @@ def test_other_group_sizes(torch_cuda, bits, G, part):
     check(torch_cuda, h, c, gi.activations(3, K, seed=10))
 
 
+@pytest.mark.parametrize("bits,G", [(4, 8), (8, 8), (4, 32), (4, 64), (4, 128), (8, 32), (8, 64)])
+@pytest.mark.parametrize("K,part", [(128, None), (4096, None), (4096, (3, 4)), (4224, None), (8320, None)])
+def test_other_group_sizes_small_batches(torch_cuda, bits, G, K, part):
+    """The kernels for several activation rows, on both sides of the steps of K at which fewer rows fit a
+    launch (4096, 8192), one tile to a worker and several: every batch against the oracle, every row of it
+    the single-row result to the last bit (each row is summed by the same operations in the same
+    order), nothing written outside y."""
+    torch = torch_cuda
+    N = 101
+    W = gi.dense_weight(N, K, seed=92)
+    keep = gi.imbalanced_keep_counts(N, K // G, seed=92)
+    keep[[0, 50, 100]] = 0, K // G, 0
+    h = gq.gqsa_pack_rows(W, keep, G, bits)
+    c = oracle.pack(W, G, bits, keep_per_row=keep)
+    if part is not None:
+        gq.gqsa_set_partition(h, *part)
+    x16 = gi.activations(16, K, seed=12)
+    rows = np.concatenate([run_gemv(torch, h, x16[b:b + 1]) for b in range(16)])
+    for batch in (2, 3, 4, 5, 7, 8, 11, 16):
+        y, _ = check(torch, h, c, x16[:batch])
+        assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
+    buf = torch.full((8, N), 7.0, dtype=torch.float16, device="cuda")
+    gq.gqsa_gemv(h, torch.from_numpy(x16[:7].copy()).cuda(), buf[:7])
+    torch.cuda.synchronize()
+    assert (buf[7] == 7.0).all()
+
+
 @pytest.mark.parametrize("G", [8, 32, 64, 128])
 def test_other_group_sizes_full_size_and_sparsities(torch_cuda, G):
     """4096x4096 W4 at G = 32, 64, 128, S = 0 and 50 %, default partition."""
