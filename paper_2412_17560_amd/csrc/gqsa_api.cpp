@@ -74,9 +74,12 @@ gqsa_status_t upload(gqsa_matrix* m)
 // panel image: its time hardly depends on the row count (16 rows' worth of products either way),
 // the wavefront kernel's grows with every row, and they cross between 4 and 5 rows on an MI355X
 // for K up to 8192 and between 2 and 3 rows beyond (4096x11008, 4096x14336: every workgroup of
-// the wavefront kernel stages all of x; group sizes other than 16: between 2 and 3 rows as well --
-// 4096x4096 at 2 / 3 rows, W4: G = 32 4.3 / 6.5 against 5.0 / 5.1 us, G = 64 4.5 / 6.8 against 4.7 / 4.8 us).
-constexpr int panel_min_batch(const gqsa_matrix* m) { return m->G == 16 && m->K <= 8192 ? 5 : 3; }
+// the wavefront kernel stages all of x).  So they do for 8-bit codes in larger groups (4096x4096 at 4 / 5
+// rows: G = 32 5.4 / 8.8 against 6.0 / 6.0 us, G = 64 5.2 / 8.6 against 5.6 / 5.6 us); with 4-bit codes in
+// larger groups, whose panel image is smaller still, they cross between 2 and 3 (4096x4096 at 2 / 3 rows:
+// G = 32 4.2 / 6.1 against 5.1 / 5.1 us, G = 64 4.1 / 5.7 against 4.8 / 4.9 us; at 14336x4096 the two take the
+// same time at 3 and 4 rows).
+constexpr int panel_min_batch(const gqsa_matrix* m) { return (m->G == 16 || m->bits == 8) && m->K <= 8192 ? 5 : 3; }
 
 }  // namespace
 

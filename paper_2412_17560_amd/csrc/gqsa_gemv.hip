@@ -445,6 +445,14 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 // two arrays -- a group's 8 activations are one slot of the first or of the second -- and a sum
 // per half-slot, 8 bytes per column.)
 //
+// Groups of M = 2, 4 or 8 chunks begin at multiples of M slots, so chunk i of 64 lanes' groups would
+// lie in every M-th 16-byte slot only and their reads in 1/M of the banks.  The low bits of a
+// slot's number are therefore changed where it is stored: slot s lies at s xor ((s / 16) mod M) in the two
+// arrays of halves (16 slots fill the banks once), its sum at s xor ((s / 64) mod M) (64 sums do).
+// The bits taken are the same for all chunks of a group, so a lane works them out once per group.
+// (14336x4096 W4 at 1 / 2 / 4 rows: G = 32 6.1 / 8.1 / 13.9 -> 6.1 / 7.6 / 11.5 us, G = 64 6.2 / 9.5 / 16.9 ->
+// 5.8 / 7.0 / 10.2 us, G = 128 7.3 / 12.1 / 22.1 -> 5.5 / 6.8 / 9.4 us.)
+//
 // EAGER: the tile's loads may still be in flight.  All gathers are issued first (they need only
 // the index words, the first of the tile's loads to arrive), then the groups are decoded block
 // by block as their codes come in.  Otherwise the gathers go group by group (fewer registers).
@@ -605,16 +613,20 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                     dotz[b] = __builtin_fmaf(-z, xs, join<F::BITS>(lo, hi));
                 }
             }
+            // (where the group's chunk 0 lies and its sum; those of chunk i differ in the bits of i)
+            const uint32_t slot0 = F::M > 1 ? slot | ((slot >> 4) & ((F::M - 1) * 16u)) : slot;
+            const uint32_t sum0 = F::M > 1 ? (slot >> 2) | ((slot >> 8) & ((F::M - 1) * 4u)) : slot >> 2;
 #pragma unroll
             for (int i = 0; i < F::M; ++i) {                // the group's 16-element chunks
                 Codes c;
                 decode_chunk<F>(t, u, i, c);
+                const uint32_t sloti = slot0 ^ (16u * i);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const uint32_t xb = x0 + slot + 16 * i + b * (48 * KGP);
+                    const uint32_t xb = x0 + sloti + b * (48 * KGP);
                     const uint4 xl = lds_read16(xb);
                     const uint4 xh = lds_read16(xb + 16 * KGP);
-                    const float xs = lds_read_float(x0 + b * (48 * KGP) + 32 * KGP + (slot >> 2) + 4 * i);
+                    const float xs = lds_read_float(x0 + b * (48 * KGP) + 32 * KGP + (sum0 ^ (4u * i)));
                     const float d = __builtin_fmaf(-z, xs, dot16<F::BITS>(c, xl, xh));
                     dotz[b] = i == 0 ? d : dotz[b] + d;
                 }
@@ -920,7 +932,11 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
 
     auto stage = [&](int c, uint4 lo, uint4 hi) {   // c = slot over all rows: b * kg + column
         const int b = NB == 1 ? 0 : c / kg;
-        uint8_t* slot = xlds + b * (48 * KGP) + (c - b * kg) * 16;
+        const int column = c - b * kg;
+        // (where the slot and its sum lie: see compute_tile)
+        const int at = F::M > 1 ? column ^ ((column >> 4) & (F::M - 1)) : column;
+        const int sum_at = F::M > 1 ? column ^ ((column >> 6) & (F::M - 1)) : column;
+        uint8_t* slot = xlds + b * (48 * KGP) + at * 16;
         *reinterpret_cast<uint4*>(slot) = lo;
         *reinterpret_cast<uint4*>(slot + 16 * KGP) = hi;
         const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -932,12 +948,12 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
                 s0 = __builtin_amdgcn_fdot2(as_half2(w[i]), ones, s0, false);
                 s1 = __builtin_amdgcn_fdot2(as_half2(w[4 + i]), ones, s1, false);
             }
-            *reinterpret_cast<float2*>(xlds + b * (48 * KGP) + 32 * KGP + (c - b * kg) * 8) = float2{s0, s1};
+            *reinterpret_cast<float2*>(xlds + b * (48 * KGP) + 32 * KGP + sum_at * 8) = float2{s0, s1};
         } else {
             float s = 0.0f;      // sum of the slot's 16 activations, fp32: a pair per instruction
 #pragma unroll
             for (int i = 0; i < 8; ++i) s = __builtin_amdgcn_fdot2(as_half2(w[i]), ones, s, false);
-            *reinterpret_cast<float*>(xlds + b * (48 * KGP) + 32 * KGP + (c - b * kg) * 4) = s;
+            *reinterpret_cast<float*>(xlds + b * (48 * KGP) + 32 * KGP + sum_at * 4) = s;
         }
     };
     // x into LDS (the loads of the tiles are already out), then the workgroup meets
@@ -1064,9 +1080,10 @@ Variant variant_if_it_fits()
 // Compiled variants: 1, 2, 4 or 8 activation rows per launch, as far as NB copies of x fit the
 // 160 KB of LDS.
 // (Group sizes other than 16 had the kernel for one row only, so a batch read and decoded the matrix once
-// per row: 14336x4096 W4 at 2 / 4 / 16 rows, G = 8 15.0 / 28.3 / 108 -> 11.3 / 15.7 / 68 us, G = 32
-// 10.7 / 20.0 / 75 -> 8.1 / 13.9 / 56 us, G = 128 13.9 / 27.1 / 106 -> 12.1 / 22.1 / 89 us; with 8-bit codes
-// G = 8 19.5 / 37.8 / 148 -> 12.1 / 16.5 / 74 us, G = 64 13.2 / 24.3 / 91 -> 9.7 / 16.8 / 69 us.)
+// per row: 14336x4096 W4 at 2 / 4 / 16 rows, G = 8 15.0 / 28.3 / 108 -> 11.1 / 15.7 / 68 us, G = 32
+// 10.7 / 20.0 / 75 -> 7.6 / 11.5 / 47 us, G = 128 13.9 / 27.1 / 106 -> 6.8 / 9.4 / 38 us; with 8-bit codes
+// G = 8 19.5 / 37.8 / 148 -> 12.2 / 16.6 / 74 us, G = 64 13.2 / 24.3 / 91 -> 9.2 / 12.0 / 46 us, all with the
+// slots placed as compute_tile describes.)
 template <typename F, int KGP>
 Variant pick_variant(int nb)
 {
