@@ -315,7 +315,7 @@ gqsa_status_t gqsa_gemv_multi(const gqsa_handle_t* handles, int n_matrices, cons
         // One launch when the matrices can share a kernel variant (the zero is handled the same
         // way in all of them): a workgroup's panels then come from different matrices and the
         // activations, most of what a compute unit reads, are loaded once for all of them.
-        // (Not beyond four panels per compute unit's workgroup: a second round of workgroups
+        // (Not beyond eight panels per compute unit's workgroup: a second round of workgroups
         // would leave most compute units idle.)
         bool alike = true;
         int64_t panels_in_all = 0;
@@ -323,7 +323,7 @@ gqsa_status_t gqsa_gemv_multi(const gqsa_handle_t* handles, int n_matrices, cons
             if (handles[i]->panel_integer_zeros != handles[0]->panel_integer_zeros) alike = false;
             panels_in_all += handles[i]->n_panels;
         }
-        if (alike && n_matrices > 1 && panels_in_all <= 4 * gqsa::kMaxDefaultWorkgroups)
+        if (alike && n_matrices > 1 && panels_in_all <= 8 * gqsa::kMaxDefaultWorkgroups)
             return gqsa::panels_gemm(handles, n_matrices, x_dev, y_devs, batch, hip_stream);
         for (int i = 0; i < n_matrices; ++i)
             if (gqsa_status_t st = gqsa::panels_gemm(&handles[i], 1, x_dev, &y_devs[i], batch, hip_stream)) return st;

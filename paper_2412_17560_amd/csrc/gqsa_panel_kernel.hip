@@ -27,7 +27,7 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kPanelsPerWorkgroup = 4;   // panels a workgroup takes at most (each needs its own sums)
+constexpr int kPanelsPerQuad = 4;      // panels whose records are staged, and whose headers are held, together
 constexpr int kInFlight = 4;          // group-columns whose products are under way together
 constexpr int kPanelWaves = 16;      // wavefronts of a workgroup (or 8, see WAVES): each takes every 16th (8th) unit (a run of group-columns) of the panel
 constexpr int kWaveLds = 9216;        // bytes of LDS a wavefront stages records in (16 x 9 KB = 144 of the 160 KB)
@@ -86,7 +86,7 @@ struct PanelTargets {
     int total;                  // panels of all matrices
 };
 
-// A workgroup takes up to four panels of 16 output rows (blockIdx.x, + gridDim.x, ...); wavefront
+// A workgroup takes up to four panels (eight: QUADS) of 16 output rows (blockIdx.x, + gridDim.x, ...); wavefront
 // w takes the units w, w + 16, ... (a unit = a run of group-columns, half a slice or less) of
 // every one of them, so the activations under a unit are loaded once for all of the workgroup's
 // panels.  A block's header is the same for all lanes and is read with scalar loads.  The records
@@ -116,11 +116,18 @@ struct PanelTargets {
 // zero is an arbitrary fp16 number and multiplies the second product's sum of activations.
 // MULTI: more than one matrix in the launch (the lookups of a panel's matrix cost scalar
 // registers, which the headers of four panels already fill: one matrix keeps its own code).
-// WAVES: 16 wavefronts per workgroup and one workgroup per compute unit, or -- for launches of
-// more workgroups than compute units -- 8 and two: the loads of one then run under the products
+// WAVES: 16 wavefronts per workgroup and one workgroup per compute unit, or -- for one matrix of more
+// panels than four per compute unit -- 8 and two: the loads of one then run under the products
 // of the other (workgroups of 16 wavefronts can only follow one another, each loading, then
 // computing).  Either way four wavefronts per SIMD unit, 128 vector registers each.
-template <int BITS, int M, bool INTZ, bool MULTI, int WAVES>
+// QUADS: a workgroup takes its panels four at a time (a quad: their headers share the scalar registers,
+// their records the staging area), and up to QUADS quads under the activations of a unit, which are loaded
+// once for all of them: every compute unit pulls all of x through its L1 (128 KB at 16 rows and K = 4096, at
+// about 16 bytes per cycle: 3.4 us), so a second workgroup or launch for the panels beyond the fourth
+// pays that again.  Two quads against one, at 16 rows, K = 4096, W4 S = 50 %: gate/up of 2 x 11008 in one launch
+// instead of two 24.3 -> 22.6 us, 2 x 14336 29.0 -> 25.1 us (W8 33.5 -> 29.4), one matrix of 20000 rows
+// 25.0 -> 18.5 us, 28672x8192 45.4 -> 40.2 us, 60000 rows 46.5 -> 43.4 us, 32000 rows the same.
+template <int BITS, int M, bool INTZ, bool MULTI, int WAVES, int QUADS>
 __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     const uint16_t* __restrict__ x,
     const uint8_t* __restrict__ headers0, const uint8_t* __restrict__ headers1,
@@ -135,6 +142,7 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     constexpr int QB = (BITS / 2) * M;              // code bytes of a lane (one quarter of every chunk)
     constexpr int QW = (QB + 3) / 4;                // ... in registers
     constexpr bool PAIRED = QB == 2;                // 4-bit, G = 16: a 12-byte record, read whole
+    constexpr int kPanelsPerWorkgroup = QUADS * kPanelsPerQuad;     // at most
     __shared__ __attribute__((aligned(16))) uint8_t staged[WAVES * kWaveLds];
     float* part = reinterpret_cast<float*>(staged);            // the same memory once the products are done
     const int tid = threadIdx.x;
@@ -174,10 +182,6 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
         }
         return is_live;
     };
-    int mat[kPanelsPerWorkgroup], pan[kPanelsPerWorkgroup];
-    bool live[kPanelsPerWorkgroup];
-#pragma unroll
-    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) live[pp] = locate(pp, mat[pp], pan[pp]);
     float acc[kPanelsPerWorkgroup][4];
 #pragma unroll
     for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp)
@@ -220,166 +224,183 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
             const int g = col0 * M + 2 * pr + (j >> 1);
             xw[pr] = *reinterpret_cast<const uint4*>(xrow + 16 * (g < last_chunk ? g : last_chunk));
         }
-        // the headers of all the workgroup's panels at once (scalar loads; a panel beyond the
-        // last one stands in as the last one and is not computed)
-        // (where 4 x HC words do not fit the scalar registers -- AGAIN -- only the first and the
-        // last column's word of each panel are read here, and all of a panel's words a second
-        // time, from the scalar cache, when its products start)
-        constexpr bool AGAIN = kPanelsPerWorkgroup * HC > 32;
-        uint32_t hh_all[AGAIN ? 1 : kPanelsPerWorkgroup][AGAIN ? 1 : HC];
-        uint32_t header_at[kPanelsPerWorkgroup];        // byte offset of the unit's first word in the panel's matrix's headers
-        uint32_t h_first[kPanelsPerWorkgroup], h_last[kPanelsPerWorkgroup], where[kPanelsPerWorkgroup];
 #pragma unroll
-        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-            // (the choice is made here, at the load: a header is read with scalar loads only if the
-            // compiler can trace its address to a read-only argument)
-            const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
-            const uint32_t* header = reinterpret_cast<const uint32_t*>(
-                headers + static_cast<size_t>(pan[pp] * n_slices + s) * kPanelHeaderBytes);
-            header_at[pp] = static_cast<uint32_t>((pan[pp] * n_slices + s) * kPanelHeaderBytes + sub * HC * 4);
-            if constexpr (!AGAIN) {
+        for (int quad = 0; quad < QUADS; ++quad) {
+            int mat[kPanelsPerQuad], pan[kPanelsPerQuad];
+            bool live[kPanelsPerQuad];
 #pragma unroll
-                for (int c = 0; c < HC; ++c) hh_all[pp][c] = header[sub * HC + c];
+            for (int pp = 0; pp < kPanelsPerQuad; ++pp) live[pp] = locate(quad * kPanelsPerQuad + pp, mat[pp], pan[pp]);
+            if (quad > 0) {
+                if (!live[0]) break;                        // (the same for the whole workgroup)
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the staging area has been read
             }
-            h_first[pp] = header[sub * HC];
-            h_last[pp] = header[sub * HC + HC - 1];
-            where[pp] = header[32];
-        }
-        // Where each panel's records of this unit lie (they are contiguous: first group of the
-        // first column .. last group of the last column) and where they go in the wavefront's
-        // staging area: one after the other, each rounded up to 16 bytes plus room for one more
-        // record (a lane without a group may read the one behind the last).  All four panels are
-        // staged at once when they fit, else two and two.
-        constexpr uint32_t kSpare = (RB + 15u) & ~15u;
-        static_assert(2 * (kMaxUnitBytes + kSpare) <= kWaveLds, "two panels' worth must fit a wavefront's staging area");
-        uint32_t first[kPanelsPerWorkgroup], bytes[kPanelsPerWorkgroup], room[kPanelsPerWorkgroup], slot[kPanelsPerWorkgroup];
+            // the headers of four panels at once (scalar loads; a panel beyond the
+            // last one stands in as the last one and is not computed)
+            // (where 4 x HC words do not fit the scalar registers -- AGAIN -- only the first and the
+            // last column's word of each panel are read here, and all of a panel's words a second
+            // time, from the scalar cache, when its products start)
+            constexpr bool AGAIN = kPanelsPerQuad * HC > 32;
+            uint32_t hh_all[AGAIN ? 1 : kPanelsPerQuad][AGAIN ? 1 : HC];
+            uint32_t header_at[kPanelsPerQuad];        // byte offset of the unit's first word in the panel's matrix's headers
+            uint32_t h_first[kPanelsPerQuad], h_last[kPanelsPerQuad], where[kPanelsPerQuad];
 #pragma unroll
-        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-            const uint32_t last = h_last[pp];
-            first[pp] = h_first[pp] >> 16;
-            bytes[pp] = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first[pp]) * RB;     // <= kMaxUnitBytes
-            room[pp] = ((bytes[pp] + 15u) & ~15u) + kSpare;
-        }
-        const bool two_and_two = room[0] + room[1] + room[2] + room[3] > static_cast<uint32_t>(kWaveLds);
-        slot[0] = 0;
-        slot[1] = room[0];
-        slot[2] = two_and_two ? 0 : room[0] + room[1];
-        slot[3] = slot[2] + room[2];
-#pragma unroll
-        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-            if (pp == 0 || (pp == 2 && two_and_two)) {
-                // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
-                // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
-#pragma unroll
-                for (int q = pp; q < kPanelsPerWorkgroup; ++q) {
-                    if (live[q] && (q < pp + 2 || !two_and_two)) {
-                        const uint8_t* data = !MULTI || mat[q] == 0 ? data0 : mat[q] == 1 ? data1 : mat[q] == 2 ? data2 : data3;
-                        const uint8_t* from = data + static_cast<size_t>(where[q]) * 16 + first[q] * RB;
-#pragma unroll
-                        for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
-                            const uint32_t o = 16u * lane + 1024u * i;
-                            if (o < bytes[q])
-                                __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
-                                                                 (__attribute__((address_space(3))) void*)(mine + slot[q] + 1024u * i),
-                                                                 16, 0, 0);
-                        }
-                    }
-                }
-                if (pp == 0) {
-                    uint2* flat = &xa[0][0];
-#pragma unroll
-                    for (int pr = 0; pr < XCH / 2; ++pr) {
-                        const auto s0 = __builtin_amdgcn_permlane32_swap(xw[pr].x, xw[pr].z, false, false);
-                        const auto s1 = __builtin_amdgcn_permlane32_swap(xw[pr].y, xw[pr].w, false, false);
-                        flat[2 * pr] = uint2{s0[0], s1[0]};
-                        flat[2 * pr + 1] = uint2{s0[1], s1[1]};
-                    }
-                }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
-            }
-            if (live[pp]) {                             // (the same for the whole workgroup)
-                const uint8_t* records = mine + slot[pp];           // in LDS
-                const uint32_t before0 = first[pp];
-                uint32_t hh[HC];
+            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                // (the choice is made here, at the load: a header is read with scalar loads only if the
+                // compiler can trace its address to a read-only argument)
+                const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
+                const uint32_t* header = reinterpret_cast<const uint32_t*>(
+                    headers + static_cast<size_t>(pan[pp] * n_slices + s) * kPanelHeaderBytes);
+                header_at[pp] = static_cast<uint32_t>((pan[pp] * n_slices + s) * kPanelHeaderBytes + sub * HC * 4);
                 if constexpr (!AGAIN) {
 #pragma unroll
-                    for (int c = 0; c < HC; ++c) hh[c] = hh_all[pp][c];
-                } else {
-                    uint32_t at = header_at[pp];
-                    asm volatile("" : "+s"(at));            // (a read of its own, not the values kept from above)
-                    const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
-                    const uint32_t* again = reinterpret_cast<const uint32_t*>(headers + at);
-#pragma unroll
-                    for (int c = 0; c < HC; ++c) hh[c] = again[c];
+                    for (int c = 0; c < HC; ++c) hh_all[pp][c] = header[sub * HC + c];
                 }
-                uint32_t code[HC][(PAIRED || PAIRED8) ? 2 : QW], sz[HC];
-                constexpr bool TRI = PAIRED || PAIRED8;     // three words, the middle one is scale | zero as it is: the whole 12-byte
-                                                            // record, or the half of the 24-byte one that holds the lane's quarter
+                h_first[pp] = header[sub * HC];
+                h_last[pp] = header[sub * HC + HC - 1];
+                where[pp] = header[32];
+            }
+            // Where each panel's records of this unit lie (they are contiguous: first group of the
+            // first column .. last group of the last column) and where they go in the wavefront's
+            // staging area: one after the other, each rounded up to 16 bytes plus room for one more
+            // record (a lane without a group may read the one behind the last).  All four panels are
+            // staged at once when they fit, else two and two.
+            constexpr uint32_t kSpare = (RB + 15u) & ~15u;
+            static_assert(2 * (kMaxUnitBytes + kSpare) <= kWaveLds, "two panels' worth must fit a wavefront's staging area");
+            uint32_t first[kPanelsPerQuad], bytes[kPanelsPerQuad], room[kPanelsPerQuad], slot[kPanelsPerQuad];
 #pragma unroll
-                for (int c = 0; c < HC; ++c) {
-                    const uint32_t h = hh[c];
-                    const uint32_t idx = ((h >> 16) - before0) + __builtin_popcount(h & 0xFFFFu & below);
-                    if constexpr (TRI) {
-                        const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + (PAIRED8 ? half_of_record : 0u)));
-                        code[c][0] = w[0];
-                        sz[c] = w[1];
-                        code[c][1] = w[2];
-                    } else {
-                        const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + code_lane));
+            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                const uint32_t last = h_last[pp];
+                first[pp] = h_first[pp] >> 16;
+                bytes[pp] = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first[pp]) * RB;     // <= kMaxUnitBytes
+                room[pp] = ((bytes[pp] + 15u) & ~15u) + kSpare;
+            }
+            const bool two_and_two = room[0] + room[1] + room[2] + room[3] > static_cast<uint32_t>(kWaveLds);
+            slot[0] = 0;
+            slot[1] = room[0];
+            slot[2] = two_and_two ? 0 : room[0] + room[1];
+            slot[3] = slot[2] + room[2];
 #pragma unroll
-                        for (int t = 0; t < QW; ++t) code[c][t] = w[t];
-                        sz[c] = *reinterpret_cast<const uint32_t*>(records + (idx * RB + CB / 2));
-                    }
-                }
-                // four columns at a time: the products of the later ones are under way while the
-                // first one's sums are scaled.  Which lanes have a group in a column is a lane
-                // mask made from the header word with scalar arithmetic (bit r -> lanes r, r + 16, ...)
+            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                if (pp == 0 || (pp == 2 && two_and_two)) {
+                    // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
+                    // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
 #pragma unroll
-                for (int c = 0; c < HC; c += FLY) {
-                    float4_t d[FLY], e[FLY];
-                    uint32_t sz_word[FLY];
+                    for (int q = pp; q < kPanelsPerQuad; ++q) {
+                        if (live[q] && (q < pp + 2 || !two_and_two)) {
+                            const uint8_t* data = !MULTI || mat[q] == 0 ? data0 : mat[q] == 1 ? data1 : mat[q] == 2 ? data2 : data3;
+                            const uint8_t* from = data + static_cast<size_t>(where[q]) * 16 + first[q] * RB;
 #pragma unroll
-                    for (int i = 0; i < FLY; ++i) {
-                        sz_word[i] = sz[c + i];
-                        half2_t off_lo = k1024, off_hi = k64;
-                        if constexpr (INTZ) {
-                            const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
-                            const half2_t zz = {both.y, both.y};
-                            off_lo = k1024 + zz;
-                            off_hi = k64 + zz;
-                        }
-                        d[i] = zero4;
-                        e[i] = zero4;
-#pragma unroll
-                        for (int k = 0; k < M; ++k) {
-                            const half4_t a = __builtin_bit_cast(half4_t, xa[c + i][k]);
-                            half4_t q;
-                            if constexpr (PAIRED8) {
-                                q = decode4_w8(code[c + i][1], code[c + i][0], sel_codes, dk, off_lo);
-                            } else if constexpr (PAIRED) {
-                                q = decode4_w4(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off_lo, off_hi);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
-                            } else if constexpr (BITS == 4) {     // chunk k: two bytes, the lower or the upper half of a word
-                                q = decode4_w4(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off_lo, off_hi);
-                            } else {
-                                q = decode4_w8(0u, code[c + i][k], 0x0c010c00u, dk, off_lo);
+                            for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
+                                const uint32_t o = 16u * lane + 1024u * i;
+                                if (o < bytes[q])
+                                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
+                                                                     (__attribute__((address_space(3))) void*)(mine + slot[q] + 1024u * i),
+                                                                     16, 0, 0);
                             }
-                            d[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, q, d[i], 0, 0, 0);      // sum_j q_j x_j, or sum_j (q_j - z) x_j
-                            if constexpr (!INTZ) e[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, e[i], 0, 0, 0);   // sum_j x_j
                         }
                     }
+                    if (pp == 0 && quad == 0) {
+                        uint2* flat = &xa[0][0];
 #pragma unroll
-                    for (int i = 0; i < FLY; ++i) {
-                        const unsigned long long lanes = static_cast<unsigned long long>(hh[c + i] & 0xFFFFu) * 0x0001000100010001ull;
-                        if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
-                            const float sc = half_bits_to_float(sz_word[i] & 0xFFFFu);
-                            if constexpr (INTZ) {
+                        for (int pr = 0; pr < XCH / 2; ++pr) {
+                            const auto s0 = __builtin_amdgcn_permlane32_swap(xw[pr].x, xw[pr].z, false, false);
+                            const auto s1 = __builtin_amdgcn_permlane32_swap(xw[pr].y, xw[pr].w, false, false);
+                            flat[2 * pr] = uint2{s0[0], s1[0]};
+                            flat[2 * pr + 1] = uint2{s0[1], s1[1]};
+                        }
+                    }
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
+                }
+                if (live[pp]) {                             // (the same for the whole workgroup)
+                    const uint8_t* records = mine + slot[pp];           // in LDS
+                    const uint32_t before0 = first[pp];
+                    uint32_t hh[HC];
+                    if constexpr (!AGAIN) {
 #pragma unroll
-                                for (int v = 0; v < 4; ++v) acc[pp][v] = __builtin_fmaf(sc, d[i][v], acc[pp][v]);
+                        for (int c = 0; c < HC; ++c) hh[c] = hh_all[pp][c];
+                    } else {
+                        uint32_t at = header_at[pp];
+                        asm volatile("" : "+s"(at));            // (a read of its own, not the values kept from above)
+                        const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
+                        const uint32_t* again = reinterpret_cast<const uint32_t*>(headers + at);
+#pragma unroll
+                        for (int c = 0; c < HC; ++c) hh[c] = again[c];
+                    }
+                    // (sums of eight panels leave registers for the records of eight columns at a time, of four where a column takes two sums)
+                    constexpr int HL = QUADS == 1 || BITS == 8 ? HC : HC > 8 ? 8 : !INTZ && HC > 4 ? 4 : HC;
+#pragma unroll
+                    for (int c0 = 0; c0 < HC; c0 += HL) {
+                        if (c0 > 0) asm volatile("" ::: "memory");
+                        uint32_t code[HL][(PAIRED || PAIRED8) ? 2 : QW], sz[HL];
+                        constexpr bool TRI = PAIRED || PAIRED8;     // three words, the middle one is scale | zero as it is: the whole 12-byte
+                                                                    // record, or the half of the 24-byte one that holds the lane's quarter
+#pragma unroll
+                        for (int c = 0; c < HL; ++c) {
+                            const uint32_t h = hh[c0 + c];
+                            const uint32_t idx = ((h >> 16) - before0) + __builtin_popcount(h & 0xFFFFu & below);
+                            if constexpr (TRI) {
+                                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + (PAIRED8 ? half_of_record : 0u)));
+                                code[c][0] = w[0];
+                                sz[c] = w[1];
+                                code[c][1] = w[2];
                             } else {
-                                const float z = half_bits_to_float(sz_word[i] >> 16);
+                                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + code_lane));
 #pragma unroll
-                                for (int v = 0; v < 4; ++v)
-                                    acc[pp][v] = __builtin_fmaf(sc, __builtin_fmaf(-z, e[i][v], d[i][v]), acc[pp][v]);
+                                for (int t = 0; t < QW; ++t) code[c][t] = w[t];
+                                sz[c] = *reinterpret_cast<const uint32_t*>(records + (idx * RB + CB / 2));
+                            }
+                        }
+                        // four columns at a time: the products of the later ones are under way while the
+                        // first one's sums are scaled.  Which lanes have a group in a column is a lane
+                        // mask made from the header word with scalar arithmetic (bit r -> lanes r, r + 16, ...)
+#pragma unroll
+                        for (int c = 0; c < HL; c += FLY) {
+                            float4_t d[FLY], e[FLY];
+                            uint32_t sz_word[FLY];
+#pragma unroll
+                            for (int i = 0; i < FLY; ++i) {
+                                sz_word[i] = sz[c + i];
+                                half2_t off_lo = k1024, off_hi = k64;
+                                if constexpr (INTZ) {
+                                    const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
+                                    const half2_t zz = {both.y, both.y};
+                                    off_lo = k1024 + zz;
+                                    off_hi = k64 + zz;
+                                }
+                                d[i] = zero4;
+                                e[i] = zero4;
+#pragma unroll
+                                for (int k = 0; k < M; ++k) {
+                                    const half4_t a = __builtin_bit_cast(half4_t, xa[c0 + c + i][k]);
+                                    half4_t q;
+                                    if constexpr (PAIRED8) {
+                                        q = decode4_w8(code[c + i][1], code[c + i][0], sel_codes, dk, off_lo);
+                                    } else if constexpr (PAIRED) {
+                                        q = decode4_w4(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off_lo, off_hi);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
+                                    } else if constexpr (BITS == 4) {     // chunk k: two bytes, the lower or the upper half of a word
+                                        q = decode4_w4(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off_lo, off_hi);
+                                    } else {
+                                        q = decode4_w8(0u, code[c + i][k], 0x0c010c00u, dk, off_lo);
+                                    }
+                                    d[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, q, d[i], 0, 0, 0);      // sum_j q_j x_j, or sum_j (q_j - z) x_j
+                                    if constexpr (!INTZ) e[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, e[i], 0, 0, 0);   // sum_j x_j
+                                }
+                            }
+#pragma unroll
+                            for (int i = 0; i < FLY; ++i) {
+                                const unsigned long long lanes = static_cast<unsigned long long>(hh[c0 + c + i] & 0xFFFFu) * 0x0001000100010001ull;
+                                if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
+                                    const float sc = half_bits_to_float(sz_word[i] & 0xFFFFu);
+                                    if constexpr (INTZ) {
+#pragma unroll
+                                        for (int v = 0; v < 4; ++v) acc[quad * kPanelsPerQuad + pp][v] = __builtin_fmaf(sc, d[i][v], acc[quad * kPanelsPerQuad + pp][v]);
+                                    } else {
+                                        const float z = half_bits_to_float(sz_word[i] >> 16);
+#pragma unroll
+                                        for (int v = 0; v < 4; ++v)
+                                            acc[quad * kPanelsPerQuad + pp][v] = __builtin_fmaf(sc, __builtin_fmaf(-z, e[i][v], d[i][v]), acc[quad * kPanelsPerQuad + pp][v]);
+                                    }
+                                }
                             }
                         }
                     }
@@ -396,7 +417,7 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     __syncthreads();
 #pragma unroll
     for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-        if (!live[pp]) break;                           // (the same for the whole workgroup)
+        if (blockIdx.x + pp * gridDim.x >= static_cast<unsigned>(tgt.total)) break;     // (the same for the whole workgroup)
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[((pp * 4 + v) * WAVES + wl) * kLanes + lane] = acc[pp][v];
     }
@@ -486,11 +507,16 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     }
     tgt.total = static_cast<int>(total);
     const gqsa_matrix* m = ms[0];
-    // one workgroup per compute unit unless that gives a workgroup more than four panels
-    const int64_t wgs = std::min<int64_t>(total, std::max<int64_t>(kMaxDefaultWorkgroups,
-                                                                   (total + kPanelsPerWorkgroup - 1) / kPanelsPerWorkgroup));
-    // more workgroups than compute units: smaller ones, two to a compute unit (see WAVES)
-    const bool halves = n == 1 && wgs > kMaxDefaultWorkgroups;
+    // Up to four panels per compute unit: one workgroup of 16 wavefronts on each.  More panels:
+    // workgroups of up to eight (see QUADS) -- with several matrices still one per compute unit (the caller
+    // sends no more than eight panels per compute unit this way), with one matrix smaller ones, two
+    // to a compute unit (see WAVES; with 16 wavefronts and one per compute unit 20000 and 28672x8192
+    // take 2 % longer, 60000 rows 13 %).
+    const bool many = total > kPanelsPerQuad * kMaxDefaultWorkgroups;
+    const bool halves = many && n == 1;
+    const int64_t per_wg = many ? 2 * kPanelsPerQuad : kPanelsPerQuad;
+    const int64_t wgs = std::min<int64_t>(total, std::max<int64_t>((halves ? 2 : 1) * kMaxDefaultWorkgroups,
+                                                                   (total + per_wg - 1) / per_wg));
     const dim3 grid(static_cast<unsigned>(wgs)), block((halves ? kPanelWaves / 2 : kPanelWaves) * kLanes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const auto launch = [&](auto kernel) {
@@ -498,32 +524,35 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
                            headers[3], data[0], data[1], data[2], data[3], tgt, static_cast<int>(m->K),
                            static_cast<int>(m->n_slices), batch);
     };
-    const auto pick = [&](auto multi, auto waves) {
+    const auto pick = [&](auto multi, auto waves, auto quads) {
         constexpr bool kMulti = decltype(multi)::value;
         constexpr int kWaves = decltype(waves)::value;
+        constexpr int kQuads = decltype(quads)::value;
         switch (m->bits * 1000 + m->G + (m->panel_integer_zeros ? 500 : 0)) {
-            case 4016: launch(gqsa_panel_kernel<4, 1, false, kMulti, kWaves>); break;
-            case 4032: launch(gqsa_panel_kernel<4, 2, false, kMulti, kWaves>); break;
-            case 4064: launch(gqsa_panel_kernel<4, 4, false, kMulti, kWaves>); break;
-            case 4128: launch(gqsa_panel_kernel<4, 8, false, kMulti, kWaves>); break;
-            case 8016: launch(gqsa_panel_kernel<8, 1, false, kMulti, kWaves>); break;
-            case 8032: launch(gqsa_panel_kernel<8, 2, false, kMulti, kWaves>); break;
-            case 8064: launch(gqsa_panel_kernel<8, 4, false, kMulti, kWaves>); break;
-            case 4516: launch(gqsa_panel_kernel<4, 1, true, kMulti, kWaves>); break;
-            case 4532: launch(gqsa_panel_kernel<4, 2, true, kMulti, kWaves>); break;
-            case 4564: launch(gqsa_panel_kernel<4, 4, true, kMulti, kWaves>); break;
-            case 4628: launch(gqsa_panel_kernel<4, 8, true, kMulti, kWaves>); break;
-            case 8516: launch(gqsa_panel_kernel<8, 1, true, kMulti, kWaves>); break;
-            case 8532: launch(gqsa_panel_kernel<8, 2, true, kMulti, kWaves>); break;
-            case 8564: launch(gqsa_panel_kernel<8, 4, true, kMulti, kWaves>); break;
+            case 4016: launch(gqsa_panel_kernel<4, 1, false, kMulti, kWaves, kQuads>); break;
+            case 4032: launch(gqsa_panel_kernel<4, 2, false, kMulti, kWaves, kQuads>); break;
+            case 4064: launch(gqsa_panel_kernel<4, 4, false, kMulti, kWaves, kQuads>); break;
+            case 4128: launch(gqsa_panel_kernel<4, 8, false, kMulti, kWaves, kQuads>); break;
+            case 8016: launch(gqsa_panel_kernel<8, 1, false, kMulti, kWaves, kQuads>); break;
+            case 8032: launch(gqsa_panel_kernel<8, 2, false, kMulti, kWaves, kQuads>); break;
+            case 8064: launch(gqsa_panel_kernel<8, 4, false, kMulti, kWaves, kQuads>); break;
+            case 4516: launch(gqsa_panel_kernel<4, 1, true, kMulti, kWaves, kQuads>); break;
+            case 4532: launch(gqsa_panel_kernel<4, 2, true, kMulti, kWaves, kQuads>); break;
+            case 4564: launch(gqsa_panel_kernel<4, 4, true, kMulti, kWaves, kQuads>); break;
+            case 4628: launch(gqsa_panel_kernel<4, 8, true, kMulti, kWaves, kQuads>); break;
+            case 8516: launch(gqsa_panel_kernel<8, 1, true, kMulti, kWaves, kQuads>); break;
+            case 8532: launch(gqsa_panel_kernel<8, 2, true, kMulti, kWaves, kQuads>); break;
+            case 8564: launch(gqsa_panel_kernel<8, 4, true, kMulti, kWaves, kQuads>); break;
             default: return false;
         }
         return true;
     };
     using Whole = std::integral_constant<int, kPanelWaves>;
     using Half = std::integral_constant<int, kPanelWaves / 2>;
-    const bool ok = n > 1 ? pick(std::true_type{}, Whole{})
-                          : (halves ? pick(std::false_type{}, Half{}) : pick(std::false_type{}, Whole{}));
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    const bool ok = n > 1 ? (many ? pick(std::true_type{}, Whole{}, Two{}) : pick(std::true_type{}, Whole{}, One{}))
+                          : (many ? pick(std::false_type{}, Half{}, Two{}) : pick(std::false_type{}, Whole{}, One{}));
     if (!ok) return GQSA_ERR_UNSUPPORTED;
     GQSA_HIP(hipGetLastError());
     return GQSA_OK;

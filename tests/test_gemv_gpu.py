@@ -623,6 +623,53 @@ def test_vocabulary_sized_matrix(torch_cuda):
     gq.gqsa_free(h)
 
 
+@pytest.mark.parametrize("integer_zeros", [True, False])
+@pytest.mark.parametrize("bits,G", [(4, 16), (4, 32), (4, 64), (4, 128), (8, 16), (8, 32), (8, 64)])
+def test_panel_kernel_more_than_four_panels_per_compute_unit(torch_cuda, bits, G, integer_zeros):
+    """Workgroups of up to eight panels: two matrices of 601 + 512 and 601 + 1447 panels in one launch (just
+    beyond four for each of 256 workgroups, and the most there are of eight), the same with one more panel
+    (separate launches), and 1113 panels of one matrix.  Dense rows (a quad's records do not fit their staging
+    area at once) and ragged ones; a sample of rows against the oracle, all rows of the joint launch
+    the bits of separate calls."""
+    torch = torch_cuda
+    K = 4 * 32 * 16 + G if G <= 32 else 2048 + G       # (the last slice is a short one)
+    rng = np.random.default_rng(bits * 1000 + G)
+
+    def packed(panels, seed, dense):
+        n = 16 * panels - 5
+        W = np.tile(gi.dense_weight(96, K, seed=seed), (n // 96 + 1, 1))[:n]
+        keep = np.full(n, K // G) if dense else gi.imbalanced_keep_counts(n, K // G, seed=seed)
+        c = oracle.pack(W, G, bits, keep_per_row=keep)
+        if not integer_zeros:
+            c.zeros = (c.zeros.view(np.float16) + rng.standard_normal(c.nnzg).astype(np.float16)).view(np.uint16)
+        h = gq.gqsa_import(c.rowIndex, c.groups, c.values, c.scales, c.zeros, n, K, G, bits)
+        gq.gqsa_build_panels(h)
+        assert gq.gqsa_info(h)["panel_integer_zeros"] == int(integer_zeros)
+        return h, c
+
+    a, b, c, d, e = (packed(601, 1, True), packed(512, 2, False), packed(1447, 3, False), packed(1448, 4, False),
+                     packed(1113, 5, False))
+    x_np = gi.activations(16, K, seed=31)
+    for batch in (16, 5):
+        x = torch.from_numpy(x_np[:batch].copy()).cuda()
+
+        def run(group):
+            ys = [torch.full((batch, p[1].N), float("nan"), dtype=torch.float16, device="cuda") for p in group]
+            gq.gqsa_gemv_multi([p[0] for p in group], x, ys)
+            torch.cuda.synchronize()
+            return [y.cpu().numpy() for y in ys]
+
+        for group in ((a, b), (a, c), (a, d), (e,)):
+            for (h, packing), y in zip(group, run(group)):
+                ref = oracle.gemv(packing, x_np[:batch], threads=8)
+                for row in range(batch):
+                    assert oracle.rel_error(y[row], ref[row]) <= TOL
+                if len(group) > 1:
+                    alone = run(((h, packing),))[0]
+                    if packing.N <= 16 * 1024:
+                        assert np.array_equal(y.view(np.uint16), alone.view(np.uint16))
+
+
 @pytest.mark.parametrize("bits,G", [(4, 16), (8, 16), (4, 32), (4, 64), (4, 128), (8, 32), (8, 64)])
 @pytest.mark.parametrize("batch", [1, 2, 5, 8, 9, 13, 16])
 def test_panel_kernel_ragged(torch_cuda, bits, G, batch):
