@@ -7,12 +7,11 @@
 // saliency sums in index order, single IEEE fp32 operations in the quantiser, round-half-even),
 // so the results are the same bits.
 //
-// One workgroup per output row.  The row's saliencies live in LDS; which groups go is decided by
-// counting, for every group, the groups that are pruned before it (lower saliency, or equal
-// saliency and lower column): a group is pruned iff that count is below the row's pruned count.
-// A prefix sum over the kept flags gives every kept group its place in the row, and with the
-// row's first stream position (worked out on the host from the row pointers alone) its block and
-// lane in the image.
+// One wavefront per output row.  The saliencies of the row lie in LDS as 64-bit keys (a sum of
+// squares is not negative, so its bit pattern orders like the number); the pruned count-th smallest
+// is found by bisection over the keys' bits, one ballot per 64 columns and step, and the columns
+// that stay are listed in order.  Lane by lane the listed groups are then quantised and written,
+// neighbouring lanes to neighbouring places.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -25,8 +24,8 @@
 namespace gqsa {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kMaxColumns = 4096;      // group-columns of a row (the format's limit)
+constexpr int kThreads = 256;          // of the small kernels
+constexpr int kMaxColumns = 4096;      // group-columns of a row (the format's limit): 40 KB of LDS
 
 struct PackArgs {
     const float* W;            // [N][K]
@@ -40,84 +39,132 @@ struct PackArgs {
     uint8_t* blocks;           // device image, blocks region (zeroed beforehand)
     int* status;               // bit 0: a non-finite saliency; bit 1: a bad entry of hinv; bit 2: a scale beyond fp16
     long long K;
-    int kg, G, bits, cb, U, L, bb, slots_per_group;     // (U blocks per tile, L lanes in use per block)
+    int kg, bits, cb, U, L, bb, slots_per_group;     // (U blocks per tile, L lanes in use per block)
 };
 
 __device__ __forceinline__ uint16_t half_bits(float f) { return __builtin_bit_cast(uint16_t, static_cast<_Float16>(f)); }
 __device__ __forceinline__ float half_value(uint16_t b) { return static_cast<float>(__builtin_bit_cast(_Float16, b)); }
 
-__global__ __launch_bounds__(kThreads) void pack_rows_kernel(PackArgs a)
+// Eight weights.  WIDE: the address is a multiple of 16 bytes (two loads); else any float's.
+template <bool WIDE>
+__device__ __forceinline__ void load8(const float* p, float* w)
 {
-    __shared__ double sal[kMaxColumns];
-    __shared__ uint8_t kept[kMaxColumns];
-    __shared__ int counts[kThreads];
-    __shared__ int bad;
+    if constexpr (WIDE) {
+        const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
+        w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
+        w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = p[e];
+    }
+}
 
-    const int tid = threadIdx.x;
+// A workgroup is one wavefront: its LDS accesses complete in order, this only keeps the compiler
+// from moving them across.
+__device__ __forceinline__ void wavefront_fence() { __syncthreads(); }
+
+// W is read twice (the second time, by the kept groups, mostly from the caches); the 64 MB of 4096x4096 take 11 us
+// at the rate of a plain read, the kernel 36 us: the rest is the bisection's chain of LDS reads and ballots
+// (about 25 steps: a step per leading bit until the pruned count is met exactly) and 17 divisions per kept
+// group.  A workgroup of 256 threads per row that compared every key with every other one, its threads
+// each reading and writing groups of their own, took 101 us, and its time grew with the square of the columns: S = 50 %,
+// W4 G = 16 4096x4096 101 -> 36 us, 2441x16384 595 -> 94 us; W8 G = 8 4096x4096 219 -> 46 us, 4883x8192 at
+// S = 30 % 927 -> 145 us; W4 G = 128 4096x8192 186 -> 65 us; W4 G = 32 40000x1024 at S = 70 % 454 -> 98 us.
+template <int G, bool WIDE>
+__global__ __launch_bounds__(kLanes) void pack_rows_kernel(PackArgs a)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int kg = a.kg;
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(lds);      // [kg]
+    uint16_t* list = reinterpret_cast<uint16_t*>(lds + static_cast<size_t>(kg) * 8);    // [kept groups] their columns
+
+    const int lane = threadIdx.x;
     const long long n = blockIdx.x;
     const float* wrow = a.W + n * a.K;
     const int g0 = a.rowIndex[n];
     const int keep = a.rowIndex[n + 1] - g0;
-    const int kg = a.kg, G = a.G;
-    if (keep == 0) return;                                  // (uniform: the whole workgroup leaves)
+    if (keep == 0) return;                                  // (uniform: the whole wavefront leaves)
     const int drop = kg - keep;
-    // every thread owns a contiguous run of group-columns
-    const int chunk = (kg + kThreads - 1) / kThreads;
-    const int c_begin = min(kg, tid * chunk), c_end = min(kg, c_begin + chunk);
 
-    if (tid == 0) bad = 0;
-    __syncthreads();
     // saliency of a weight: w^2 / d_k^2; of a group: the sum over its members, float64, index order
-    for (int c = c_begin; c < c_end; ++c) {
+    bool bad = false;
+    for (int c = lane; c < kg; c += kLanes) {
         const float* p = wrow + static_cast<long long>(c) * G;
         double acc = 0.0;
-        if (a.hinv) {
-            const float* d = a.hinv + static_cast<long long>(c) * G;
-            for (int j = 0; j < G; ++j) {
-                const double t = static_cast<double>(p[j]) / static_cast<double>(d[j]);
-                acc += t * t;
+#pragma unroll
+        for (int h = 0; h < G / 8; ++h) {
+            float w[8];
+            load8<WIDE>(p + 8 * h, w);
+            if (a.hinv) {
+                const float* d = a.hinv + static_cast<long long>(c) * G + 8 * h;
+                for (int e = 0; e < 8; ++e) {
+                    const double t = static_cast<double>(w[e]) / static_cast<double>(d[e]);
+                    acc += t * t;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc += static_cast<double>(w[e]) * static_cast<double>(w[e]);
             }
-        } else {
-            for (int j = 0; j < G; ++j) acc += static_cast<double>(p[j]) * static_cast<double>(p[j]);
         }
-        sal[c] = acc;
-        if (!(fabs(acc) <= 1.79769313486231570815e+308)) bad = 1;     // NaN or infinite
+        keys[c] = __builtin_bit_cast(unsigned long long, acc);
+        bad = bad || !(fabs(acc) <= 1.79769313486231570815e+308);     // NaN or infinite
     }
-    __syncthreads();
-    if (bad) {
-        if (tid == 0) atomicOr(a.status, 1);
+    if (__ballot(bad) != 0) {
+        if (lane == 0) atomicOr(a.status, 1);
         return;
     }
-    // a group is pruned iff fewer than `drop` groups come before it in the order of pruning
-    int mine = 0;
-    for (int c = c_begin; c < c_end; ++c) {
-        bool k = true;
-        if (drop > 0) {
-            const double s = sal[c];
-            int before = 0;
-            for (int o = 0; o < kg; ++o) {
-                const double so = sal[o];
-                before += (so < s || (so == s && o < c)) ? 1 : 0;
-            }
-            k = before >= drop;
-        }
-        kept[c] = k ? 1 : 0;
-        mine += k ? 1 : 0;
-    }
-    counts[tid] = mine;
-    __syncthreads();
-    // place of this thread's first kept group in the row: kept groups of the threads before it
-    int place = 0;
-    for (int t = 0; t < tid; ++t) place += counts[t];
+    wavefront_fence();
 
+    // The pruned groups are the `drop` first ones in the order (saliency, column).  Bisection from the
+    // top bit down (bit 63, the sign, is clear): `low` = the largest number found so far with at most `drop`
+    // keys below it, bit by bit; once exactly `drop` keys lie below it, no tie is left to decide.
+    unsigned long long low = 0;
+    int below = 0;             // keys less than low
+    if (drop > 0) {
+        for (int bit = 62; bit >= 0 && below != drop; --bit) {
+            const unsigned long long candidate = low | (1ull << bit);
+            int count = 0;
+            for (int c = lane; c - lane < kg; c += kLanes)
+                count += __popcll(__ballot(c < kg && keys[c] < candidate));
+            if (count <= drop) {
+                low = candidate;
+                below = count;
+            }
+        }
+    }
+    // pruned: the keys below `low`, and of those equal to it the first drop - below by column
+    int ties_left = drop - below, kept_before = 0;
+    for (int base = 0; base < kg; base += kLanes) {
+        const int c = base + lane;
+        const unsigned long long key = c < kg ? keys[c] : 0;
+        const unsigned long long lanes_below = (1ull << lane) - 1ull;
+        const unsigned long long equal = __ballot(c < kg && key == low);
+        const bool tie_goes = ((equal >> lane) & 1ull) != 0 && static_cast<int>(__popcll(equal & lanes_below)) < ties_left;
+        const bool stays = c < kg && key >= low && !tie_goes;
+        const unsigned long long staying = __ballot(stays);
+        if (stays) list[kept_before + __popcll(staying & lanes_below)] = static_cast<uint16_t>(c);
+        kept_before += __popcll(staying);
+        ties_left -= min(ties_left, static_cast<int>(__popcll(equal)));
+    }
+    wavefront_fence();
+
+    // where the row begins in the image: tiles of U blocks of L groups, lane l owns U consecutive positions
+    const int tile_groups = a.L * a.U;
+    const long long tile0 = a.row_pos[n] / tile_groups;
+    const int first = static_cast<int>(a.row_pos[n] % tile_groups);
+    constexpr float kMinScale = 0x1p-14f;
     const float levels = static_cast<float>((1 << a.bits) - 1);
-    for (int c = c_begin; c < c_end; ++c) {
-        if (!kept[c]) continue;
-        const int i = place++;                      // the group's number inside its row
+    const int cb = a.cb, pb = cb < 16 ? cb : 16;
+    for (int i = lane; i < keep; i += kLanes) {         // i = the group's number inside its row
+        const int c = list[i];
         const long long g = static_cast<long long>(g0) + i;
-        const float* w = wrow + static_cast<long long>(c) * G;
+        const float* p = wrow + static_cast<long long>(c) * G;
+        float w[G];
+#pragma unroll
+        for (int h = 0; h < G / 8; ++h) load8<WIDE>(p + 8 * h, w + 8 * h);
         // Eq. 1: the first smallest and the last largest element, as the host's scan finds them
         float lo = w[0], hi = w[0];
+#pragma unroll
         for (int j = 1; j < G; ++j) {
             if (w[j] < lo) lo = w[j];
             if (!(w[j] < hi)) hi = w[j];
@@ -126,7 +173,6 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(PackArgs a)
         uint16_t sb = half_bits(s);
         if ((sb & 0x7FFFu) >= 0x7C00u) atomicOr(a.status, 4);      // the group's range is beyond what an fp16 scale holds
         s = half_value(sb);
-        const float kMinScale = 0x1p-14f;
         if (!(s >= kMinScale)) {
             s = kMinScale;
             sb = half_bits(s);
@@ -138,19 +184,18 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(PackArgs a)
         a.groups[g] = c;
         a.scales[g] = sb;
         a.zeros[g] = zb;
-        // where the group sits in the image: tile of U blocks, lane l owns U consecutive positions
-        const long long pos = a.row_pos[n] + i;
-        const long long tile_groups = static_cast<long long>(a.L) * a.U;
-        const long long p = pos % tile_groups;
-        const long long block = pos / tile_groups * a.U + p % a.U;
-        const int lane = static_cast<int>(p / a.U);
+        const int place = first + i;                // of the group, counted from the start of the row's first tile
+        const int position = place % tile_groups;
+        const long long block = (tile0 + place / tile_groups) * a.U + position % a.U;
+        const int slot = position / a.U;
         uint8_t* base = a.blocks + block * a.bb;
-        const int cb = a.cb, pb = cb < 16 ? cb : 16;
         uint8_t* vout = a.values + g * cb;
         // Eq. 2, eight codes at a time: a canonical word (two codes per byte, even element low; or
         // one byte per code) and the image's word (4-bit: element 2m at bits 4m, 2m+1 at 16+4m)
-        for (int h = 0; h < G / 8 + (G < 8 ? 1 : 0); ++h) {
+#pragma unroll
+        for (int h = 0; h < G / 8; ++h) {
             uint32_t q8[8];
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float q = __builtin_rintf(w[8 * h + e] / s) + z;
                 q = (0.0f < q) ? q : 0.0f;
@@ -159,26 +204,40 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(PackArgs a)
             }
             if (a.bits == 4) {
                 uint32_t canon = 0, image = 0;
+#pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     canon |= q8[e] << (4 * e);
                     image |= q8[e] << ((e & 1) ? 16 + 4 * (e >> 1) : 4 * (e >> 1));
                 }
                 *reinterpret_cast<uint32_t*>(vout + 4 * h) = canon;
                 const int byte = 4 * h;             // of the lane's code string
-                *reinterpret_cast<uint32_t*>(base + (byte / pb) * a.L * pb + lane * pb + byte % pb) = image;
+                *reinterpret_cast<uint32_t*>(base + (byte / pb) * a.L * pb + slot * pb + byte % pb) = image;
             } else {
+#pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     const uint32_t word = q8[4 * half] | (q8[4 * half + 1] << 8) | (q8[4 * half + 2] << 16) | (q8[4 * half + 3] << 24);
                     const int byte = 8 * h + 4 * half;
                     *reinterpret_cast<uint32_t*>(vout + byte) = word;
-                    *reinterpret_cast<uint32_t*>(base + (byte / pb) * a.L * pb + lane * pb + byte % pb) = word;
+                    *reinterpret_cast<uint32_t*>(base + (byte / pb) * a.L * pb + slot * pb + byte % pb) = word;
                 }
             }
         }
-        *reinterpret_cast<uint32_t*>(base + a.L * cb + lane * 4) = static_cast<uint32_t>(sb) | (static_cast<uint32_t>(zb) << 16);
-        *reinterpret_cast<uint16_t*>(base + a.L * (cb + 4) + lane * 2) =
+        *reinterpret_cast<uint32_t*>(base + a.L * cb + slot * 4) = static_cast<uint32_t>(sb) | (static_cast<uint32_t>(zb) << 16);
+        *reinterpret_cast<uint16_t*>(base + a.L * (cb + 4) + slot * 2) =
             static_cast<uint16_t>(((c * a.slots_per_group) << 4) | (i == 0 ? 1 : 0));
     }
+}
+
+template <int G>
+void launch_pack_rows(const PackArgs& a, int64_t n_rows, hipStream_t s)
+{
+    const size_t lds = static_cast<size_t>(a.kg) * 10;
+    const dim3 grid(static_cast<unsigned>(n_rows)), block(kLanes);
+    // (K is a multiple of 16: with an aligned W every group of every row is aligned)
+    if ((reinterpret_cast<uintptr_t>(a.W) & 15u) == 0)
+        hipLaunchKernelGGL((pack_rows_kernel<G, true>), grid, block, lds, s, a);
+    else
+        hipLaunchKernelGGL((pack_rows_kernel<G, false>), grid, block, lds, s, a);
 }
 
 __global__ __launch_bounds__(kThreads) void check_hinv_kernel(const float* d, long long K, int* status)
@@ -251,7 +310,6 @@ gqsa_status_t pack_on_device(const float* W_dev, const float* hinv_dev, gqsa_mat
     a.status = static_cast<int*>(tmp.p[6]);
     a.K = m->K;
     a.kg = static_cast<int>(m->K / m->G);
-    a.G = m->G;
     a.bits = m->bits;
     a.cb = cb;
     a.U = m->tile_blocks;
@@ -261,7 +319,14 @@ gqsa_status_t pack_on_device(const float* W_dev, const float* hinv_dev, gqsa_mat
     if (hinv_dev)
         hipLaunchKernelGGL(check_hinv_kernel, dim3(static_cast<unsigned>((m->K + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                            hinv_dev, static_cast<long long>(m->K), a.status);
-    hipLaunchKernelGGL(pack_rows_kernel, dim3(static_cast<unsigned>(m->N)), dim3(kThreads), 0, s, a);
+    switch (m->G) {
+        case 8: launch_pack_rows<8>(a, m->N, s); break;
+        case 16: launch_pack_rows<16>(a, m->N, s); break;
+        case 32: launch_pack_rows<32>(a, m->N, s); break;
+        case 64: launch_pack_rows<64>(a, m->N, s); break;
+        case 128: launch_pack_rows<128>(a, m->N, s); break;
+        default: return GQSA_ERR_UNSUPPORTED;
+    }
     GQSA_HIP(hipGetLastError());
     int status = 0;
     GQSA_HIP(hipMemcpyAsync(&status, tmp.p[6], 4, hipMemcpyDeviceToHost, s));

@@ -189,3 +189,33 @@ def test_group_range_beyond_an_fp16_scale_is_refused_on_the_gpu(torch_cuda):
     with pytest.raises(gq.GqsaError) as e:
         gq.gqsa_pack_device(torch_cuda.from_numpy(W).cuda(), 16, 4, 0.0)
     assert e.value.status == 4
+
+
+@pytest.mark.parametrize("columns", [1, 2, 63, 64, 65, 130, 2048, 4096])
+@pytest.mark.parametrize("G", [8, 16, 128])
+def test_selection_at_the_edges_of_64_columns_with_ties(torch_cuda, columns, G):
+    """Rows of 1 to 4096 groups (the selection takes 64 at a time), every kept count at the edges, many groups
+    of equal saliency on both sides of the cut, and weights whose address is no multiple of 16 bytes."""
+    torch = torch_cuda
+    if columns * G % 16 or columns * G > 32768:
+        pytest.skip("not a size the format has")
+    rng = np.random.default_rng(columns * 1000 + G)
+    keeps = sorted({0, 1, columns // 3, columns // 2, columns - 1, columns})
+    few = rng.standard_normal((3, G)).astype(np.float32)       # three patterns: thousands of ties
+    rows = []
+    for _ in keeps:
+        w = rng.standard_normal((columns, G)).astype(np.float32)
+        tied = few[rng.integers(0, 3, columns)]
+        rows += [w.ravel(), tied.ravel(), np.where(rng.random(columns)[:, None] < 0.5, tied, w).ravel(), np.zeros(columns * G, np.float32)]
+    W = np.stack(rows).astype(np.float32)
+    keep = np.repeat(np.asarray(keeps, dtype=np.int32), 4)
+    c = oracle.pack(W, G, 4, keep_per_row=keep)
+    for offset in (0, 1):
+        buf = torch.empty(W.size + 4, dtype=torch.float32, device="cuda")
+        Wd = buf[offset:offset + W.size].view(W.shape)
+        Wd.copy_(torch.from_numpy(W))
+        h = gq.gqsa_pack_device(Wd, G, 4, 0.0, keep_per_row=keep)
+        e = gq.gqsa_export(h)
+        for name in ("rowIndex", "groups", "values", "scales", "zeros"):
+            assert np.array_equal(e[name], getattr(c, name)), (name, offset)
+        assert gq.gqsa_export_device_blob(h) == oracle.device_blob_for(c, gq.gqsa_info(h))
