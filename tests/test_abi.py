@@ -196,6 +196,26 @@ def test_info_fields():
     assert info["algorithmic_bytes"] == nnz * 22 + 101 * 4 + (512 + 100) * 2
 
 
+def test_a_freed_handle_is_refused_whatever_was_known_of_it():
+    """The binding keeps a handle's (N, K) after the first call that needs it, and forgets it with the handle."""
+    class Rows:                     # the checks on the shape come before anything looks at the data
+        shape = (1, 64)
+
+        def dim(self):
+            return 2
+
+    h = gq.gqsa_pack(gi.dense_weight(4, 64, seed=1), 16, 4, 0.5)
+    with pytest.raises(ValueError):
+        gq.gqsa_gemv(h, Rows(), Rows())           # y is not [1, 4]
+    assert h.shape == (4, 64)
+    gq.gqsa_free(h)
+    for call in (lambda: gq.gqsa_gemv(h, Rows(), Rows()), lambda: gq.gqsa_gemv_static(h, Rows(), Rows()),
+                 lambda: gq.gqsa_gemv_multi([h], Rows(), [Rows()])):
+        with pytest.raises(gq.GqsaError) as e:
+            call()
+        assert e.value.status == 1
+
+
 def test_pack_hessian_argument_checks():
     W = np.ones((4, 64), dtype=np.float32)
     d = np.ones(64, dtype=np.float32)
