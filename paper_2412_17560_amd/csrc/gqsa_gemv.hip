@@ -303,7 +303,8 @@ __device__ __forceinline__ void store_row(const MatArgs& m, int b, int rank, flo
 // U_ > 0 (FLEX): U_ blocks of L groups each, L <= 64 given at launch -- the same three arrays
 // with L entries, the lanes from L on take no group (partitions that keep whole rows inside a
 // wavefront's run choose U_ and L so that the rows fill the tiles).
-template <int BITS_, int M_, int U_ = 0>
+// SPREAD_ (group size 16): the slots of x change places in LDS as larger groups' do (compute_tile).
+template <int BITS_, int M_, int U_ = 0, bool SPREAD_ = false>
 struct Fmt {
     static constexpr bool FLEX = U_ != 0;
     static constexpr int BITS = BITS_;
@@ -312,6 +313,9 @@ struct Fmt {
     static constexpr int CB = (HALF ? 8 : 16 * M_) * BITS_ / 8;   // code bytes per group
     static constexpr int CW = CB / 4;                    // code words per group
     static constexpr int CWC = HALF ? CW : CW / (M_ ? M_ : 1);    // code words per chunk (2 or 4; half chunk: 1 or 2)
+    static constexpr bool SPREAD = SPREAD_;
+    static constexpr uint32_t SLOT_MASK = M_ > 1 ? M_ - 1 : (SPREAD_ ? 15 : 0);   // which low bits of a slot's number higher ones change
+    static constexpr uint32_t SUM_MASK = M_ > 1 ? M_ - 1 : 0;                     // ... and of its sum's
     static constexpr int PB = CB < 16 ? CB : 16;         // bytes per lane in one code plane
     static constexpr int PLANES = CB / PB;
     static constexpr int UMAX = U_ ? U_ : largest_tile(CB);   // blocks of a tile
@@ -452,6 +456,13 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 // The bits taken are the same for all chunks of a group, so a lane works them out once per group.
 // (14336x4096 W4 at 1 / 2 / 4 rows: G = 32 6.1 / 8.1 / 13.9 -> 6.1 / 7.6 / 11.5 us, G = 64 6.2 / 9.5 / 16.9 ->
 // 5.8 / 7.0 / 10.2 us, G = 128 7.3 / 12.1 / 22.1 -> 5.5 / 6.8 / 9.4 us.)
+//
+// At G = 16 the lanes' slots are as far apart as the rows' gaps make them, except in unpruned rows: there a
+// lane's four groups are neighbours and the lanes' u-th ones 4 slots apart, in a quarter of the banks.
+// The kernels for several rows, which LDS bounds, come in a form for such matrices (SPREAD: slot s at
+// s xor ((s / 16) mod 16)): 14336x4096 W4 without pruning at 2 / 4 / 8 rows 14.6 / 22.4 / 52.7 -> 13.9 / 18.6 /
+// 38.9 us.  At S = 50 % it gains nothing and costs what its address arithmetic takes (1024x4096 at 4 / 8
+// rows 4.6 / 7.3 -> 4.75 / 7.75 us), so pruned matrices keep the plain form.
 //
 // EAGER: the tile's loads may still be in flight.  All gathers are issued first (they need only
 // the index words, the first of the tile's loads to arrive), then the groups are decoded block
@@ -614,8 +625,8 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                 }
             }
             // (where the group's chunk 0 lies and its sum; those of chunk i differ in the bits of i)
-            const uint32_t slot0 = F::M > 1 ? slot | ((slot >> 4) & ((F::M - 1) * 16u)) : slot;
-            const uint32_t sum0 = F::M > 1 ? (slot >> 2) | ((slot >> 8) & ((F::M - 1) * 4u)) : slot >> 2;
+            const uint32_t slot0 = slot ^ ((slot >> 4) & (F::SLOT_MASK * 16u));
+            const uint32_t sum0 = (slot >> 2) ^ ((slot >> 8) & (F::SUM_MASK * 4u));
 #pragma unroll
             for (int i = 0; i < F::M; ++i) {                // the group's 16-element chunks
                 Codes c;
@@ -934,8 +945,8 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
         const int b = NB == 1 ? 0 : c / kg;
         const int column = c - b * kg;
         // (where the slot and its sum lie: see compute_tile)
-        const int at = F::M > 1 ? column ^ ((column >> 4) & (F::M - 1)) : column;
-        const int sum_at = F::M > 1 ? column ^ ((column >> 6) & (F::M - 1)) : column;
+        const int at = column ^ ((column >> 4) & static_cast<int>(F::SLOT_MASK));
+        const int sum_at = column ^ ((column >> 6) & static_cast<int>(F::SUM_MASK));
         uint8_t* slot = xlds + b * (48 * KGP) + at * 16;
         *reinterpret_cast<uint4*>(slot) = lo;
         *reinterpret_cast<uint4*>(slot + 16 * KGP) = hi;
@@ -1088,7 +1099,9 @@ template <typename F, int KGP>
 Variant pick_variant(int nb)
 {
     switch (nb) {
-        case 1: return variant_if_it_fits<F, KGP, 1>();
+        case 1:
+            if constexpr (F::SPREAD) return Variant{};       // (one row: LDS does not bound it)
+            else return variant_if_it_fits<F, KGP, 1>();
         case 2: return variant_if_it_fits<F, KGP, 2>();
         case 4: return variant_if_it_fits<F, KGP, 4>();
         case 8: return variant_if_it_fits<F, KGP, 8>();
@@ -1169,7 +1182,8 @@ Variant GQSA_PART_NAME(int bits, int u, int slots, int nb, int* kgp)
 
 #else   // GQSA_GEMV_PART == 0: the formats' own tile sizes, and the host side
 
-Variant pick(const gqsa_matrix* m, int nb, int* kgp)
+// spread: the form for unpruned matrices (Fmt::SPREAD), where there is one.
+Variant pick(const gqsa_matrix* m, int nb, int* kgp, bool spread = false)
 {
     const int slots = static_cast<int>(m->K / 16);
     *kgp = 0;
@@ -1181,6 +1195,8 @@ Variant pick(const gqsa_matrix* m, int nb, int* kgp)
             if (Variant v = part(m->bits, m->tile_blocks, slots, nb, kgp)) return v;
         return Variant{};
     }
+    if (m->G == 16 && spread && nb > 1)
+        return m->bits == 4 ? pick_kernel<Fmt<4, 1, 0, true>>(slots, nb, kgp) : pick_kernel<Fmt<8, 1, 0, true>>(slots, nb, kgp);
     if (m->G == 16)
         return m->bits == 4 ? pick_kernel<Fmt<4, 1>>(slots, nb, kgp) : pick_kernel<Fmt<8, 1>>(slots, nb, kgp);
     Variant (*const parts[4])(int, int, int, int, int*) = {group_variant_part5, group_variant_part6, group_variant_part7,
@@ -1189,6 +1205,9 @@ Variant pick(const gqsa_matrix* m, int nb, int* kgp)
         if (Variant v = part(m->bits, m->G / 16, slots, nb, kgp)) return v;
     return Variant{};
 }
+
+// Stored groups that are neighbours in their rows, or nearly all of them: seven in eight.
+bool unpruned(const gqsa_matrix* m) { return m->nnzg() * 8 >= m->N * (m->K / m->G) * 7; }
 
 constexpr size_t counters_offset(int n_waves)
 {
@@ -1222,15 +1241,18 @@ gqsa_status_t device_upload(gqsa_matrix* m, void* filled_image)
     if (!pick(m, 1, &kgp)) return GQSA_ERR_UNSUPPORTED;   // K/16 above 2048: x does not fit the LDS layout
     int dev = 0;
     GQSA_HIP(hipGetDevice(&dev));
-    for (int nb = 1; nb <= kMaxRowsPerLaunch; nb *= 2) {
-        Variant v = pick(m, nb, &kgp);
-        if (!v) continue;
-        hipFuncAttributes attr{};
-        GQSA_HIP(hipFuncGetAttributes(&attr, v.fn));
-        if (attr.sharedSizeBytes != 0) return GQSA_ERR_HIP;      // the kernel addresses x from LDS offset 0
-        if (lds_bytes(kgp, nb) > 64 * 1024)
-            GQSA_HIP(hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(lds_bytes(kgp, nb))));
+    const bool spread = unpruned(m);      // (the form the launches of this matrix take, the other one where it shares a launch with a pruned one)
+    for (int form = 0; form <= (spread ? 1 : 0); ++form) {
+        for (int nb = 1; nb <= kMaxRowsPerLaunch; nb *= 2) {
+            Variant v = pick(m, nb, &kgp, form == 1);
+            if (!v) continue;
+            hipFuncAttributes attr{};
+            GQSA_HIP(hipFuncGetAttributes(&attr, v.fn));
+            if (attr.sharedSizeBytes != 0) return GQSA_ERR_HIP;      // the kernel addresses x from LDS offset 0
+            if (lds_bytes(kgp, nb) > 64 * 1024)
+                GQSA_HIP(hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             static_cast<int>(lds_bytes(kgp, nb))));
+        }
     }
     void* img = filled_image;
     void* carry = nullptr;
@@ -1303,7 +1325,9 @@ gqsa_status_t launch(gqsa_matrix* const* ms, int n_mats, const uint16_t* x, uint
 {
     const gqsa_matrix* m0 = ms[0];
     int kgp = 0;
-    const Variant v = pick(m0, nb, &kgp);
+    bool all_unpruned = true;
+    for (int i = 0; i < n_mats; ++i) all_unpruned = all_unpruned && unpruned(ms[i]);
+    const Variant v = pick(m0, nb, &kgp, all_unpruned);
     if (!v) return GQSA_ERR_UNSUPPORTED;
     LaunchArgs a{};
     int wg_end[kMaxMatrices] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};

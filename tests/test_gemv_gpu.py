@@ -513,6 +513,37 @@ def test_other_group_sizes_small_batches(torch_cuda, bits, G, K, part):
     assert (buf[7] == 7.0).all()
 
 
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("K", [16, 256, 4096, 4176, 8192, 8208])
+def test_small_batches_of_unpruned_matrices(torch_cuda, bits, K):
+    """Unpruned matrices have kernels of their own for several rows: every batch against the oracle, each row the
+    single-row bits, on both sides of the share of stored groups (seven in eight) that decides, and in one
+    launch with a pruned matrix."""
+    torch = torch_cuda
+    N, columns = 72, K // 16
+    W = gi.dense_weight(N, K, seed=93)
+    x16 = gi.activations(16, K, seed=13)
+    full = np.full(N, columns)
+    edge = np.full(N, (columns * 7 + 7) // 8)          # just within
+    below = edge - 1
+    pruned = np.full(N, columns // 2)
+    hs = [gq.gqsa_pack_rows(W, keep, 16, bits) for keep in (full, edge, below, pruned)]
+    cs = [oracle.pack(W, 16, bits, keep_per_row=keep) for keep in (full, edge, below, pruned)]
+    gq.gqsa_set_partition(hs[3], 3, 2)          # (several tiles to a worker)
+    for h, c in zip(hs, cs):
+        rows = np.concatenate([run_gemv(torch, h, x16[b:b + 1]) for b in range(16)])
+        for batch in (2, 3, 4, 7, 8, 13):
+            y, _ = check(torch, h, c, x16[:batch])
+            assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
+    x = torch.from_numpy(x16[:4].copy()).cuda()
+    for group in ((0, 2), (0, 1), (0, 1, 2, 3)):
+        ys = [torch.full((4, N), float("nan"), dtype=torch.float16, device="cuda") for _ in group]
+        gq.gqsa_gemv_multi([hs[i] for i in group], x, ys)
+        torch.cuda.synchronize()
+        for i, y in zip(group, ys):
+            assert np.array_equal(y.cpu().numpy().view(np.uint16), run_gemv(torch, hs[i], x16[:4]).view(np.uint16))
+
+
 @pytest.mark.parametrize("G", [8, 32, 64, 128])
 def test_other_group_sizes_full_size_and_sparsities(torch_cuda, G):
     """4096x4096 W4 at G = 32, 64, 128, S = 0 and 50 %, default partition."""
