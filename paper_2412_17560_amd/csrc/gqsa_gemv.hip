@@ -1111,11 +1111,17 @@ Variant pick_variant(int nb)
 
 // The kernel is compiled for counts of 16-element activation slots (K/16) rounded up to a power
 // of two (the LDS offsets between the x arrays are immediates).
+// Four rows of 512 < K/16 <= 768 slots fit LDS (147 KB), but not rounded up to 1024 (196 KB): as
+// two launches of two rows they read and decoded the matrix twice.  4096x11008 at 3 / 4 / 8 rows, W4
+// S = 50 %: 13.9 / 14.6 / 27.1 -> 11.8 / 12.2 / 21.7 us; 4 rows of 1024x8320 14.1 -> 10.9, 14336x11008 52.5 ->
+// 42.9 (3 rows 41.5 -> 42.2, the one size where a row and two more were as fast; 20000x11008 45.3 -> 41.1),
+// 8192x10240 W8 32.6 -> 23.5, 4096x11008 G = 64 22.5 -> 12.6, G = 8 29.7 -> 18.3 us.
 template <typename F>
 Variant pick_kernel(int slots, int nb, int* kgp)
 {
     if (slots <= 256) { *kgp = 256; return pick_variant<F, 256>(nb); }
     if (slots <= 512) { *kgp = 512; return pick_variant<F, 512>(nb); }
+    if (slots <= 768 && nb == 4) { *kgp = 768; return variant_if_it_fits<F, 768, 4>(); }
     if (slots <= 1024) { *kgp = 1024; return pick_variant<F, 1024>(nb); }
     if (slots <= 2048) { *kgp = 2048; return pick_variant<F, 2048>(nb); }
     *kgp = 0;

@@ -544,6 +544,22 @@ def test_small_batches_of_unpruned_matrices(torch_cuda, bits, K):
             assert np.array_equal(y.cpu().numpy().view(np.uint16), run_gemv(torch, hs[i], x16[:4]).view(np.uint16))
 
 
+@pytest.mark.parametrize("bits,G,sparsity", [(4, 16, 0.5), (4, 16, 0.0), (8, 16, 0.3), (4, 8, 0.5), (4, 32, 0.5), (8, 64, 0.3), (4, 128, 0.5)])
+@pytest.mark.parametrize("K", [8192, 8320, 11008, 12288, 12416])
+def test_four_rows_between_8192_and_12288_columns(torch_cuda, bits, G, sparsity, K):
+    """Four copies of x fit LDS up to K = 12288 in a form of their own: every batch against the oracle, each row the
+    single-row bits, at both ends of its range and on either side of them."""
+    torch = torch_cuda
+    W = gi.dense_weight(200, K, seed=95)
+    x16 = gi.activations(8, K, seed=14)
+    h = gq.gqsa_pack(W, G, bits, sparsity)
+    c = oracle.pack(W, G, bits, sparsity)
+    rows = np.concatenate([run_gemv(torch, h, x16[b:b + 1]) for b in range(8)])
+    for batch in (2, 3, 4, 5, 7, 8):
+        y, _ = check(torch, h, c, x16[:batch])
+        assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
+
+
 @pytest.mark.parametrize("G", [8, 32, 64, 128])
 def test_other_group_sizes_full_size_and_sparsities(torch_cuda, G):
     """4096x4096 W4 at G = 32, 64, 128, S = 0 and 50 %, default partition."""
