@@ -296,6 +296,17 @@ __device__ __forceinline__ void store_row(const MatArgs& m, int b, int rank, flo
     m.y[static_cast<size_t>(b) * m.N + row] = float_to_half_bits(v);
 }
 
+// Bytes of LDS from one activation row to the next: 48 per slot, or, where NB rows would not fit then, the 36
+// that 16 activations and their sum take (G = 8 has two sums: no room to spare).  That makes one launch of
+// 4 rows of 12288 < K <= 16384, of 8 rows of 4096 < K <= 8192 and of 2 rows of K > 16384, which went out as two:
+// 4 rows of 4096x14336 17.8 -> 15.3 us, 14336x14336 66.7 -> 55.3; 8 rows of 5120x5120 21.4 -> 18.3, 20000x6144
+// 58.2 -> 51.5, 8192x8192 27.2 -> 25.0, 4096x8192 W8 G = 64 15.6 -> 14.1.  (36 everywhere: 4096x4096 W8 at 8 rows
+// 10.15 -> 10.75.)
+__host__ __device__ constexpr int row_bytes(int kgp, int nb, bool half_groups)
+{
+    return kgp * (!half_groups && nb * 48 * kgp > 156 * 1024 ? 36 : 48);
+}
+
 // Storage format of a group as the kernel is compiled for it: code width, group size
 // G = 16 * M, or G = 8 (M = 0: half a chunk), and blocks per tile.  U_ = 0: the format's own
 // count, and a block holds 64 groups, one per lane: the code bytes in planes of at most 16 bytes
@@ -445,7 +456,7 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 // as a dense array of floats at 32*KGP (4 bytes per column: a wavefront's 64 reads of it spread
 // over all banks instead of a quarter of them; with one 16-byte slot per sum the three reads of
 // a group would share an address and save a shift, but the kernels for several activation rows,
-// which LDS bounds, took 5 % longer).  Row b starts at b * 48 * KGP.  (G = 8: the same
+// which LDS bounds, took 5 % longer).  Row b starts at b * row_bytes.  (G = 8: the same
 // two arrays -- a group's 8 activations are one slot of the first or of the second -- and a sum
 // per half-slot, 8 bytes per column.)
 //
@@ -617,8 +628,8 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                 const uint32_t xoff = ((slot >> 5) << 4) + ((slot >> 4) & 1u) * (16 * KGP);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const uint4 xl = lds_read16(x0 + xoff + b * (48 * KGP));
-                    const float xs = lds_read_float(x0 + b * (48 * KGP) + 32 * KGP + (slot >> 2));
+                    const uint4 xl = lds_read16(x0 + xoff + b * row_bytes(KGP, NB, F::HALF));
+                    const float xs = lds_read_float(x0 + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + (slot >> 2));
                     float lo = 0.0f, hi = 0.0f;
                     lo = dot8<F::BITS>(&c.q[0], xl, lo, hi);
                     dotz[b] = __builtin_fmaf(-z, xs, join<F::BITS>(lo, hi));
@@ -634,10 +645,10 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                 const uint32_t sloti = slot0 ^ (16u * i);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const uint32_t xb = x0 + sloti + b * (48 * KGP);
+                    const uint32_t xb = x0 + sloti + b * row_bytes(KGP, NB, F::HALF);
                     const uint4 xl = lds_read16(xb);
                     const uint4 xh = lds_read16(xb + 16 * KGP);
-                    const float xs = lds_read_float(x0 + b * (48 * KGP) + 32 * KGP + (sum0 ^ (4u * i)));
+                    const float xs = lds_read_float(x0 + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + (sum0 ^ (4u * i)));
                     const float d = __builtin_fmaf(-z, xs, dot16<F::BITS>(c, xl, xh));
                     dotz[b] = i == 0 ? d : dotz[b] + d;
                 }
@@ -871,9 +882,9 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
     const uint16_t* x, const uint8_t* blocks0, const int4_t* wave_info0, unsigned long long magic0, int base0, int extra0,
     int kg_wpw, int wg_end0, int wg_end1, int wg_end2, LaunchArgs a)
 {
-    // x arrays (NB * 48 * KGP bytes), then what the wavefronts tell each other about shared rows
+    // x arrays (NB rows of row_bytes), then what the wavefronts tell each other about shared rows
     extern __shared__ __align__(16) uint8_t xlds[];
-    LdsRecord* rec = reinterpret_cast<LdsRecord*>(xlds + NB * 48 * KGP);        // [wavefront][NB]
+    LdsRecord* rec = reinterpret_cast<LdsRecord*>(xlds + NB * row_bytes(KGP, NB, F::HALF));        // [wavefront][NB]
 
     const int kg = kg_wpw & 0xFFFF;       // 16-element slots of K
     const int wpw = (kg_wpw >> 16) & 0x1F;    // wavefronts per workgroup
@@ -947,7 +958,7 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
         // (where the slot and its sum lie: see compute_tile)
         const int at = column ^ ((column >> 4) & static_cast<int>(F::SLOT_MASK));
         const int sum_at = column ^ ((column >> 6) & static_cast<int>(F::SUM_MASK));
-        uint8_t* slot = xlds + b * (48 * KGP) + at * 16;
+        uint8_t* slot = xlds + b * row_bytes(KGP, NB, F::HALF) + at * 16;
         *reinterpret_cast<uint4*>(slot) = lo;
         *reinterpret_cast<uint4*>(slot + 16 * KGP) = hi;
         const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -959,12 +970,12 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
                 s0 = __builtin_amdgcn_fdot2(as_half2(w[i]), ones, s0, false);
                 s1 = __builtin_amdgcn_fdot2(as_half2(w[4 + i]), ones, s1, false);
             }
-            *reinterpret_cast<float2*>(xlds + b * (48 * KGP) + 32 * KGP + sum_at * 8) = float2{s0, s1};
+            *reinterpret_cast<float2*>(xlds + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + sum_at * 8) = float2{s0, s1};
         } else {
             float s = 0.0f;      // sum of the slot's 16 activations, fp32: a pair per instruction
 #pragma unroll
             for (int i = 0; i < 8; ++i) s = __builtin_amdgcn_fdot2(as_half2(w[i]), ones, s, false);
-            *reinterpret_cast<float*>(xlds + b * (48 * KGP) + 32 * KGP + sum_at * 4) = s;
+            *reinterpret_cast<float*>(xlds + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + sum_at * 4) = s;
         }
     };
     // x into LDS (the loads of the tiles are already out), then the workgroup meets
@@ -1062,9 +1073,9 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
                      st.lead, st.carry, rec, lane, wl, wpw, worker);
 }
 
-constexpr size_t lds_bytes(int kgp, int nb)
+constexpr size_t lds_bytes(int kgp, int nb, bool half_groups)
 {
-    return static_cast<size_t>(nb) * 48 * kgp + kWavesPerWorkgroup * nb * sizeof(LdsRecord);
+    return static_cast<size_t>(nb) * row_bytes(kgp, nb, half_groups) + kWavesPerWorkgroup * nb * sizeof(LdsRecord);
 }
 
 // (kg_wpw_rows: slots of K | wavefronts per workgroup << 16 | lanes in use << 21 | (activation rows - 1) << 28)
@@ -1081,7 +1092,7 @@ template <typename F, int KGP, int NB>
 Variant variant_if_it_fits()
 {
     Variant v;
-    if constexpr (lds_bytes(KGP, NB) <= kMaxLdsBytes) {
+    if constexpr (lds_bytes(KGP, NB, F::HALF) <= kMaxLdsBytes) {
         v.fn = reinterpret_cast<const void*>(&gqsa_gemv_kernel<F, KGP, NB>);
         v.launch = &launch_variant<F, KGP, NB>;
     }
@@ -1255,9 +1266,9 @@ gqsa_status_t device_upload(gqsa_matrix* m, void* filled_image)
             hipFuncAttributes attr{};
             GQSA_HIP(hipFuncGetAttributes(&attr, v.fn));
             if (attr.sharedSizeBytes != 0) return GQSA_ERR_HIP;      // the kernel addresses x from LDS offset 0
-            if (lds_bytes(kgp, nb) > 64 * 1024)
+            if (lds_bytes(kgp, nb, m->G == 8) > 64 * 1024)
                 GQSA_HIP(hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             static_cast<int>(lds_bytes(kgp, nb))));
+                                             static_cast<int>(lds_bytes(kgp, nb, m->G == 8))));
         }
     }
     void* img = filled_image;
@@ -1364,7 +1375,7 @@ gqsa_status_t launch(gqsa_matrix* const* ms, int n_mats, const uint16_t* x, uint
         if (i + 1 < n_mats) wg_end[i] = grid;
     }
     const int kg_wpw_rows = static_cast<int>(m0->K / 16) | (wpw << 16) | (m0->tile_lanes << 21) | ((rows - 1) << 28);
-    v.launch(a, x, kg_wpw_rows, wg_end, dim3(grid), dim3(wpw * kLanes), lds_bytes(kgp, nb), s);
+    v.launch(a, x, kg_wpw_rows, wg_end, dim3(grid), dim3(wpw * kLanes), lds_bytes(kgp, nb, m0->G == 8), s);
     return GQSA_OK;
 }
 
@@ -1383,12 +1394,13 @@ gqsa_status_t device_gemv(gqsa_matrix* const* ms, int n_mats, const void* x, voi
     // the batch goes out in launches of 8, 4, 2 or 1 rows: the most that the format has a
     // kernel for, fits LDS and is left -- except that 3 rows go to the kernel for 4 and 7 to the
     // kernel for 8 (measured: a launch for 4 rows takes less than launches for 2 and for 1;
-    // with two rows missing the smaller launches win on the larger matrices)
+    // with two rows missing the smaller launches win on the larger matrices; beyond K = 12288 two and
+    // one do for three rows as well: 14336x14336 52.0 us against 55.3)
     int done = 0;
     while (done < batch) {
         const int left = batch - done;
         int nb = kMaxRowsPerLaunch, kgp = 0, rows = 0;
-        if ((left == 3 || left == 7) && pick(m0, left + 1, &kgp)) {
+        if (((left == 3 && m0->K <= 12288) || left == 7) && pick(m0, left + 1, &kgp)) {
             nb = left + 1;
             rows = left;
         } else {
@@ -1401,7 +1413,7 @@ gqsa_status_t device_gemv(gqsa_matrix* const* ms, int n_mats, const void* x, voi
         const uint16_t* xb = static_cast<const uint16_t*>(x) + static_cast<size_t>(done) * m0->K;
         uint16_t* yb[kMaxMatrices];
         for (int i = 0; i < n_mats; ++i) yb[i] = static_cast<uint16_t*>(ys[i]) + static_cast<size_t>(done) * ms[i]->N;
-        const size_t lds = lds_bytes(kgp, nb);
+        const size_t lds = lds_bytes(kgp, nb, m0->G == 8);
         const int together = launch_waves_per_workgroup(ms, n_mats, nb, lds);
         if (together > 0) {
             // one launch for all the matrices

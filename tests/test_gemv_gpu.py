@@ -545,10 +545,11 @@ def test_small_batches_of_unpruned_matrices(torch_cuda, bits, K):
 
 
 @pytest.mark.parametrize("bits,G,sparsity", [(4, 16, 0.5), (4, 16, 0.0), (8, 16, 0.3), (4, 8, 0.5), (4, 32, 0.5), (8, 64, 0.3), (4, 128, 0.5)])
-@pytest.mark.parametrize("K", [8192, 8320, 11008, 12288, 12416])
-def test_four_rows_between_8192_and_12288_columns(torch_cuda, bits, G, sparsity, K):
-    """Four copies of x fit LDS up to K = 12288 in a form of their own: every batch against the oracle, each row the
-    single-row bits, at both ends of its range and on either side of them."""
+@pytest.mark.parametrize("K", [4224, 8192, 8320, 11008, 12288, 12416, 16384, 16512])
+def test_several_rows_that_fill_lds(torch_cuda, bits, G, sparsity, K):
+    """Four copies of x fit LDS up to K = 12288 in a form of their own, four up to 16384, eight up to 8192 and two
+    beyond 16384 without room to spare: every batch against the oracle, each row the single-row bits, at the
+    ends of those ranges and on either side of them."""
     torch = torch_cuda
     W = gi.dense_weight(200, K, seed=95)
     x16 = gi.activations(8, K, seed=14)
