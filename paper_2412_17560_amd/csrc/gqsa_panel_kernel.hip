@@ -230,10 +230,7 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
             bool live[kPanelsPerQuad];
 #pragma unroll
             for (int pp = 0; pp < kPanelsPerQuad; ++pp) live[pp] = locate(quad * kPanelsPerQuad + pp, mat[pp], pan[pp]);
-            if (quad > 0) {
-                if (!live[0]) break;                        // (the same for the whole workgroup)
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the staging area has been read
-            }
+            if (quad > 0 && !live[0]) break;                // (the same for the whole workgroup)
             // the headers of four panels at once (scalar loads; a panel beyond the
             // last one stands in as the last one and is not computed)
             // (where 4 x HC words do not fit the scalar registers -- AGAIN -- only the first and the
@@ -282,6 +279,11 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
 #pragma unroll
             for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
                 if (pp == 0 || (pp == 2 && two_and_two)) {
+                    // The records go where others lay: panels 0 and 1, the quad before, the unit before.  A lane's
+                    // reads of those must be back first -- the loads into LDS are not ordered against
+                    // them, and the compiler waits for a value where it is used, which may be further down
+                    // (in 8 of the 56 compiled forms it was).
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
                     // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
 #pragma unroll

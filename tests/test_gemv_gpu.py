@@ -718,6 +718,33 @@ def test_panel_kernel_more_than_four_panels_per_compute_unit(torch_cuda, bits, G
                         assert np.array_equal(y.view(np.uint16), alone.view(np.uint16))
 
 
+@pytest.mark.parametrize("integer_zeros", [True, False])
+@pytest.mark.parametrize("bits,G", [(4, 16), (4, 32), (4, 64), (4, 128), (8, 16), (8, 32), (8, 64)])
+@pytest.mark.parametrize("panels", [769, 2561])
+def test_panel_kernel_staging_area_used_again(torch_cuda, bits, G, integer_zeros, panels):
+    """Dense rows, four panels to a workgroup or six (two quads) and two units and more to the first wavefront: its
+    staging area is filled again for panels 2 and 3, for the next quad and for the next unit.  The rows
+    repeat a pattern of 80, whose products the oracle has."""
+    torch = torch_cuda
+    period, N, K = 80, 16 * panels, (4096 if bits == 4 else 2048) + G
+    rng = np.random.default_rng(bits * 1000 + G)
+    c = oracle.pack(gi.dense_weight(period, K, seed=97), G, bits, sparsity=0.0)
+    if not integer_zeros:
+        c.zeros = (c.zeros.view(np.float16) + rng.standard_normal(c.nnzg).astype(np.float16)).view(np.uint16)
+    columns, times = K // G, -(-N // period)
+    h = gq.gqsa_import(np.arange(N + 1, dtype=np.int32) * columns,
+                       *(np.tile(a, times)[:N * columns * (len(a) // (period * columns))] for a in (c.groups, c.values, c.scales, c.zeros)),
+                       N, K, G, bits)
+    gq.gqsa_build_panels(h)
+    assert gq.gqsa_info(h)["panel_integer_zeros"] == int(integer_zeros)
+    x = gi.activations(16, K, seed=17)
+    ref = oracle.gemv(c, x, threads=8)
+    y = run_gemv(torch, h, x, panels=True)
+    for b in range(16):
+        assert oracle.rel_error(y[b][:period], ref[b]) <= TOL
+        assert np.array_equal(y[b].view(np.uint16), np.tile(y[b][:period], times)[:N].view(np.uint16))
+
+
 @pytest.mark.parametrize("bits,G", [(4, 16), (8, 16), (4, 32), (4, 64), (4, 128), (8, 32), (8, 64)])
 @pytest.mark.parametrize("batch", [1, 2, 5, 8, 9, 13, 16])
 def test_panel_kernel_ragged(torch_cuda, bits, G, batch):

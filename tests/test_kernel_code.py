@@ -1,0 +1,108 @@
+"""What the compiled device code of the library must hold whatever its inputs: read off the code objects
+that were built from this tree's sources (their disassembly), on the CPU."""
+from __future__ import annotations
+
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2412_17560_amd import binding
+
+LLVM = "/opt/rocm/llvm/bin"
+pytestmark = pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-objdump")), reason="no llvm-objdump here")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """The gfx950 code objects in the built library, as files."""
+    binding._lib()                                     # (builds it if nothing is built)
+    d = tmp_path_factory.mktemp("code")
+    shutil.copy(binding.library_path(), d / "lib.so")
+    subprocess.run([f"{LLVM}/llvm-objdump", "--offloading", "lib.so"], cwd=d, check=True, capture_output=True)
+    files = [d / f for f in os.listdir(d) if f.endswith("gfx950")]
+    if not files:
+        pytest.skip("a library without device code")
+    return files
+
+
+def _kernels(code_object, part_of_name):
+    """(name, [(address, mnemonic, operands, comment)]) of every kernel whose name has the part."""
+    text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(code_object)], check=True,
+                          capture_output=True, text=True).stdout
+    for body in re.split(r"\n(?=[0-9a-f]+ <)", text):
+        head = re.match(r"[0-9a-f]+ <(\S+)>:", body)
+        if head and part_of_name in head[1]:
+            lines = re.findall(r"^\s+(\S+)[ \t]*(.*?)\s*// ([0-9A-F]+):(.*)$", body, re.M)
+            yield head[1], [(int(a, 16), op, args, rest) for op, args, a, rest in lines]
+
+
+def _loads_into_lds_with_reads_outstanding(code):
+    """Addresses of the loads from global memory into LDS that some path reaches with reads of LDS still under way:
+    (LDS reads possibly outstanding, scalar loads possibly outstanding) carried along every path to a fixed
+    point.  LDS operations return in order, so a wait for n leaves at most n of them -- unless scalar
+    loads, which share the counter and return out of order, are outstanding too: then only a wait for 0 counts."""
+    place = {a: i for i, (a, *_) in enumerate(code)}
+    seen, todo, found = {}, [(0, (0, 0))], set()
+    while todo:
+        i, state = todo.pop()
+        while i < len(code):
+            if i in seen:
+                merged = tuple(map(max, seen[i], state))
+                if merged == seen[i]:
+                    break
+                state = merged
+            seen[i] = state
+            reads, scalar = state
+            address, op, args, rest = code[i]
+            if op.startswith("ds_read"):
+                reads = min(reads + 1, 64)
+            elif op.startswith(("s_load", "s_buffer_load")):
+                scalar = 1
+            elif op == "s_waitcnt" and (n := re.search(r"lgkmcnt\((\d+)\)", args)):
+                if int(n[1]) == 0:
+                    reads = scalar = 0
+                elif not scalar:
+                    reads = min(reads, int(n[1]))
+            elif "load_lds" in op and reads:
+                found.add(address)
+            state = (reads, scalar)
+            if op == "s_endpgm":
+                break
+            if op == "s_branch" or op.startswith("s_cbranch"):
+                target = re.search(r"<[^>]*?(?:\+0x([0-9a-f]+))?>", rest)
+                to = place[code[0][0] + int(target[1] or "0", 16)]
+                if op != "s_branch":
+                    todo.append((i + 1, state))
+                i = to
+            else:
+                i += 1
+    return found
+
+
+def test_the_check_itself_sees_a_missing_wait():
+    def at(*ops):
+        return [(4 * i, op, args, rest) for i, (op, args, rest) in enumerate(ops)]
+    read, load, end = ("ds_read_b96", "v[0:2], v3", ""), ("global_load_lds_dwordx4", "v[4:5], off", ""), ("s_endpgm", "", "")
+    assert _loads_into_lds_with_reads_outstanding(at(read, load, end)) == {4}
+    assert not _loads_into_lds_with_reads_outstanding(at(read, ("s_waitcnt", "lgkmcnt(0)", ""), load, end))
+    assert _loads_into_lds_with_reads_outstanding(at(read, read, ("s_waitcnt", "lgkmcnt(1)", ""), load, end)) == {12}
+    # round a loop: the load at its top follows the read at its end
+    assert _loads_into_lds_with_reads_outstanding(at(load, read, ("s_cbranch_scc1", "", " <k>"), end)) == {0}
+
+
+def test_panel_kernels_wait_for_their_lds_reads_before_staging_over_them(code_objects):
+    """The panel kernel stages a unit's records by loads from global memory straight into LDS, over the records of
+    the panels, quad or unit before.  In no compiled form may such a load be reached while reads of those
+    are outstanding."""
+    checked, found = 0, {}
+    for f in code_objects:
+        for name, code in _kernels(f, "gqsa_panel_kernel"):
+            assert any("load_lds" in c[1] for c in code), name
+            checked += 1
+            if late := _loads_into_lds_with_reads_outstanding(code):
+                found[name] = len(late)
+    assert checked >= 28
+    assert not found
