@@ -228,8 +228,8 @@ gqsa_status_t gqsa_set_partition_rows(gqsa_handle_t h, int tile_blocks, int tile
  * 32, 64 or 128 weights takes 2, 4 or 8 products).  Once built, gqsa_upload copies both images and
  * gqsa_gemv / gqsa_gemv_multi use this one for batch >= 5 with K <= 8192 and G = 16 or 8-bit codes, and for
  * batch >= 3 with larger K or larger groups of 4-bit codes (gqsa_gemv_multi: still one launch, the workgroups' panels taken from all the
- * matrices so that they share the activations they load, if the matrices have at most 2048 panels
- * of 16 rows together and their zeros are either all small integers or not -- else one launch
+ * matrices so that they share the activations they load, if the matrices have at most 1024 panels
+ * of 16 rows each and 2048 together and their zeros are either all small integers or not -- else one launch
  * per matrix; same bits either way); results stay within the same bound (fp32
  * accumulation of exact products, one rounding to fp16) but are not bit-identical to those of
  * the other kernel.
@@ -297,7 +297,8 @@ gqsa_status_t gqsa_gemv_static(gqsa_handle_t h, const void* x_dev, void* y_dev, 
  *   x_dev    [device] fp16 [batch,K], 16-byte aligned
  *   y_devs   [host] array of n_matrices [device] pointers, y_devs[i] fp16 [batch,N_i]
  * Results are bit-identical to n_matrices separate gqsa_gemv calls (which is what happens behind
- * the call when the handles' partitions differ in their wavefronts per workgroup).
+ * the call when the handles' partitions differ in their wavefronts per workgroup).  Of handles with
+ * and without a second image in one call none uses it: then they are the bits of handles without.
  */
 gqsa_status_t gqsa_gemv_multi(const gqsa_handle_t* handles, int n_matrices, const void* x_dev,
                               void* const* y_devs, int batch, void* hip_stream);

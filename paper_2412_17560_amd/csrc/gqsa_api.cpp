@@ -316,14 +316,17 @@ gqsa_status_t gqsa_gemv_multi(const gqsa_handle_t* handles, int n_matrices, cons
         // way in all of them): a workgroup's panels then come from different matrices and the
         // activations, most of what a compute unit reads, are loaded once for all of them.
         // (Not beyond eight panels per compute unit's workgroup: a second round of workgroups
-        // would leave most compute units idle.)
-        bool alike = true;
+        // would leave most compute units idle.  And not with a matrix of more than four: alone it
+        // goes out in workgroups of 8 wavefronts, which deal its columns out and add their sums in
+        // another order than the 16 of a joint launch do, and the bits are those of separate calls.)
+        bool together = n_matrices > 1;
         int64_t panels_in_all = 0;
         for (int i = 0; i < n_matrices; ++i) {
-            if (handles[i]->panel_integer_zeros != handles[0]->panel_integer_zeros) alike = false;
+            if (handles[i]->panel_integer_zeros != handles[0]->panel_integer_zeros) together = false;
+            if (handles[i]->n_panels > 4 * gqsa::kMaxDefaultWorkgroups) together = false;
             panels_in_all += handles[i]->n_panels;
         }
-        if (alike && n_matrices > 1 && panels_in_all <= 8 * gqsa::kMaxDefaultWorkgroups)
+        if (together && panels_in_all <= 8 * gqsa::kMaxDefaultWorkgroups)
             return gqsa::panels_gemm(handles, n_matrices, x_dev, y_devs, batch, hip_stream);
         for (int i = 0; i < n_matrices; ++i)
             if (gqsa_status_t st = gqsa::panels_gemm(&handles[i], 1, x_dev, &y_devs[i], batch, hip_stream)) return st;

@@ -674,11 +674,10 @@ def test_vocabulary_sized_matrix(torch_cuda):
 @pytest.mark.parametrize("integer_zeros", [True, False])
 @pytest.mark.parametrize("bits,G", [(4, 16), (4, 32), (4, 64), (4, 128), (8, 16), (8, 32), (8, 64)])
 def test_panel_kernel_more_than_four_panels_per_compute_unit(torch_cuda, bits, G, integer_zeros):
-    """Workgroups of up to eight panels: two matrices of 601 + 512 and 601 + 1447 panels in one launch (just
-    beyond four for each of 256 workgroups, and the most there are of eight), the same with one more panel
-    (separate launches), and 1113 panels of one matrix.  Dense rows (a quad's records do not fit their staging
-    area at once) and ragged ones; a sample of rows against the oracle, all rows of the joint launch
-    the bits of separate calls."""
+    """Two matrices of 601 + 512 and of 1024 + 1024 panels in one launch (just beyond four for each of 256 workgroups, and
+    the most there are of eight); 601 + 1447 and 601 + 1448, which a matrix of more than 1024 panels or more than 2048 in
+    all keep apart; 1113 panels of one matrix.  Dense rows (a quad's records do not fit their staging
+    area at once) and ragged ones; every row against the oracle, and the bits of separate calls."""
     torch = torch_cuda
     K = 4 * 32 * 16 + G if G <= 32 else 2048 + G       # (the last slice is a short one)
     rng = np.random.default_rng(bits * 1000 + G)
@@ -695,8 +694,8 @@ def test_panel_kernel_more_than_four_panels_per_compute_unit(torch_cuda, bits, G
         assert gq.gqsa_info(h)["panel_integer_zeros"] == int(integer_zeros)
         return h, c
 
-    a, b, c, d, e = (packed(601, 1, True), packed(512, 2, False), packed(1447, 3, False), packed(1448, 4, False),
-                     packed(1113, 5, False))
+    a, b, c, d, e, f, g = (packed(601, 1, True), packed(512, 2, False), packed(1447, 3, False), packed(1448, 4, False),
+                           packed(1113, 5, False), packed(1024, 6, True), packed(1024, 7, False))
     x_np = gi.activations(16, K, seed=31)
     for batch in (16, 5):
         x = torch.from_numpy(x_np[:batch].copy()).cuda()
@@ -707,15 +706,14 @@ def test_panel_kernel_more_than_four_panels_per_compute_unit(torch_cuda, bits, G
             torch.cuda.synchronize()
             return [y.cpu().numpy() for y in ys]
 
-        for group in ((a, b), (a, c), (a, d), (e,)):
+        for group in ((a, b), (f, g), (a, c), (a, d), (e,)):
             for (h, packing), y in zip(group, run(group)):
                 ref = oracle.gemv(packing, x_np[:batch], threads=8)
                 for row in range(batch):
                     assert oracle.rel_error(y[row], ref[row]) <= TOL
                 if len(group) > 1:
                     alone = run(((h, packing),))[0]
-                    if packing.N <= 16 * 1024:
-                        assert np.array_equal(y.view(np.uint16), alone.view(np.uint16))
+                    assert np.array_equal(y.view(np.uint16), alone.view(np.uint16))
 
 
 @pytest.mark.parametrize("integer_zeros", [True, False])
