@@ -296,11 +296,11 @@ def _shape(h: GqsaHandle):
     return h.shape
 
 
-def _stream_ptr(stream) -> int | None:
+def _stream_ptr(stream):
     if stream is None:
         import torch
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return getattr(stream, "cuda_stream", stream)
+    return C.c_void_p(getattr(stream, "cuda_stream", stream))      # (an integer; as an argument itself ctypes would take a text too)
 
 
 _DTYPES = {}      # name -> torch.dtype

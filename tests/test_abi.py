@@ -216,6 +216,25 @@ def test_a_freed_handle_is_refused_whatever_was_known_of_it():
         assert e.value.status == 1
 
 
+@pytest.mark.parametrize("stream", ["0", b"0", 1.5, (1,), object()])
+def test_a_stream_that_is_none_is_refused(stream):
+    """A text is no stream: a C function's pointer argument would take its address."""
+    from paper_2412_17560_amd import binding
+    with pytest.raises(TypeError):
+        binding._stream_ptr(stream)
+
+
+def test_streams_as_numbers_and_objects():
+    from paper_2412_17560_amd import binding
+
+    class Stream:
+        cuda_stream = 4096
+
+    assert binding._stream_ptr(Stream()).value == 4096
+    assert binding._stream_ptr(4096).value == 4096
+    assert binding._stream_ptr(0).value is None          # the default stream
+
+
 def test_pack_hessian_argument_checks():
     W = np.ones((4, 64), dtype=np.float32)
     d = np.ones(64, dtype=np.float32)
