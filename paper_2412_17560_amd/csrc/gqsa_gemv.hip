@@ -904,7 +904,11 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
     // registers.
     // (one slot per thread covers K up to 4096 with one activation row; with several rows, or larger K, two:
     // what is not requested here is requested behind the tile and arrives behind it)
-    constexpr int XPRE = (KGP >= 512 || NB == 2 || NB == 4 || (NB == 8 && F::BITS == 4 && F::M != 2)) ? 2 : 1;      // (8 rows of 8-bit codes, or of groups of 32: the registers are not there)
+    // (8 rows of 8-bit codes, or of groups of 32, up to K = 4096: the registers are not there; nor are they beyond for 8-bit codes in
+    // the format's own tiles -- with two slots that kernel spilled 24 of them and took longer than two launches of 4 rows:
+    // 8 rows of 4096x8192 20.0 us against 17.6, now 15.2; 14336x7168 at S = 43 % 70.1 against 59.8, now 51.1)
+    constexpr bool kOwnTiles8 = F::BITS == 8 && F::M == 1 && !F::FLEX;
+    constexpr int XPRE = ((KGP >= 512 && !(NB == 8 && kOwnTiles8)) || NB == 2 || NB == 4 || (NB == 8 && F::BITS == 4 && F::M != 2)) ? 2 : 1;
     const int n_slots = NB * kg;
     uint4 xlo[XPRE], xhi[XPRE];
 #pragma unroll

@@ -106,3 +106,18 @@ def test_panel_kernels_wait_for_their_lds_reads_before_staging_over_them(code_ob
                 found[name] = len(late)
     assert checked >= 28
     assert not found
+
+
+def test_gemv_kernels_keep_their_registers(code_objects):
+    """A GEMV kernel that runs out of registers waits for its own spills between the loads of x and those of the tile:
+    with 24 of them 8 rows of 4096x8192 W8 took longer in one launch than in two of 4 rows.  Four words a lane at most."""
+    checked, spilled = 0, {}
+    for f in code_objects:
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(f)], check=True, capture_output=True, text=True).stdout
+        for name, size in re.findall(r"\.name: +(\S+)\n.*?\.private_segment_fixed_size: +(\d+)", notes, re.S):
+            if "gqsa_gemv_kernel" in name:
+                checked += 1
+                if int(size) > 16:
+                    spilled[name] = int(size)
+    assert checked >= 200
+    assert not spilled
