@@ -1310,12 +1310,22 @@ void device_release(gqsa_matrix* m)
 
 namespace {
 
+// Whether the last bit of some row's sum may depend on how the workers are grouped: the pieces of a row spread over
+// three workers or more are added side by side where the row crosses one workgroup's end, in worker order else
+// (fixup_matrix).  Rows kept inside a span of workers cross none as long as a group holds whole spans.
+bool grouping_shows(const gqsa_matrix* m, int waves_per_workgroup)
+{
+    return m->needs_fixup && (m->span_tiles == 0 || waves_per_workgroup % m->waves_per_workgroup != 0);
+}
+
 // Wavefronts per workgroup of a launch of nb activation rows on these matrices, 0 if they
 // cannot share a launch.  One activation row: the partition's own grouping.  Several rows: x
 // takes nb times the LDS, so fewer workgroups fit a compute unit; the workers are then taken 8
 // or 16 to a workgroup -- as many as keep about 16 wavefronts on a compute unit -- where the
 // worker counts allow and every compute unit still gets a workgroup (the deal of tiles to
-// workers does not depend on the grouping).
+// workers does not depend on the grouping).  Together there are more workers than each matrix has alone,
+// but one whose sums show the grouping keeps the one it has alone: a call with several matrices
+// gives the bits of separate calls.
 int launch_waves_per_workgroup(gqsa_matrix* const* ms, int n_mats, int nb, size_t lds_per_workgroup)
 {
     const int wpw = ms[0]->waves_per_workgroup;
@@ -1330,13 +1340,26 @@ int launch_waves_per_workgroup(gqsa_matrix* const* ms, int n_mats, int nb, size_
     const int per_cu = static_cast<int>(std::max<size_t>(1, kMaxLdsBytes / lds_per_workgroup));
     int want = 1;
     while (want < kWavesPerWorkgroup && want * per_cu < kWavesPerWorkgroup) want *= 2;
-    for (int bigger = want; bigger > wpw; bigger /= 2) {
-        bool fits = workers / bigger >= kMaxDefaultWorkgroups;
+    const auto deals_out = [&](int waves) {
         for (int i = 0; i < n_mats; ++i)
-            if (ms[i]->n_waves % bigger != 0) fits = false;
-        if (fits) return bigger;
+            if (ms[i]->n_waves % waves != 0) return false;
+        return true;
+    };
+    int chosen = wpw;
+    for (int bigger = want; bigger > wpw && chosen == wpw; bigger /= 2)
+        if (workers / bigger >= kMaxDefaultWorkgroups && deals_out(bigger)) chosen = bigger;
+    int alone = 0;          // the grouping of those that show it
+    for (int i = 0; i < n_mats && n_mats > 1; ++i) {
+        if (!grouping_shows(ms[i], chosen)) continue;
+        const int own = launch_waves_per_workgroup(ms + i, 1, nb, lds_per_workgroup);
+        if (alone != 0 && own != alone) return 0;
+        alone = own;
     }
-    return wpw;
+    if (alone == 0 || alone == chosen) return chosen;
+    if (!deals_out(alone)) return 0;
+    for (int i = 0; i < n_mats; ++i)
+        if (grouping_shows(ms[i], alone) && launch_waves_per_workgroup(ms + i, 1, nb, lds_per_workgroup) != alone) return 0;
+    return alone;
 }
 
 // One launch: the kernel for nb activation rows (1, 2, 4 or 8), of which the caller has `rows`

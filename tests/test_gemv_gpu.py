@@ -425,6 +425,24 @@ def test_gemv_multi_equals_separate_calls(torch_cuda, part, batch):
         assert torch.equal(y2, y)
 
 
+@pytest.mark.parametrize("bits,G,sizes,K", [(4, 16, (512, 512), 11008), (4, 16, (512, 512, 512), 11008), (8, 16, (512, 200), 12288),
+                                            (8, 64, (700, 700), 11008), (8, 64, (512, 512, 512, 512), 12288)])
+def test_gemv_multi_equals_separate_calls_rows_over_many_workers(torch_cuda, bits, G, sizes, K):
+    """Unpruned rows that follow one another without gaps, each spread over three or four workers: how the workers
+    are grouped decides where its pieces meet and so, now and then, the last bit.  A launch for several
+    matrices has more workers than each alone and must group them as the separate launches do."""
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda").manual_seed(K + G)
+    hs = [gq.gqsa_pack_device(torch.randn((N, K), generator=gen, device="cuda"), G, bits, 0.0) for N in sizes]
+    assert any(gq.gqsa_partition(h)[2] == 0 for h in hs)          # (rows without gaps)
+    x = torch.randn((16, K), generator=gen, device="cuda").to(torch.float16)
+    for batch in (1, 2, 3, 4, 7, 8, 16):
+        together = gq.gqsa_gemv_multi(hs, x[:batch].contiguous())
+        for h, y in zip(hs, together):
+            alone = gq.gqsa_gemv(h, x[:batch].contiguous())
+            assert torch.equal(y.view(torch.int16), alone.view(torch.int16)), batch
+
+
 def test_gemv_multi_error_paths(torch_cuda):
     torch = torch_cuda
     W = gi.dense_weight(32, 256, seed=1)
