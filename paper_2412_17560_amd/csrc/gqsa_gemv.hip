@@ -1348,6 +1348,13 @@ int launch_waves_per_workgroup(gqsa_matrix* const* ms, int n_mats, int nb, size_
     int chosen = wpw;
     for (int bigger = want; bigger > wpw && chosen == wpw; bigger /= 2)
         if (workers / bigger >= kMaxDefaultWorkgroups && deals_out(bigger)) chosen = bigger;
+    // Fewer workgroups than compute units still beat a second round in which few compute units have one, every workgroup staging x
+    // again.  (344 workgroups of 4, W4 G = 16 512x11008 without pruning, 2 / 3 / 4 rows 9.8 / 15.8 / 16.5 -> 6.1 / 9.2 / 9.5 us; W4 G = 32
+    // 2500x8704 at S = 50 %, 2 / 3 rows 9.1 / 14.0 -> 5.8 / 8.5 us, 8.7 and 12.8 as launches of one row; 316 of 8, W4 G = 16
+    // 2500x5120 at S = 50 %, 3 / 7 rows 7.9 / 12.3 -> 6.4 / 9.9 us.)
+    if (chosen == wpw && workers / wpw > per_cu * kMaxDefaultWorkgroups)
+        for (int bigger = 2; bigger <= want && chosen == wpw; bigger *= 2)
+            if (bigger > wpw && deals_out(bigger)) chosen = bigger;
     int alone = 0;          // the grouping of those that show it
     for (int i = 0; i < n_mats && n_mats > 1; ++i) {
         if (!grouping_shows(ms[i], chosen)) continue;

@@ -579,6 +579,26 @@ def test_several_rows_that_fill_lds(torch_cuda, bits, G, sparsity, K):
         assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
 
 
+@pytest.mark.parametrize("bits,G,N,K,sparsity", [(4, 16, 1000, 5120, 0.0), (4, 16, 512, 11008, 0.0), (4, 16, 700, 8320, 0.3), (4, 32, 2500, 8704, 0.5),
+                                                 (8, 16, 2500, 8192, 0.7), (8, 64, 1000, 5120, 0.0), (8, 8, 500, 8320, 0.3), (4, 32, 2500, 11008, 0.7)])
+def test_several_rows_more_workgroups_than_fit_at_once(torch_cuda, bits, G, N, K, sparsity):
+    """Default partitions of between one and two workgroups per compute unit, which launches of several rows take together into
+    one round: every batch against the oracle, and each row the single-row bits unless rows are spread over
+    workers without regard to the grouping."""
+    torch = torch_cuda
+    W = gi.dense_weight(N, K, seed=96)
+    x16 = gi.activations(8, K, seed=15)
+    h = gq.gqsa_pack(W, G, bits, sparsity)
+    c = oracle.pack(W, G, bits, sparsity)
+    part = gq.gqsa_partition(h)
+    assert 256 < part[0] < 512
+    rows = np.concatenate([run_gemv(torch, h, x16[b:b + 1]) for b in range(8)])
+    for batch in (2, 3, 4, 7, 8):
+        y, _ = check(torch, h, c, x16[:batch])
+        if part[2] > 0:
+            assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
+
+
 @pytest.mark.parametrize("G", [8, 32, 64, 128])
 def test_other_group_sizes_full_size_and_sparsities(torch_cuda, G):
     """4096x4096 W4 at G = 32, 64, 128, S = 0 and 50 %, default partition."""
