@@ -226,11 +226,13 @@ gqsa_status_t gqsa_set_partition_rows(gqsa_handle_t h, int tile_blocks, int tile
  * bytes per stored 4-bit group of 16 on top of the first one.  Host only; only before the handle
  * is uploaded (GQSA_ERR_UNSUPPORTED after); G >= 16 (GQSA_ERR_UNSUPPORTED for G = 8; a group of
  * 32, 64 or 128 weights takes 2, 4 or 8 products).  Once built, gqsa_upload copies both images and
- * gqsa_gemv / gqsa_gemv_multi use this one for batch >= 5 with K <= 8192 and G = 16 or 8-bit codes, and for
- * batch >= 3 with larger K or larger groups of 4-bit codes (gqsa_gemv_multi: still one launch, the workgroups' panels taken from all the
+ * gqsa_gemv / gqsa_gemv_multi use this one for batch >= 5, and for batch >= 3
+ *   with 4-bit codes and G > 16, with 8-bit codes, G > 16 and K > 8192,
+ *   and, where more than 52 % of the groups are stored, with G = 16 and K > 8192 and with 8-bit codes, G > 16 and K <= 8192
+ * (gqsa_gemv_multi: still one launch, the workgroups' panels taken from all the
  * matrices so that they share the activations they load, if the matrices have at most 1024 panels
- * of 16 rows each and 2048 together and their zeros are either all small integers or not -- else one launch
- * per matrix; same bits either way); results stay within the same bound (fp32
+ * of 16 rows each and 2048 together, their zeros are either all small integers or not and none is better off with the first
+ * image -- else one launch per matrix; same bits either way); results stay within the same bound (fp32
  * accumulation of exact products, one rounding to fp16) but are not bit-identical to those of
  * the other kernel.
  */

@@ -71,15 +71,24 @@ gqsa_status_t upload(gqsa_matrix* m)
 }
 
 // Calls with this many activation rows or more go to the matrix-core kernel if the handle has a
-// panel image: its time hardly depends on the row count (16 rows' worth of products either way),
-// the wavefront kernel's grows with every row, and they cross between 4 and 5 rows on an MI355X
-// for K up to 8192 and between 2 and 3 rows beyond (4096x11008, 4096x14336: every workgroup of
-// the wavefront kernel stages all of x).  So they do for 8-bit codes in larger groups (4096x4096 at 4 / 5
-// rows: G = 32 5.4 / 8.8 against 6.0 / 6.0 us, G = 64 5.2 / 8.6 against 5.6 / 5.6 us); with 4-bit codes in
-// larger groups, whose panel image is smaller still, they cross between 2 and 3 (4096x4096 at 2 / 3 rows:
-// G = 32 4.2 / 6.1 against 5.1 / 5.1 us, G = 64 4.1 / 5.7 against 4.8 / 4.9 us; at 14336x4096 the two take the
-// same time at 3 and 4 rows).
-constexpr int panel_min_batch(const gqsa_matrix* m) { return (m->G == 16 || m->bits == 8) && m->K <= 8192 ? 5 : 3; }
+// panel image.  Its time hardly depends on the row count (16 rows' worth of products either way) and little on
+// the pruning; the wavefront kernel's grows with the rows and with the stored groups.  With G = 16 and K up to 8192 they
+// cross between 4 and 5 rows, with 4-bit codes in larger groups between 2 and 3 (4096x4096 at S = 50 %, 4 rows: G = 32 6.1
+// against 5.3 us; 4096x11008 13.9 against 9.5), and so with 8-bit codes in larger groups beyond K = 8192 (4096x11008, 3 and 4 rows: 13.0
+// against 11.0).  In the two classes between, whether 3 and 4 rows take them depends on the share of the groups that is stored:
+//   G = 16 beyond K = 8192, 4 rows of 4096x11008 W4 / W8 at S = 0: 22.5 / 21.8 against 11.5 / 15.1 us; 30 % 12.5 / 17.9 against 11.2 / 14.3;
+//     50 % 10.3 / 14.4 against 11.3 / 13.6; 70 % 8.2 / 8.0 against 10.8 / 13.0 (16 sizes, 12 with 8-bit codes, mean of the quotients: W4 1.32, 1.08, 0.87,
+//     0.70, at 40 % 1.00; W8 1.14, 1.04, 0.86, 0.64, at 40 % 1.03);
+//   8-bit codes in larger groups up to K = 8192, 4 rows of 4096x4096 G = 32 at S = 0, 30, 45, 50, 70 %: 6.9, 8.5, 8.5, 5.3, 5.6 against
+//     6.2, 5.9, 6.0, 6.0, 5.9 us (26 sizes, mean of the quotients: 1.04, 1.35, 1.19, 0.89, 0.87).
+// The share and not the size, though a matrix of few rows would be better off with the other kernel: the matrices of
+// one call (q/k/v) differ in size but are pruned alike, and they must choose alike to go out together.
+int panel_min_batch(const gqsa_matrix* m)
+{
+    if (m->G > 16 && (m->bits == 4 || m->K > 8192)) return 3;
+    if (m->G == 16 && m->K <= 8192) return 5;
+    return m->nnzg() * 25 > m->N * (m->K / m->G) * 13 ? 3 : 5;
+}
 
 }  // namespace
 
@@ -304,13 +313,26 @@ gqsa_status_t gqsa_gemv_multi(const gqsa_handle_t* handles, int n_matrices, cons
         for (int j = 0; j < i; ++j)
             if (handles[j] == handles[i]) return GQSA_ERR_SHAPE;   // a handle has one carry workspace
     }
-    bool panels = batch >= panel_min_batch(handles[0]);
+    bool panels = true;          // every handle has the second image
+    int wanted = 0;              // how many would be multiplied from it in a call of their own
     for (int i = 0; i < n_matrices; ++i) {
         if (!handles[i]->d_image) {
             if (gqsa_status_t st = upload(handles[i])) return st;
         }
         if (!handles[i]->d_panels) panels = false;
+        if (batch >= panel_min_batch(handles[i])) ++wanted;
     }
+    if (panels && wanted > 0 && wanted < n_matrices) {
+        // some from one image and some from the other: as the separate calls would do it
+        for (int i = 0; i < n_matrices; ++i) {
+            const gqsa_status_t st = batch >= panel_min_batch(handles[i])
+                ? gqsa::panels_gemm(&handles[i], 1, x_dev, &y_devs[i], batch, hip_stream)
+                : gqsa::device_gemv(&handles[i], 1, x_dev, &y_devs[i], batch, hip_stream);
+            if (st) return st;
+        }
+        return GQSA_OK;
+    }
+    if (wanted == 0) panels = false;
     if (panels) {
         // One launch when the matrices can share a kernel variant (the zero is handled the same
         // way in all of them): a workgroup's panels then come from different matrices and the

@@ -781,6 +781,39 @@ def test_panel_kernel_staging_area_used_again(torch_cuda, bits, G, integer_zeros
         assert np.array_equal(y[b].view(np.uint16), np.tile(y[b][:period], times)[:N].view(np.uint16))
 
 
+@pytest.mark.parametrize("bits,G,K,first", [(4, 16, 4096, (5, 5)), (8, 16, 4096, (5, 5)), (4, 16, 8320, (5, 3)), (8, 16, 8320, (5, 3)), (8, 32, 4096, (5, 3)),
+                                            (8, 64, 1024, (5, 3)), (4, 32, 4096, (3, 3)), (8, 64, 8320, (3, 3))])
+def test_batch_from_which_the_second_image_is_used(torch_cuda, bits, G, K, first):
+    """first = the smallest batch that a matrix with 13 in 25 of its groups stored, and one with a group more, is
+    multiplied from the second image; in one call each takes the image it takes alone."""
+    torch = torch_cuda
+    N, columns = 75, K // G
+    total = N * columns * 13 // 25
+    hs, plain = [], []
+    for more in (0, 1):
+        keep = np.full(N, total // N)
+        keep[:total % N + more] += 1
+        assert keep.sum() == total + more
+        W = gi.dense_weight(N, K, seed=131 + more)
+        h, p = gq.gqsa_pack_rows(W, keep, G, bits), gq.gqsa_pack_rows(W, keep, G, bits)
+        gq.gqsa_build_panels(h)
+        hs.append(h)
+        plain.append(p)
+    x_np = gi.activations(8, K, seed=19)
+    differ = 0
+    for batch in (1, 2, 3, 4, 5, 8):
+        x = torch.from_numpy(x_np[:batch].copy()).cuda()
+        together = gq.gqsa_gemv_multi(hs, x)
+        for h, p, y, f in zip(hs, plain, together, first):
+            alone = run_gemv(torch, h, x_np[:batch])
+            of_panels, of_blocks = run_gemv(torch, h, x_np[:batch], panels=True), run_gemv(torch, p, x_np[:batch])
+            expected = of_panels if batch >= f else of_blocks
+            assert np.array_equal(alone.view(np.uint16), expected.view(np.uint16)), batch
+            assert np.array_equal(y.cpu().numpy().view(np.uint16), alone.view(np.uint16)), batch
+            differ += int(not np.array_equal(of_panels.view(np.uint16), of_blocks.view(np.uint16)))
+    assert differ > 0          # (the two kernels add in different orders: the bits tell them apart)
+
+
 @pytest.mark.parametrize("bits,G", [(4, 16), (8, 16), (4, 32), (4, 64), (4, 128), (8, 32), (8, 64)])
 @pytest.mark.parametrize("batch", [1, 2, 5, 8, 9, 13, 16])
 def test_panel_kernel_ragged(torch_cuda, bits, G, batch):
