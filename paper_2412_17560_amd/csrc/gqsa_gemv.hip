@@ -1310,12 +1310,12 @@ void device_release(gqsa_matrix* m)
 
 namespace {
 
-// Whether the last bit of some row's sum may depend on how the workers are grouped: the pieces of a row spread over
-// three workers or more are added side by side where the row crosses one workgroup's end, in worker order else
-// (fixup_matrix).  Rows kept inside a span of workers cross none as long as a group holds whole spans.
+// Whether the last bit of some row's sum may depend on how the workers are grouped: the pieces of a row held by three
+// workers or more are added side by side where it crosses a workgroup's end and in worker order else
+// (fixup_matrix).  A row inside one of the partition's workgroups stays inside one of several of them taken together.
 bool grouping_shows(const gqsa_matrix* m, int waves_per_workgroup)
 {
-    return m->needs_fixup && (m->span_tiles == 0 || waves_per_workgroup % m->waves_per_workgroup != 0);
+    return m->row_workers >= 3 && (m->rows_leave_workgroup || waves_per_workgroup % m->waves_per_workgroup != 0);
 }
 
 // Wavefronts per workgroup of a launch of nb activation rows on these matrices, 0 if they

@@ -89,6 +89,8 @@ struct gqsa_matrix {
     int64_t n_tiles = 0;
     int64_t n_empty = 0;
     int needs_fixup = 0;
+    int row_workers = 0;      // the most workers that hold pieces of one row
+    bool rows_leave_workgroup = false;   // a row of three workers or more has them in several of the partition's workgroups
     gqsa::ImageMap map;
     std::vector<uint8_t> image;
     // optional second image for calls with many activation rows (gqsa_panels.cpp)

@@ -555,7 +555,8 @@ gqsa_status_t build_image(gqsa_matrix* m, const Partition& part, bool fill_block
                                     first_block.begin() - 1);
     };
     int32_t* info = reinterpret_cast<int32_t*>(img.data() + map.wave_info);
-    int fix = 0;
+    int fix = 0, row_workers = n_waves > 0 ? 1 : 0;
+    bool leaves = false;
     for (int w = 0; w < n_waves; ++w) {
         const int64_t mine = first_block[w + 1] - first_block[w];
         const int64_t first = first_block[w] * lanes;
@@ -569,6 +570,8 @@ gqsa_status_t build_image(gqsa_matrix* m, const Partition& part, bool fill_block
             const int64_t row_last = (he < static_cast<int64_t>(head_pos.size()) ? head_pos[he] : len) - 1;
             chain_len = worker_of(row_last) - w + 1;
             fix = 1;
+            row_workers = std::max<int>(row_workers, chain_len);
+            if (chain_len >= 3 && w / waves_per_workgroup != (w + chain_len - 1) / waves_per_workgroup) leaves = true;
         }
         info[4 * w + 0] = static_cast<int32_t>(hb - 1);
         info[4 * w + 1] = closed;
@@ -596,6 +599,8 @@ gqsa_status_t build_image(gqsa_matrix* m, const Partition& part, bool fill_block
     m->n_tiles = n_tiles;
     m->n_empty = static_cast<int64_t>(empty.size());
     m->needs_fixup = fix;
+    m->row_workers = row_workers;
+    m->rows_leave_workgroup = leaves;
     return GQSA_OK;
 }
 

@@ -443,6 +443,32 @@ def test_gemv_multi_equals_separate_calls_rows_over_many_workers(torch_cuda, bit
             assert torch.equal(y.view(torch.int16), alone.view(torch.int16)), batch
 
 
+@pytest.mark.parametrize("n_mats,workgroups,waves,span", [(4, 272, 4, 1), (2, 272, 3, 1), (4, 400, 4, 3), (2, 1080, 1, 1)])
+def test_gemv_multi_equals_separate_calls_rows_longer_than_spans(torch_cuda, n_mats, workgroups, waves, span):
+    """The same with spans that are shorter than the rows, the workers' own (waves of 3: no whole number of them in a larger
+    workgroup) or the workgroups'.  The two halves of a row nearly cancel, so that the order of the sum shows."""
+    torch = torch_cuda
+    N, K = 290, 11008
+    hs = []
+    for i in range(n_mats):
+        W = gi.dense_weight(N, K, seed=210 + i)
+        W[:, :K // 2] += 1.0
+        W[:, K // 2:] -= 1.0
+        h = gq.gqsa_pack(W, 16, 4, 0.0)
+        if span == 1:
+            gq.gqsa_set_partition_rows(h, 4, 64, 1, workgroups, waves)
+        else:
+            gq.gqsa_set_partition_aligned(h, span, workgroups, waves)
+        assert gq.gqsa_info(h)["needs_fixup"]
+        hs.append(h)
+    x = torch.from_numpy((1.0 + 0.1 * gi.activations(16, K, seed=78).astype(np.float32)).astype(np.float16)).cuda()
+    for batch in (1, 2, 3, 4, 8, 16):
+        together = gq.gqsa_gemv_multi(hs, x[:batch].contiguous())
+        for h, y in zip(hs, together):
+            alone = gq.gqsa_gemv(h, x[:batch].contiguous())
+            assert torch.equal(y.view(torch.int16), alone.view(torch.int16)), batch
+
+
 def test_gemv_multi_error_paths(torch_cuda):
     torch = torch_cuda
     W = gi.dense_weight(32, 256, seed=1)
