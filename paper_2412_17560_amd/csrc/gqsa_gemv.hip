@@ -1369,6 +1369,28 @@ int launch_waves_per_workgroup(gqsa_matrix* const* ms, int n_mats, int nb, size_
     return alone;
 }
 
+// Whether three rows go to the kernel for four (kgp = its slots) or to those for two and for one.  The one launch reads and decodes
+// the matrix once and is the faster one nearly everywhere (4096x11008 W4 13.9 -> 11.7 us, 4096x14336 16.3 -> 14.2, W8 19.8 -> 16.7,
+// 14336x14336 W8 at S = 30 % 81.9 -> 48.0).  But x of four rows beyond K = 4096 leaves a compute unit one workgroup: where
+// each worker has one tile and there are many rounds of workgroups, nothing runs under their loads, while those of the smaller launches
+// overlap.  4-bit codes then, for groups larger than 16 up to K = 8192 from the second round on (14336x8192 G = 32, 300
+// workgroups of 16 at S = 70 %: 22.0 against 17.9 us, 896 without pruning 51.8 against 38.9), and beyond K = 11264 from the
+// third on (10000x16384, 626 workgroups: 39.8 against 38.7; 14336x12288, 896: 39.9 against 39.0; but 14336x8704, 896: 37.5 against 39.3, and
+// 8192x14336, 512: 18.6 against 20.8).
+bool three_in_one(gqsa_matrix* const* ms, int n_mats, int kgp)
+{
+    const gqsa_matrix* m0 = ms[0];
+    if (m0->bits == 8 || m0->K <= 4096 || (m0->K <= 8192 && m0->G <= 16)) return true;
+    const size_t lds = lds_bytes(kgp, 4, m0->G == 8);
+    const int together = launch_waves_per_workgroup(ms, n_mats, 4, lds);
+    int workgroups = 0;
+    for (int i = 0; i < n_mats; ++i) {
+        if (ms[i]->needs_fixup) return true;      // (the launches group the workers differently, which may show in such a row: the company must not)
+        workgroups += ms[i]->n_waves / (together ? together : launch_waves_per_workgroup(ms + i, 1, 4, lds));
+    }
+    return m0->K <= 8192 ? workgroups <= kMaxDefaultWorkgroups : workgroups <= 2 * kMaxDefaultWorkgroups || m0->K <= 11264;
+}
+
 // One launch: the kernel for nb activation rows (1, 2, 4 or 8), of which the caller has `rows`
 // (nb, or one fewer), times n_mats matrices that share x and the wavefronts per workgroup.
 gqsa_status_t launch(gqsa_matrix* const* ms, int n_mats, const uint16_t* x, uint16_t* const* ys, int nb, int rows, int wpw,
@@ -1426,15 +1448,14 @@ gqsa_status_t device_gemv(gqsa_matrix* const* ms, int n_mats, const void* x, voi
     for (int i = 0; i < n_mats; ++i)
         if (ms[i]->device != dev) return GQSA_ERR_HIP;
     // the batch goes out in launches of 8, 4, 2 or 1 rows: the most that the format has a
-    // kernel for, fits LDS and is left -- except that 3 rows go to the kernel for 4 and 7 to the
-    // kernel for 8 (measured: a launch for 4 rows takes less than launches for 2 and for 1;
-    // with two rows missing the smaller launches win on the larger matrices; beyond K = 12288 two and
-    // one do for three rows as well: 14336x14336 52.0 us against 55.3)
+    // kernel for, fits LDS and is left -- except that 3 rows mostly go to the kernel for 4 (three_in_one) and 7 to the
+    // kernel for 8 (measured: a launch for 8 rows takes less than launches for 4, for 2 and for 1;
+    // with two rows missing the smaller launches win on the larger matrices)
     int done = 0;
     while (done < batch) {
         const int left = batch - done;
         int nb = kMaxRowsPerLaunch, kgp = 0, rows = 0;
-        if (((left == 3 && m0->K <= 12288) || left == 7) && pick(m0, left + 1, &kgp)) {
+        if ((left == 3 || left == 7) && pick(m0, left + 1, &kgp) && (left == 7 || three_in_one(ms, n_mats, kgp))) {
             nb = left + 1;
             rows = left;
         } else {

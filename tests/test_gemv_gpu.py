@@ -625,6 +625,34 @@ def test_several_rows_more_workgroups_than_fit_at_once(torch_cuda, bits, G, N, K
             assert np.array_equal(y.view(np.uint16), rows[:batch].view(np.uint16)), batch
 
 
+@pytest.mark.parametrize("bits,G,K,workgroups", [(4, 32, 8192, 256), (4, 32, 8192, 257), (4, 128, 4224, 257), (4, 16, 8192, 257), (8, 32, 8192, 257),
+                                                 (4, 16, 11264, 513), (4, 16, 11280, 512), (4, 16, 11280, 513), (4, 16, 16384, 513), (8, 16, 11280, 513)])
+def test_three_rows_of_many_workgroups(torch_cuda, bits, G, K, workgroups):
+    """Three rows go out in one launch or in two by the format, K and the number of workgroups: on both sides of
+    each line the oracle's values, the single-row bits and nothing written beyond the third row."""
+    torch = torch_cuda
+    N = 16 * workgroups - 5
+    W = gi.dense_weight(64, K, seed=97)
+    kept = gi.imbalanced_keep_counts(64, 6, seed=97)           # (few groups a row: the number of workgroups is what counts)
+    c = oracle.pack(W, G, bits, keep_per_row=kept)
+    times = -(-N // 64)
+    rows = np.concatenate([[0], np.cumsum(np.tile(np.diff(c.rowIndex), times)[:N])]).astype(np.int32)
+    h = gq.gqsa_import(rows, *(np.tile(a, times)[:rows[-1] * (len(a) // c.nnzg)] for a in (c.groups, c.values, c.scales, c.zeros)), N, K, G, bits)
+    info = gq.gqsa_info(h)
+    gq.gqsa_set_partition_rows(h, info["tile_blocks"], 64, 1, workgroups, 16)
+    x = gi.activations(3, K, seed=18)
+    ref = oracle.gemv(c, x, threads=4)
+    single = np.concatenate([run_gemv(torch, h, x[b:b + 1]) for b in range(3)])
+    buf = torch.full((4, N), 7.0, dtype=torch.float16, device="cuda")
+    gq.gqsa_gemv(h, torch.from_numpy(x.copy()).cuda(), buf[:3])
+    torch.cuda.synchronize()
+    y = buf[:3].cpu().numpy()
+    assert (buf[3] == 7.0).all()
+    assert np.array_equal(y.view(np.uint16), single.view(np.uint16))
+    for b in range(3):
+        assert oracle.rel_error(y[b], np.tile(ref[b], times)[:N]) <= TOL
+
+
 @pytest.mark.parametrize("G", [8, 32, 64, 128])
 def test_other_group_sizes_full_size_and_sparsities(torch_cuda, G):
     """4096x4096 W4 at G = 32, 64, 128, S = 0 and 50 %, default partition."""
