@@ -1227,8 +1227,10 @@ Variant pick(const gqsa_matrix* m, int nb, int* kgp, bool spread = false)
     return Variant{};
 }
 
-// Stored groups that are neighbours in their rows, or nearly all of them: seven in eight.
-bool unpruned(const gqsa_matrix* m) { return m->nnzg() * 8 >= m->N * (m->K / m->G) * 7; }
+// Stored groups that are neighbours in their rows, or nearly all of them: 63 in 64.  (With fewer the lanes' slots lose step by
+// themselves: at S = 2 to 12 % the spread form gained nothing at 4096 and 14336 rows and cost 3 to 7 % where there are few rows --
+// 4 rows of 512x8192 W4 at S = 10 % 6.26 against 6.67 us.  At S = 0.8 and 1.6 % it is ahead: 4096x4096 8.0 -> 7.4, 7.8 -> 7.45.)
+bool unpruned(const gqsa_matrix* m) { return m->nnzg() * 64 >= m->N * (m->K / m->G) * 63; }
 
 constexpr size_t counters_offset(int n_waves)
 {

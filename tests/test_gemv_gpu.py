@@ -558,21 +558,31 @@ def test_other_group_sizes_small_batches(torch_cuda, bits, G, K, part):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("own_tiles", [True, False])
 @pytest.mark.parametrize("K", [16, 256, 4096, 4176, 8192, 8208])
-def test_small_batches_of_unpruned_matrices(torch_cuda, bits, K):
-    """Unpruned matrices have kernels of their own for several rows: every batch against the oracle, each row the
-    single-row bits, on both sides of the share of stored groups (seven in eight) that decides, and in one
-    launch with a pruned matrix."""
+def test_small_batches_of_unpruned_matrices(torch_cuda, bits, own_tiles, K):
+    """Unpruned matrices in the format's own tiles have kernels of their own for several rows: every batch against the
+    oracle, each row the single-row bits, on both sides of the share of stored groups (63 in 64) that
+    decides, and in one launch with a pruned matrix; and the same with the partitions that such matrices have
+    by default, whose tiles often have a chosen shape and no such form."""
     torch = torch_cuda
     N, columns = 72, K // 16
     W = gi.dense_weight(N, K, seed=93)
     x16 = gi.activations(16, K, seed=13)
     full = np.full(N, columns)
-    edge = np.full(N, (columns * 7 + 7) // 8)          # just within
-    below = edge - 1
+    edge, below = full.copy(), full.copy()
+    dropped = N * columns // 64                          # the most that may be missing
+    for keep, missing in ((edge, dropped), (below, dropped + 1)):
+        keep -= missing // N
+        keep[:missing % N] -= 1
+        assert keep.sum() == N * columns - missing
     pruned = np.full(N, columns // 2)
     hs = [gq.gqsa_pack_rows(W, keep, 16, bits) for keep in (full, edge, below, pruned)]
     cs = [oracle.pack(W, 16, bits, keep_per_row=keep) for keep in (full, edge, below, pruned)]
+    if own_tiles:
+        for h in hs[:3]:
+            gq.gqsa_set_partition(h, 5, 4)
+            assert gq.gqsa_partition(h)[3:5] == (4, 64)
     gq.gqsa_set_partition(hs[3], 3, 2)          # (several tiles to a worker)
     for h, c in zip(hs, cs):
         rows = np.concatenate([run_gemv(torch, h, x16[b:b + 1]) for b in range(16)])
