@@ -108,10 +108,10 @@ Variant tile_variant_part3(int bits, int u, int slots, int nb, int* kgp);
 Variant tile_variant_part4(int bits, int u, int slots, int nb, int* kgp);
 // The variants for group sizes other than 16 (m = 16-element chunks per group, 0: half a chunk) that the
 // other compilations hold.
-Variant group_variant_part5(int bits, int m, int slots, int nb, int* kgp);
-Variant group_variant_part6(int bits, int m, int slots, int nb, int* kgp);
-Variant group_variant_part7(int bits, int m, int slots, int nb, int* kgp);
-Variant group_variant_part8(int bits, int m, int slots, int nb, int* kgp);
+Variant group_variant_part5(int bits, int m, bool spread, int slots, int nb, int* kgp);
+Variant group_variant_part6(int bits, int m, bool spread, int slots, int nb, int* kgp);
+Variant group_variant_part7(int bits, int m, bool spread, int slots, int nb, int* kgp);
+Variant group_variant_part8(int bits, int m, bool spread, int slots, int nb, int* kgp);
 
 namespace {
 
@@ -314,7 +314,8 @@ __host__ __device__ constexpr int row_bytes(int kgp, int nb, bool half_groups)
 // U_ > 0 (FLEX): U_ blocks of L groups each, L <= 64 given at launch -- the same three arrays
 // with L entries, the lanes from L on take no group (partitions that keep whole rows inside a
 // wavefront's run choose U_ and L so that the rows fill the tiles).
-// SPREAD_ (group size 16): the slots of x change places in LDS as larger groups' do (compute_tile).
+// SPREAD_ (group size 16 with several rows, 4-bit groups of 32 with one): the form for unpruned matrices, in which
+// the slots of x change places in LDS as larger groups' do (compute_tile).
 template <int BITS_, int M_, int U_ = 0, bool SPREAD_ = false>
 struct Fmt {
     static constexpr bool FLEX = U_ != 0;
@@ -325,8 +326,10 @@ struct Fmt {
     static constexpr int CW = CB / 4;                    // code words per group
     static constexpr int CWC = HALF ? CW : CW / (M_ ? M_ : 1);    // code words per chunk (2 or 4; half chunk: 1 or 2)
     static constexpr bool SPREAD = SPREAD_;
-    static constexpr uint32_t SLOT_MASK = M_ > 1 ? M_ - 1 : (SPREAD_ ? 15 : 0);   // which low bits of a slot's number higher ones change
-    static constexpr uint32_t SUM_MASK = M_ > 1 ? M_ - 1 : 0;                     // ... and of its sum's
+    // (nb activation rows) which low bits of a slot's number higher ones change, and of its sum's
+    static constexpr bool places(int nb) { return M_ > 2 || (M_ == 2 && (BITS_ == 8 || nb > 1 || SPREAD_)); }
+    static constexpr uint32_t slot_mask(int nb) { return places(nb) ? M_ - 1 : (M_ == 1 && SPREAD_ ? 15 : 0); }
+    static constexpr uint32_t sum_mask(int nb) { return places(nb) ? M_ - 1 : 0; }
     static constexpr int PB = CB < 16 ? CB : 16;         // bytes per lane in one code plane
     static constexpr int PLANES = CB / PB;
     static constexpr int UMAX = U_ ? U_ : largest_tile(CB);   // blocks of a tile
@@ -465,7 +468,7 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 // slot's number are therefore changed where it is stored: slot s lies at s xor ((s / 16) mod M) in the two
 // arrays of halves (16 slots fill the banks once), its sum at s xor ((s / 64) mod M) (64 sums do).
 // The bits taken are the same for all chunks of a group, so a lane works them out once per group.
-// (14336x4096 W4 at 1 / 2 / 4 rows: G = 32 6.1 / 8.1 / 13.9 -> 6.1 / 7.6 / 11.5 us, G = 64 6.2 / 9.5 / 16.9 ->
+// (14336x4096 W4 at 1 / 2 / 4 rows: G = 32 - / 8.1 / 13.9 -> - / 7.6 / 11.5 us, G = 64 6.2 / 9.5 / 16.9 ->
 // 5.8 / 7.0 / 10.2 us, G = 128 7.3 / 12.1 / 22.1 -> 5.5 / 6.8 / 9.4 us.)
 //
 // At G = 16 the lanes' slots are as far apart as the rows' gaps make them, except in unpruned rows: there a
@@ -473,7 +476,9 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 // The kernels for several rows, which LDS bounds, come in a form for such matrices (SPREAD: slot s at
 // s xor ((s / 16) mod 16)): 14336x4096 W4 without pruning at 2 / 4 / 8 rows 14.6 / 22.4 / 52.7 -> 13.9 / 18.6 /
 // 38.9 us.  At S = 50 % it gains nothing and costs what its address arithmetic takes (1024x4096 at 4 / 8
-// rows 4.6 / 7.3 -> 4.75 / 7.75 us), so pruned matrices keep the plain form.
+// rows 4.6 / 7.3 -> 4.75 / 7.75 us), so pruned matrices keep the plain form.  Only the format's own tiles of 4 blocks have it; the
+// tiles of a chosen shape that most unpruned matrices take by default (K = 5120, 8192, ...) do not.
+// (One row of 4-bit groups of 32: likewise the plain order for pruned matrices, see unpruned.)
 //
 // EAGER: the tile's loads may still be in flight.  All gathers are issued first (they need only
 // the index words, the first of the tile's loads to arrive), then the groups are decoded block
@@ -636,19 +641,20 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                 }
             }
             // (where the group's chunk 0 lies and its sum; those of chunk i differ in the bits of i)
-            const uint32_t slot0 = slot ^ ((slot >> 4) & (F::SLOT_MASK * 16u));
-            const uint32_t sum0 = (slot >> 2) ^ ((slot >> 8) & (F::SUM_MASK * 4u));
+            const uint32_t slot0 = slot ^ ((slot >> 4) & (F::slot_mask(NB) * 16u));
+            const uint32_t sum0 = (slot >> 2) ^ ((slot >> 8) & (F::sum_mask(NB) * 4u));
+            constexpr bool kPlaced = F::places(NB);     // (else chunk i follows at a constant distance, no instruction)
 #pragma unroll
             for (int i = 0; i < F::M; ++i) {                // the group's 16-element chunks
                 Codes c;
                 decode_chunk<F>(t, u, i, c);
-                const uint32_t sloti = slot0 ^ (16u * i);
+                const uint32_t sloti = kPlaced ? slot0 ^ (16u * i) : slot0 + 16u * i;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     const uint32_t xb = x0 + sloti + b * row_bytes(KGP, NB, F::HALF);
                     const uint4 xl = lds_read16(xb);
                     const uint4 xh = lds_read16(xb + 16 * KGP);
-                    const float xs = lds_read_float(x0 + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + (sum0 ^ (4u * i)));
+                    const float xs = lds_read_float(x0 + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + (kPlaced ? sum0 ^ (4u * i) : sum0 + 4u * i));
                     const float d = __builtin_fmaf(-z, xs, dot16<F::BITS>(c, xl, xh));
                     dotz[b] = i == 0 ? d : dotz[b] + d;
                 }
@@ -960,8 +966,8 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
         const int b = NB == 1 ? 0 : c / kg;
         const int column = c - b * kg;
         // (where the slot and its sum lie: see compute_tile)
-        const int at = column ^ ((column >> 4) & static_cast<int>(F::SLOT_MASK));
-        const int sum_at = column ^ ((column >> 6) & static_cast<int>(F::SUM_MASK));
+        const int at = column ^ ((column >> 4) & static_cast<int>(F::slot_mask(NB)));
+        const int sum_at = column ^ ((column >> 6) & static_cast<int>(F::sum_mask(NB)));
         uint8_t* slot = xlds + b * row_bytes(KGP, NB, F::HALF) + at * 16;
         *reinterpret_cast<uint4*>(slot) = lo;
         *reinterpret_cast<uint4*>(slot + 16 * KGP) = hi;
@@ -1115,8 +1121,10 @@ Variant pick_variant(int nb)
 {
     switch (nb) {
         case 1:
-            if constexpr (F::SPREAD) return Variant{};       // (one row: LDS does not bound it)
+            if constexpr (F::SPREAD && F::M == 1) return Variant{};       // (one row: LDS does not bound it)
             else return variant_if_it_fits<F, KGP, 1>();
+    }
+    if constexpr (!(F::SPREAD && F::M == 2)) switch (nb) {         // (several rows: placed whatever the pruning)
         case 2: return variant_if_it_fits<F, KGP, 2>();
         case 4: return variant_if_it_fits<F, KGP, 4>();
         case 8: return variant_if_it_fits<F, KGP, 8>();
@@ -1125,18 +1133,20 @@ Variant pick_variant(int nb)
 }
 
 // The kernel is compiled for counts of 16-element activation slots (K/16) rounded up to a power
-// of two (the LDS offsets between the x arrays are immediates).
-// Four rows of 512 < K/16 <= 768 slots fit LDS (147 KB), but not rounded up to 1024 (196 KB): as
+// of two (the LDS offsets between the x arrays are immediates), and for four rows to 768 as well.
+// Four rows of 512 < K/16 <= 768 slots fit LDS with 48 bytes a slot (147 KB), but not rounded up to 1024 (196 KB; the 36 bytes of
+// row_bytes fit, and take 0.7 % longer over 82 sizes, 14336x8320 W8 at S = 30 % 35.8 against 33.4 us; G = 8 has no such form): as
 // two launches of two rows they read and decoded the matrix twice.  4096x11008 at 3 / 4 / 8 rows, W4
 // S = 50 %: 13.9 / 14.6 / 27.1 -> 11.8 / 12.2 / 21.7 us; 4 rows of 1024x8320 14.1 -> 10.9, 14336x11008 52.5 ->
-// 42.9 (3 rows 41.5 -> 42.2, the one size where a row and two more were as fast; 20000x11008 45.3 -> 41.1),
+// 42.9, 20000x11008 at 3 rows 45.3 -> 41.1,
 // 8192x10240 W8 32.6 -> 23.5, 4096x11008 G = 64 22.5 -> 12.6, G = 8 29.7 -> 18.3 us.
 template <typename F>
 Variant pick_kernel(int slots, int nb, int* kgp)
 {
     if (slots <= 256) { *kgp = 256; return pick_variant<F, 256>(nb); }
     if (slots <= 512) { *kgp = 512; return pick_variant<F, 512>(nb); }
-    if (slots <= 768 && nb == 4) { *kgp = 768; return variant_if_it_fits<F, 768, 4>(); }
+    if constexpr (!(F::SPREAD && F::M == 2))
+        if (slots <= 768 && nb == 4) { *kgp = 768; return variant_if_it_fits<F, 768, 4>(); }
     if (slots <= 1024) { *kgp = 1024; return pick_variant<F, 1024>(nb); }
     if (slots <= 2048) { *kgp = 2048; return pick_variant<F, 2048>(nb); }
     *kgp = 0;
@@ -1144,29 +1154,31 @@ Variant pick_kernel(int slots, int nb, int* kgp)
 }
 
 #if GQSA_GEMV_PART >= 5
-// The two (code width, chunks per group) pairs of this compilation.
+// The two (code width, chunks per group, form for unpruned matrices) of this compilation.
 #if GQSA_GEMV_PART == 5
 #define GQSA_PART_NAME group_variant_part5
-#define GQSA_PART_PAIRS {4, 0}, {4, 2}
+#define GQSA_PART_PAIRS {4, 0, false}, {4, 2, false}
 #elif GQSA_GEMV_PART == 6
 #define GQSA_PART_NAME group_variant_part6
-#define GQSA_PART_PAIRS {4, 4}, {8, 0}
+#define GQSA_PART_PAIRS {4, 4, false}, {8, 0, false}
 #elif GQSA_GEMV_PART == 7
 #define GQSA_PART_NAME group_variant_part7
-#define GQSA_PART_PAIRS {4, 8}, {8, 2}
+#define GQSA_PART_PAIRS {4, 8, false}, {8, 2, false}
 #else
 #define GQSA_PART_NAME group_variant_part8
-#define GQSA_PART_PAIRS {8, 4}, {8, 4}
+#define GQSA_PART_PAIRS {8, 4, false}, {4, 2, true}
 #endif
-struct BitsAndChunks { int bits, m; };
-constexpr BitsAndChunks kPairs[2] = {GQSA_PART_PAIRS};
+struct GroupForm { int bits, m; bool spread; };
+constexpr GroupForm kForms[2] = {GQSA_PART_PAIRS};
 
 }  // namespace
 
-Variant GQSA_PART_NAME(int bits, int m, int slots, int nb, int* kgp)
+Variant GQSA_PART_NAME(int bits, int m, bool spread, int slots, int nb, int* kgp)
 {
-    if (bits == kPairs[0].bits && m == kPairs[0].m) return pick_kernel<Fmt<kPairs[0].bits, kPairs[0].m>>(slots, nb, kgp);
-    if (bits == kPairs[1].bits && m == kPairs[1].m) return pick_kernel<Fmt<kPairs[1].bits, kPairs[1].m>>(slots, nb, kgp);
+    if (bits == kForms[0].bits && m == kForms[0].m && spread == kForms[0].spread)
+        return pick_kernel<Fmt<kForms[0].bits, kForms[0].m, 0, kForms[0].spread>>(slots, nb, kgp);
+    if (bits == kForms[1].bits && m == kForms[1].m && spread == kForms[1].spread)
+        return pick_kernel<Fmt<kForms[1].bits, kForms[1].m, 0, kForms[1].spread>>(slots, nb, kgp);
     return Variant{};
 }
 
@@ -1220,17 +1232,25 @@ Variant pick(const gqsa_matrix* m, int nb, int* kgp, bool spread = false)
         return m->bits == 4 ? pick_kernel<Fmt<4, 1, 0, true>>(slots, nb, kgp) : pick_kernel<Fmt<8, 1, 0, true>>(slots, nb, kgp);
     if (m->G == 16)
         return m->bits == 4 ? pick_kernel<Fmt<4, 1>>(slots, nb, kgp) : pick_kernel<Fmt<8, 1>>(slots, nb, kgp);
-    Variant (*const parts[4])(int, int, int, int, int*) = {group_variant_part5, group_variant_part6, group_variant_part7,
-                                                           group_variant_part8};
+    const bool spread_form = spread && m->G == 32 && m->bits == 4 && nb == 1;
+    Variant (*const parts[4])(int, int, bool, int, int, int*) = {group_variant_part5, group_variant_part6, group_variant_part7,
+                                                                 group_variant_part8};
     for (auto part : parts)
-        if (Variant v = part(m->bits, m->G / 16, slots, nb, kgp)) return v;
+        if (Variant v = part(m->bits, m->G / 16, spread_form, slots, nb, kgp)) return v;
     return Variant{};
 }
 
 // Stored groups that are neighbours in their rows, or nearly all of them: 63 in 64.  (With fewer the lanes' slots lose step by
 // themselves: at S = 2 to 12 % the spread form gained nothing at 4096 and 14336 rows and cost 3 to 7 % where there are few rows --
 // 4 rows of 512x8192 W4 at S = 10 % 6.26 against 6.67 us.  At S = 0.8 and 1.6 % it is ahead: 4096x4096 8.0 -> 7.4, 7.8 -> 7.45.)
-bool unpruned(const gqsa_matrix* m) { return m->nnzg() * 64 >= m->N * (m->K / m->G) * 63; }
+// One row of 4-bit groups of 32: 31 in 32.  (Placed slots cost a few instructions a group, which an unpruned row repays -- 14336x8192 without
+// pruning 21.4 -> 16.1 us, at S = 2 % 17.0 -> 15.6 -- and a pruned one does not: 4096x4096 at S = 50 / 70 % 3.22 / 3.16 against
+// 3.30 / 3.28 us, 28672x1024 at 70 % 3.70 against 3.84; at S = 5 and 10 % the two are level.)
+bool unpruned(const gqsa_matrix* m)
+{
+    const int64_t in = m->G == 32 ? 32 : 64;
+    return m->nnzg() * in >= m->N * (m->K / m->G) * (in - 1);
+}
 
 constexpr size_t counters_offset(int n_waves)
 {

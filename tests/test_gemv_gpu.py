@@ -598,6 +598,27 @@ def test_small_batches_of_unpruned_matrices(torch_cuda, bits, own_tiles, K):
             assert np.array_equal(y.cpu().numpy().view(np.uint16), run_gemv(torch, hs[i], x16[:4]).view(np.uint16))
 
 
+@pytest.mark.parametrize("K", [32, 1024, 4096, 4128, 8224, 16416, 32768])
+def test_one_row_of_unpruned_groups_of_32(torch_cuda, K):
+    """4-bit groups of 32 have a form for one row of (nearly) unpruned matrices: on both sides of the share of stored groups (31 in
+    32) that decides, against the oracle, and in one launch with a matrix that takes the other form."""
+    torch = torch_cuda
+    N, columns = 72, K // 32
+    W = gi.dense_weight(N, K, seed=98)
+    x = gi.activations(1, K, seed=21)
+    hs = []
+    for missing in (0, N * columns // 32, N * columns // 32 + 1, N * columns // 2):
+        keep = np.full(N, columns) - missing // N
+        keep[:missing % N] -= 1
+        h = gq.gqsa_pack_rows(W, keep, 32, 4)
+        gq.gqsa_set_partition(h, 5, 4)
+        check(torch, h, oracle.pack(W, 32, 4, keep_per_row=keep), x)
+        hs.append(h)
+    for group in (hs[:2], hs[1:3], hs):
+        for h, y in zip(group, gq.gqsa_gemv_multi(group, torch.from_numpy(x.copy()).cuda())):
+            assert np.array_equal(y.cpu().numpy().view(np.uint16), run_gemv(torch, h, x).view(np.uint16))
+
+
 @pytest.mark.parametrize("bits,G,sparsity", [(4, 16, 0.5), (4, 16, 0.0), (8, 16, 0.3), (4, 8, 0.5), (4, 32, 0.5), (8, 64, 0.3), (4, 128, 0.5)])
 @pytest.mark.parametrize("K", [4224, 8192, 8320, 11008, 12288, 12416, 16384, 16512])
 def test_several_rows_that_fill_lds(torch_cuda, bits, G, sparsity, K):
