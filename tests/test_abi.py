@@ -235,6 +235,20 @@ def test_streams_as_numbers_and_objects():
     assert binding._stream_ptr(0).value is None          # the default stream
 
 
+def test_default_stream_without_torchs_private_name(monkeypatch):
+    """The default stream is asked for by a name that torch does not promise: without it the public way gives the same."""
+    import torch
+
+    from paper_2412_17560_amd import binding
+
+    class Stream:
+        cuda_stream = 8192
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert binding._stream_ptr(None) == 8192
+
+
 def test_pack_hessian_argument_checks():
     W = np.ones((4, 64), dtype=np.float32)
     d = np.ones(64, dtype=np.float32)
