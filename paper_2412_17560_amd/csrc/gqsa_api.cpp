@@ -81,6 +81,7 @@ gqsa_status_t upload(gqsa_matrix* m)
 //     0.70, at 40 % 1.00; W8 1.14, 1.04, 0.86, 0.64, at 40 % 1.03);
 //   8-bit codes in larger groups up to K = 8192, 4 rows of 4096x4096 G = 32 at S = 0, 30, 45, 50, 70 %: 6.9, 8.5, 8.5, 5.3, 5.6 against
 //     6.2, 5.9, 6.0, 6.0, 5.9 us (26 sizes, mean of the quotients: 1.04, 1.35, 1.19, 0.89, 0.87).
+// (All of one matrix again and again, so from the caches on both sides.)
 // The share and not the size, though a matrix of few rows would be better off with the other kernel: the matrices of
 // one call (q/k/v) differ in size but are pruned alike, and they must choose alike to go out together.
 int panel_min_batch(const gqsa_matrix* m)

@@ -125,8 +125,9 @@ struct PanelTargets {
 // once for all of them: every compute unit pulls all of x through its L1 (128 KB at 16 rows and K = 4096, at
 // about 16 bytes per cycle: 3.4 us), so a second workgroup or launch for the panels beyond the fourth
 // pays that again.  Two quads against one, at 16 rows, K = 4096, W4 S = 50 %: gate/up of 2 x 11008 in one launch
-// instead of two 24.3 -> 22.6 us, 2 x 14336 29.0 -> 25.1 us (W8 33.5 -> 29.4), one matrix of 20000 rows
-// 25.0 -> 18.5 us, 28672x8192 45.4 -> 40.2 us, 60000 rows 46.5 -> 43.4 us, 32000 rows the same.
+// instead of two 24.3 -> 22.6 us, 2 x 14336 29.0 -> 25.1 us (W8 33.5 -> 29.4), one matrix of 60000 rows 46.5 -> 43.4 us, 32000 rows
+// the same.  (One matrix of 1025 to 2048 panels has at most four for each of its 512 workgroups and never reaches a second quad; what
+// it gained, 20000 rows 25.0 -> 18.5 us, 28672x8192 45.4 -> 40.2, came from there being 512 of them where there were 313 and 448.)
 template <int BITS, int M, bool INTZ, bool MULTI, int WAVES, int QUADS>
 __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     const uint16_t* __restrict__ x,

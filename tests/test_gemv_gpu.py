@@ -1006,7 +1006,7 @@ def test_panel_kernel_several_matrices_share_a_launch(torch_cuda, bits, G):
 
 @pytest.mark.parametrize("bits,G,sparsity", [(4, 16, 0.5), (8, 16, 0.3), (4, 64, 0.5), (4, 16, 0.0)])
 def test_panel_kernel_more_workgroups_than_compute_units(torch_cuda, bits, G, sparsity):
-    """More than 1024 panels (17 603 rows: 1101 panels, the last with 3 rows): 276 workgroups of
+    """More than 1024 panels (17 603 rows: 1101 panels, the last with 3 rows): 512 workgroups of
     8 wavefronts, two to a compute unit, each wavefront with several units of the panels."""
     N, K = 17603, 40 * G
     W = gi.dense_weight_chunked(N, K, seed=130)
