@@ -1119,15 +1119,18 @@ Variant variant_if_it_fits()
 template <typename F, int KGP>
 Variant pick_variant(int nb)
 {
-    switch (nb) {
-        case 1:
-            if constexpr (F::SPREAD && F::M == 1) return Variant{};       // (one row: LDS does not bound it)
-            else return variant_if_it_fits<F, KGP, 1>();
+    // the forms for unpruned matrices: of groups of 16 for several rows (LDS does not bound one), of larger groups
+    // for one (several rows have their slots placed whatever the pruning)
+    constexpr bool kOneRow = !(F::SPREAD && F::M == 1), kSeveralRows = !(F::SPREAD && F::M > 1);
+    if constexpr (kOneRow) {
+        if (nb == 1) return variant_if_it_fits<F, KGP, 1>();
     }
-    if constexpr (!(F::SPREAD && F::M == 2)) switch (nb) {         // (several rows: placed whatever the pruning)
-        case 2: return variant_if_it_fits<F, KGP, 2>();
-        case 4: return variant_if_it_fits<F, KGP, 4>();
-        case 8: return variant_if_it_fits<F, KGP, 8>();
+    if constexpr (kSeveralRows) {
+        switch (nb) {
+            case 2: return variant_if_it_fits<F, KGP, 2>();
+            case 4: return variant_if_it_fits<F, KGP, 4>();
+            case 8: return variant_if_it_fits<F, KGP, 8>();
+        }
     }
     return Variant{};
 }
@@ -1145,8 +1148,9 @@ Variant pick_kernel(int slots, int nb, int* kgp)
 {
     if (slots <= 256) { *kgp = 256; return pick_variant<F, 256>(nb); }
     if (slots <= 512) { *kgp = 512; return pick_variant<F, 512>(nb); }
-    if constexpr (!(F::SPREAD && F::M == 2))
+    if constexpr (!(F::SPREAD && F::M > 1)) {
         if (slots <= 768 && nb == 4) { *kgp = 768; return variant_if_it_fits<F, 768, 4>(); }
+    }
     if (slots <= 1024) { *kgp = 1024; return pick_variant<F, 1024>(nb); }
     if (slots <= 2048) { *kgp = 2048; return pick_variant<F, 2048>(nb); }
     *kgp = 0;
