@@ -299,8 +299,10 @@ def _shape(h: GqsaHandle):
 def _stream_ptr(stream):
     if stream is None:
         import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # (not public: torch.cuda.current_stream() makes an object a call)
-        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+        try:                 # (not a public name, but torch.cuda.current_stream() makes an object a call)
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     return C.c_void_p(getattr(stream, "cuda_stream", stream))      # (an integer; as an argument itself ctypes would take a text too)
 
 
