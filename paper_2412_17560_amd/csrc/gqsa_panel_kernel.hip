@@ -17,6 +17,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <type_traits>
+#include <utility>
 
 #include "gqsa_internal.hpp"
 
@@ -24,13 +25,17 @@ namespace gqsa {
 namespace {
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kPanelsPerQuad = 4;      // panels whose records are staged, and whose headers are held, together
 constexpr int kInFlight = 4;          // group-columns whose products are under way together
 constexpr int kPanelWaves = 16;      // wavefronts of a workgroup (or 8, see WAVES): each takes every 16th (8th) unit (a run of group-columns) of the panel
-constexpr int kWaveLds = 9216;        // bytes of LDS a wavefront stages records in (16 x 9 KB = 144 of the 160 KB)
+constexpr uint32_t kDirectArea = 9216;    // bytes of LDS a wavefront stages records in (16 x 9 KB = 144 of the 160 KB)
+constexpr uint32_t kTurnedArea = 8944;    // ... where it turns the activations' loads round as well,
+constexpr uint32_t kTurnArea = 1296;      // and in which it does that (together all of the 160 KB)
 constexpr int kMaxUnitBytes = 3072;   // records of one panel in one unit, at most (16 rows x the unit's columns)
 
 __device__ __forceinline__ float half_bits_to_float(uint32_t h)
@@ -79,6 +84,21 @@ __device__ __forceinline__ half4_t decode4_w8(uint32_t upper, uint32_t lower, ui
 // different matrices and still share the activations they load.
 // (The images themselves come as separate read-only kernel arguments: the compiler reads a
 // block's header with scalar loads only from memory it knows nothing writes to.)
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_each_index_of(F&& f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), f(1), .. f(N - 1), the numbers as compile-time constants
+template <int N, typename F>
+__device__ __forceinline__ void for_each_index(F&& f)
+{
+    for_each_index_of<N>(f, std::make_integer_sequence<int, N>{});
+}
+
+// How a wavefront gets the activations (see the kernel).
+enum class Rows { direct, turned, few };
+
 struct PanelTargets {
     uint16_t* y[kMaxMatricesPerLaunch];
     int N[kMaxMatricesPerLaunch];
@@ -89,7 +109,7 @@ struct PanelTargets {
 // A workgroup takes up to four panels (eight: QUADS) of 16 output rows (blockIdx.x, + gridDim.x, ...); wavefront
 // w takes the units w, w + 16, ... (a unit = a run of group-columns, half a slice or less) of
 // every one of them, so the activations under a unit are loaded once for all of the workgroup's
-// panels.  A block's header is the same for all lanes and is read with scalar loads.  The records
+// panels.  A block's header is the same for all lanes and is read with scalar loads (few rows: see products_few).  The records
 // of a panel in a unit are contiguous in the image; the wavefront copies them from global memory
 // straight into its own part of LDS, 1 KiB per instruction with nothing passing through
 // registers (all of its panels at once when they fit, else two and two), and every lane then
@@ -122,20 +142,19 @@ struct PanelTargets {
 // computing).  Either way four wavefronts per SIMD unit, 128 vector registers each.
 // QUADS: a workgroup takes its panels four at a time (a quad: their headers share the scalar registers,
 // their records the staging area), and up to QUADS quads under the activations of a unit, which are loaded
-// once for all of them: every compute unit pulls all of x through its L1 (128 KB at 16 rows and K = 4096, at
-// about 16 bytes per cycle: 3.4 us), so a second workgroup or launch for the panels beyond the fourth
+// once for all of them: every compute unit pulls all of x through its L1 (128 KB at 16 rows and K = 4096, direct at
+// about 16 bytes per cycle: 3.4 us, see Rows), so a second workgroup or launch for the panels beyond the fourth
 // pays that again.  Two quads against one, at 16 rows, K = 4096, W4 S = 50 %: gate/up of 2 x 11008 in one launch
 // instead of two 24.3 -> 22.6 us, 2 x 14336 29.0 -> 25.1 us (W8 33.5 -> 29.4), one matrix of 60000 rows 46.5 -> 43.4 us, 32000 rows
 // the same.  (One matrix of 1025 to 2048 panels has at most four for each of its 512 workgroups and never reaches a second quad; what
 // it gained, 20000 rows 25.0 -> 18.5 us, 28672x8192 45.4 -> 40.2, came from there being 512 of them where there were 313 and 448.)
-template <int BITS, int M, bool INTZ, bool MULTI, int WAVES, int QUADS>
-__global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
-    const uint16_t* __restrict__ x,
-    const uint8_t* __restrict__ headers0, const uint8_t* __restrict__ headers1,
-    const uint8_t* __restrict__ headers2, const uint8_t* __restrict__ headers3,
-    const uint8_t* __restrict__ data0, const uint8_t* __restrict__ data1,
-    const uint8_t* __restrict__ data2, const uint8_t* __restrict__ data3,
-    const PanelTargets tgt, int K, int n_slices, int batch)
+template <int BITS, int M, bool INTZ, bool MULTI, int WAVES, int QUADS, Rows ROWS>
+__device__ __forceinline__ void panel_products(
+    const uint16_t* __restrict__ x, const uint8_t* __restrict__ headers0, const uint8_t* __restrict__ data0,
+    int K, int n_slices, int batch, int stride, int total,
+    const uint8_t* __restrict__ headers1, const uint8_t* __restrict__ headers2, const uint8_t* __restrict__ headers3,
+    const uint8_t* __restrict__ data1, const uint8_t* __restrict__ data2, const uint8_t* __restrict__ data3,
+    const PanelTargets tgt)
 {
     constexpr int CB = 2 * BITS * M;                // code bytes per group
     constexpr bool PAIRED8 = BITS == 8 && M == 1;   // 8-bit, G = 16: quarter 0, word, quarter 1, quarter 2, word, quarter 3
@@ -144,17 +163,111 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     constexpr int QW = (QB + 3) / 4;                // ... in registers
     constexpr bool PAIRED = QB == 2;                // 4-bit, G = 16: a 12-byte record, read whole
     constexpr int kPanelsPerWorkgroup = QUADS * kPanelsPerQuad;     // at most
-    __shared__ __attribute__((aligned(16))) uint8_t staged[WAVES * kWaveLds];
+    constexpr int HC = (BITS == 4 ? 16 : 8) / M;    // group-columns of a unit: 16 rows x HC columns x RB bytes <= kMaxUnitBytes
+    static_assert(HC >= 1 && HC <= 16 && kPanelRows * HC * RB <= kMaxUnitBytes, "a unit's records must fit their staging area");
+    constexpr int XCH = HC * M;                     // 16-element chunks of activations under a unit
+    constexpr bool FEW = ROWS == Rows::few, TURNED = ROWS != Rows::direct;
+    constexpr int XL = FEW ? XCH / 4 : XCH / 2;     // loads that fetch them: 8 rows of 128 bytes or 16 of 64
+    constexpr uint32_t kWaveLds = TURNED ? kTurnedArea : kDirectArea, kTurnLds = TURNED ? kTurnArea : 0;
+    static_assert(!FEW || M == 1, "pairs of columns of 16 weights");
+    constexpr int UPS = kSliceColumns / HC;         // units per slice
+    constexpr int kFly = (INTZ || M > 1) ? kInFlight : 2;      // (two sums per column without INTZ: registers)
+    constexpr int FLY = HC < kFly ? HC : kFly;
+    constexpr uint32_t kSpare = (RB + 15u) & ~15u;
+    static_assert(kSpare + 2 * (kMaxUnitBytes + kSpare) <= kWaveLds, "two panels' worth must fit a wavefront's staging area");
+    __shared__ __attribute__((aligned(16))) uint8_t staged[WAVES * (kWaveLds + kTurnLds)];
     float* part = reinterpret_cast<float*>(staged);            // the same memory once the products are done
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wl = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint8_t* mine = staged + wl * kWaveLds;                     // this wavefront's staging area
+    const int wg = blockIdx.x;
+    const int n_units = UPS * n_slices;
+
+    // the workgroup's panels: wg, wg + stride, ... (stride = the grid's size), each in its matrix; one past the last
+    // stands in as the last and is not computed
+    const auto locate = [&](int pp, int& m, int& p) {
+        const int v = min(wg + pp * stride, total - 1);
+        if constexpr (MULTI) {
+            // (selects among values at fixed places of the argument block: no load depends on another)
+            static_assert(kMaxMatricesPerLaunch == 4, "written out for four matrices");
+            const int f1 = tgt.first[1], f2 = tgt.first[2], f3 = tgt.first[3];
+            m = (v >= f1 ? 1 : 0) + (v >= f2 ? 1 : 0) + (v >= f3 ? 1 : 0);
+            p = v - (m == 0 ? 0 : m == 1 ? f1 : m == 2 ? f2 : f3);
+        } else {
+            m = 0;
+            p = v;
+        }
+    };
+    const auto is_live = [&](int pp) { return wg + pp * stride < total; };     // (the same for the whole workgroup)
+    const uint32_t panel_headers = static_cast<uint32_t>(n_slices) * kPanelHeaderBytes;
     const int r = lane & 15;                        // activation row (A), output row of the panel (B, D)
-    const int j = lane >> 4;                        // which four of a group's 16 elements
+    const int j = lane >> 4;                        // which four of a group's 16 elements (FEW: which eight of two groups')
+    // few: a unit's header words, a vector load per panel (scalar ones, a panel after the other, arrived up to 3500 cycles later with
+    // 16 wavefronts asking): of every 16 lanes lane i takes column 2 i (the lanes 0..31) or 2 i + 1
+    // (32..63), and lane 15 the word that says where the block's data start.
+    struct Header { uint32_t words[kPanelsPerWorkgroup]; };
+    static_assert(!FEW || HC / 2 < 16, "lane 15 takes the block's place");
+    const auto load_header = [&](int unit) {
+        const uint32_t block = static_cast<uint32_t>(unit / UPS) * kPanelHeaderBytes;
+        const uint32_t lane_at = r == 15 ? kSliceColumns * 4u : (unit % UPS) * (HC * 4u) + 4u * (2 * min(r, HC / 2 - 1) + (j >> 1));
+        Header h{};
+#pragma unroll
+        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
+            if (!is_live(pp)) break;
+            int m, p;
+            locate(pp, m, p);
+            const uint8_t* base = !MULTI || m == 0 ? headers0 : m == 1 ? headers1 : m == 2 ? headers2 : headers3;
+            h.words[pp] = *reinterpret_cast<const uint32_t*>(base + (static_cast<uint64_t>(static_cast<uint32_t>(p)) * panel_headers + block) + lane_at);
+        }
+        return h;
+    };
+
+    // The activations under a unit, once for all panels of the workgroup.
+    // direct: of two neighbouring chunks the lanes 0..31 load the first (elements 0-7 and 8-15 of row r), the lanes 32..63 the
+    // second, and a swap between the two halves of the wavefront hands every lane the four elements it supplies to a product:
+    // elements 0-3, 8-11, 4-7, 12-15 of the chunk for j = 0..3 (which element sits in which of the product's 16 slots does not
+    // matter as long as the codes follow suit).  Neighbouring lanes are in different rows, so every lane's 16 bytes are a request
+    // of their own, and x arrives at 16 bytes a cycle and compute unit: 3.5 us for 16 rows of 4096.
+    // turned: a lane loads 16 bytes of row lane / 4, four lanes next to each other in memory -- 1.2 us for the same rows -- and
+    // what it needs of them comes out of a turn through LDS, rows 80 bytes apart there so that the lanes' accesses spread
+    // over the banks.  Only where a workgroup has one panel: with more of them the wavefronts whose activations
+    // arrive first multiply while the others' are on their way, and the turn is one thing more to do.  (direct / turned, 16 rows, W4 S = 50 %:
+    // 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; but 3 x 4096x4096
+    // in one launch 13.6 / 13.9, 8192x11008 19.4 / 20.1.)
+    // few (at most 8 activation rows): likewise with eight lanes to a row; elements 8 (j & 1) .. + 7 of row r & 7, of the first column of a
+    // pair for j < 2 and r < 8, of the second for j >= 2 and r >= 8, and nothing -- 16 zero bytes -- else.
+    constexpr int kRowLanes = FEW ? 8 : 4, kRowStride = FEW ? 144 : 80;
+    const int xr = TURNED ? lane / kRowLanes : r, xp = TURNED ? lane % kRowLanes : 2 * (j >> 1) + (j & 1);
+    const uint32_t x_lane = static_cast<uint32_t>(min(xr, batch - 1)) * static_cast<uint32_t>(2 * K);      // (bytes: 16 rows of at most 65536)
+    const int chunks = K >> 4;
+    uint8_t* mine = staged + wl * kWaveLds;                     // this wavefront's staging area
+    uint8_t* turn = staged + WAVES * kWaveLds + wl * kTurnLds;
+    constexpr int kZeros = 8 * 144;                             // FEW: where the zero bytes are (read at 0 and 64 from here)
+    static_assert(!TURNED || (FEW ? kZeros + 80 : 16 * 80) <= kTurnLds, "the turned load must fit its area");
+    u32x4_t* turn_in = reinterpret_cast<u32x4_t*>(turn + xr * kRowStride + xp * 16);
+    const uint8_t* turn_out = turn + (!FEW ? r * kRowStride + (2 * (j & 1) + (j >> 1)) * 8 : (r < 8) == (j < 2) ? (r & 7) * kRowStride + j * 16 : kZeros);
+    if constexpr (FEW) {
+        if (lane < 5) *reinterpret_cast<u32x4_t*>(turn + kZeros + 16 * lane) = u32x4_t{0, 0, 0, 0};
+    }
+    u32x4_t xw[XL];
+    const auto load_x = [&](int unit) {
+        const int chunk = unit * XCH;
+        const uint8_t* xb = reinterpret_cast<const uint8_t*>(x);
+        if (chunk + XCH <= chunks) {
+            const uint8_t* from = xb + 32 * chunk;
+            const uint32_t at = x_lane + 16u * xp;
+#pragma unroll
+            for (int i = 0; i < XL; ++i) xw[i] = *reinterpret_cast<const u32x4_t*>(from + at + 16 * kRowLanes * i);
+        } else {        // the last slice may be short: chunks beyond K -- no groups there -- take the last one's
+#pragma unroll
+            for (int i = 0; i < XL; ++i) {
+                const uint32_t g = min(chunk + (kRowLanes / 2) * i + (xp >> 1), chunks - 1);
+                xw[i] = *reinterpret_cast<const u32x4_t*>(xb + (x_lane + (32 * g + 16 * (xp & 1))));
+            }
+        }
+    };
+
     const uint32_t below = (1u << r) - 1u;
-    const uint16_t* xrow = x + static_cast<size_t>(r < batch ? r : batch - 1) * K + 8 * (j & 1);
-    const int last_chunk = (K >> 4) - 1;
     DecodeConstants dk;       // (kept out of the compiler's sight as constants: it would split the AND-OR)
     asm volatile("s_mov_b32 %0, 0x64006400" : "=s"(dk.splice));
     asm volatile("v_mov_b32 %0, 0x000F000F" : "=v"(dk.nib_lo));
@@ -164,36 +277,6 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     const half2_t k64 = {(_Float16)64.0f, (_Float16)64.0f};
     const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const half4_t ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
-
-    // the workgroup's panels: blockIdx.x, blockIdx.x + gridDim.x, ... (at most kPanelsPerWorkgroup),
-    // each in its matrix; one past the last stands in as the last and is not computed
-    const auto locate = [&](int pp, int& m, int& p) {
-        const int v = static_cast<int>(blockIdx.x + pp * gridDim.x);
-        const bool is_live = v < tgt.total;
-        const int vc = is_live ? v : tgt.total - 1;
-        if constexpr (MULTI) {
-            // (selects among values at fixed places of the argument block: no load depends on another)
-            static_assert(kMaxMatricesPerLaunch == 4, "written out for four matrices");
-            const int f1 = tgt.first[1], f2 = tgt.first[2], f3 = tgt.first[3];
-            m = (vc >= f1 ? 1 : 0) + (vc >= f2 ? 1 : 0) + (vc >= f3 ? 1 : 0);
-            p = vc - (m == 0 ? 0 : m == 1 ? f1 : m == 2 ? f2 : f3);
-        } else {
-            m = 0;
-            p = vc;
-        }
-        return is_live;
-    };
-    float acc[kPanelsPerWorkgroup][4];
-#pragma unroll
-    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[pp][v] = 0.0f;
-    constexpr int HC = (BITS == 4 ? 16 : 8) / M;    // group-columns of a unit: 16 rows x HC columns x RB bytes <= kMaxUnitBytes
-    static_assert(HC >= 1 && kPanelRows * HC * RB <= kMaxUnitBytes, "a unit's records must fit their staging area");
-    constexpr int XCH = HC * M;                     // 16-element chunks of activations under a unit
-    constexpr int UPS = kSliceColumns / HC;         // units per slice
-    constexpr int kFly = (INTZ || M > 1) ? kInFlight : 2;      // (two sums per column without INTZ: registers)
-    constexpr int FLY = HC < kFly ? HC : kFly;
     // a lane supplies elements 0-3, 8-11, 4-7, 12-15 of every chunk for j = 0..3: quarters 0, 2, 1, 3
     const uint32_t quarter = 2u * (j & 1) + (j >> 1);
     const uint32_t code_lane = quarter * QB + (quarter >= 2 ? 4u : 0u);     // where its codes start in a record
@@ -205,222 +288,418 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     const uint32_t half_of_record = quarter >= 2 ? 12u : 0u;
     const uint32_t sel_codes = PAIRED8 ? 0x0c010c00u + (quarter & 1u) * 0x00040004u
                                        : 0x0c010c00u + (quarter & 1u) * 0x00020002u + (quarter >= 2 ? 0x00040004u : 0u);
-    for (int unit = wl; unit < UPS * n_slices; unit += WAVES) {
-        const int s = unit / UPS;
-        const int sub = unit % UPS;
-        const int col0 = s * kSliceColumns + sub * HC;
-        // The activations under these columns (XCH chunks of 16), once for all panels of the
-        // workgroup, with 16-byte loads: of two neighbouring chunks the lanes 0..31 load the first
-        // (elements 0-7 and 8-15 of it), the lanes 32..63 the second, and a swap between the two
-        // halves of the wavefront hands every lane the four elements it supplies to a product:
-        // elements 0-3, 8-11, 4-7, 12-15 of the chunk for the lanes' j = 0..3 (which element sits in
-        // which of the product's 16 slots does not matter as long as the codes follow suit).
-        // The last slice may be short: chunks beyond K (no groups there) take the last one's.
-        // (The loads are issued here, ahead of everything; the swap waits until the records' loads
-        // have been issued too, so that nothing is held up by the activations' arrival.)
-        uint2 xa[HC][M];
-        uint4 xw[XCH / 2];
+
+    float acc[kPanelsPerWorkgroup][4];
 #pragma unroll
-        for (int pr = 0; pr < XCH / 2; ++pr) {
-            const int g = col0 * M + 2 * pr + (j >> 1);
-            xw[pr] = *reinterpret_cast<const uint4*>(xrow + 16 * (g < last_chunk ? g : last_chunk));
+    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[pp][v] = 0.0f;
+
+    const auto word_of = [&](uint32_t h, int at) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), at)); };
+    uint32_t slot[kPanelsPerQuad];      // where a panel's records begin in the staging area
+    // few: stages a unit's records of the panels from pp on of a quad, from byte `at` of the area on, as many as fit: returns
+    // one past the last.  The records of a panel in a unit are contiguous (first group of the first column .. last group of
+    // the last column); they go one panel's after the other's, each rounded up to 16 bytes plus room for one more record (a
+    // lane without a group may read the one behind the last).  Every lane copies 16 bytes per KiB of them, global memory ->
+    // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers.
+    const auto stage = [&](const Header& h, int quad, int from_panel, uint32_t at) {
+        // The records go where others lay.  A lane's reads of those must be back first -- the loads into LDS are not
+        // ordered against them, and the compiler waits for a value where it is used, which may be further down.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        int end = kPanelsPerQuad;
+#pragma unroll
+        for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+            if (pp < from_panel || pp >= end) continue;
+            if (!is_live(quad * kPanelsPerQuad + pp)) { end = pp; continue; }
+            const uint32_t words = h.words[quad * kPanelsPerQuad + pp];
+            const uint32_t last = word_of(words, 32 + HC / 2 - 1), first = word_of(words, 0) >> 16, place = word_of(words, 15);
+            const uint32_t bytes = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first) * RB;     // <= kMaxUnitBytes
+            const uint32_t next = at + ((bytes + 15u) & ~15u) + kSpare;
+            if (next > kWaveLds) { end = pp; continue; }
+            int m, p;
+            locate(quad * kPanelsPerQuad + pp, m, p);
+            const uint8_t* data = !MULTI || m == 0 ? data0 : m == 1 ? data1 : m == 2 ? data2 : data3;
+            const uint8_t* from = data + (static_cast<uint64_t>(place) * 16u + first * RB);
+            slot[pp] = at;
+            // What a lane without a group multiplies meets the zeros of the other column's activations, so it has to be finite:
+            // the record before the first one is zero.
+            if (lane < static_cast<int>(kSpare / 16)) *reinterpret_cast<u32x4_t*>(mine + (at - kSpare) + 16 * lane) = u32x4_t{0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
+                if (i > 0 && bytes <= 1024u * i) continue;
+                const uint32_t o = 16u * lane + 1024u * i;
+                if (o < bytes)
+                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
+                                                     (__attribute__((address_space(3))) void*)(mine + (at + 1024u * i)), 16, 0, 0);
+            }
+            at = next;
+        }
+        return end;
+    };
+
+    uint2 xa[HC][M];
+    // The products of one panel of a step: its records in LDS, its header words in 16 lanes of h.
+    const auto products = [&](float* sums, const uint32_t (&hh)[HC], uint32_t before0, const uint8_t* records) {
+        // (sums of eight panels leave registers for the records of eight columns at a time, of four where a column takes two sums)
+        constexpr int HL = QUADS == 1 || BITS == 8 ? HC : HC > 8 ? 8 : !INTZ && HC > 4 ? 4 : HC;
+#pragma unroll
+        for (int c0 = 0; c0 < HC; c0 += HL) {
+        if (c0 > 0) asm volatile("" ::: "memory");
+        uint32_t code[HL][(PAIRED || PAIRED8) ? 2 : QW], sz[HL];
+        constexpr bool TRI = PAIRED || PAIRED8;     // three words, the middle one is scale | zero as it is: the whole 12-byte
+                                                    // record, or the half of the 24-byte one that holds the lane's quarter
+#pragma unroll
+        for (int c = 0; c < HL; ++c) {
+            const uint32_t h = hh[c0 + c];
+            const uint32_t idx = ((h >> 16) - before0) + __builtin_popcount(h & 0xFFFFu & below);
+            if constexpr (TRI) {
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + (PAIRED8 ? half_of_record : 0u)));
+                code[c][0] = w[0];
+                sz[c] = w[1];
+                code[c][1] = w[2];
+            } else {
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + code_lane));
+#pragma unroll
+                for (int t = 0; t < QW; ++t) code[c][t] = w[t];
+                sz[c] = *reinterpret_cast<const uint32_t*>(records + (idx * RB + CB / 2));
+            }
+        }
+        // four columns at a time: the products of the later ones are under way while the
+        // first one's sums are scaled.  Which lanes have a group in a column is a lane
+        // mask made from the header word with scalar arithmetic (bit r -> lanes r, r + 16, ...)
+#pragma unroll
+        for (int c = 0; c < HL; c += FLY) {
+            float4_t d[FLY], e[FLY];
+            uint32_t sz_word[FLY];
+#pragma unroll
+            for (int i = 0; i < FLY; ++i) {
+                sz_word[i] = sz[c + i];
+                half2_t off_lo = k1024, off_hi = k64;
+                if constexpr (INTZ) {
+                    const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
+                    const half2_t zz = {both.y, both.y};
+                    off_lo = k1024 + zz;
+                    off_hi = k64 + zz;
+                }
+                d[i] = zero4;
+                e[i] = zero4;
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    const half4_t a = __builtin_bit_cast(half4_t, xa[c0 + c + i][k]);
+                    half4_t q;
+                    if constexpr (PAIRED8) {
+                        q = decode4_w8(code[c + i][1], code[c + i][0], sel_codes, dk, off_lo);
+                    } else if constexpr (PAIRED) {
+                        q = decode4_w4(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off_lo, off_hi);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
+                    } else if constexpr (BITS == 4) {     // chunk k: two bytes, the lower or the upper half of a word
+                        q = decode4_w4(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off_lo, off_hi);
+                    } else {
+                        q = decode4_w8(0u, code[c + i][k], 0x0c010c00u, dk, off_lo);
+                    }
+                    d[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, q, d[i], 0, 0, 0);      // sum_j q_j x_j, or sum_j (q_j - z) x_j
+                    if constexpr (!INTZ) e[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, e[i], 0, 0, 0);   // sum_j x_j
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < FLY; ++i) {
+                const unsigned long long lanes = static_cast<unsigned long long>(hh[c0 + c + i] & 0xFFFFu) * 0x0001000100010001ull;
+                float sc = half_bits_to_float(sz_word[i] & 0xFFFFu);
+                asm volatile("" : "+v"(sc));        // (kept a conversion of its own: an fp32 multiply-add takes 3 cycles, one that converts 5.3: 32000x4096 24.6 -> 24.0 us)
+                if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
+                    if constexpr (INTZ) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sums[v] = __builtin_fmaf(sc, d[i][v], sums[v]);
+                    } else {
+                        const float z = half_bits_to_float(sz_word[i] >> 16);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sums[v] = __builtin_fmaf(sc, __builtin_fmaf(-z, e[i][v], d[i][v]), sums[v]);
+                    }
+                }
+            }
+        }
+        }
+    };
+
+    // few: at most 8 activation rows, G = 16.  Half of a 16x16x16 product's rows would be copies; instead two columns share a
+    // product of 32 elements: A holds the first column's activations in rows 0..7 (zeros where the second's elements are) and
+    // the second's in rows 8..15, so the lanes j < 2 end up with the sums of the first column and the lanes j >= 2 with those of
+    // the second -- and each lane has read, decoded and scaled the group of its own column only.  The launches are bound by
+    // vector instructions (5.3 cycles each with four wavefronts on a SIMD unit, 3 for a plain fp32 multiply-add): per pair of
+    // columns 6 for address and presence (the header words stay in a vector register, lane i's is broadcast by the instruction that
+    // uses it), 11 (8-bit codes: 9) for the codes, 5 for the scale, where two columns by themselves take 6, 14 (12) and 8 slower
+    // ones.  At 8 rows, W4 S = 50 %: 4096x4096 6.9 -> 5.7 us, 3 x 4096x4096 in one launch 13.3 -> 11.3, 2 x 11008x4096 21.2 -> 18.1,
+    // 4096x11008 12.4 -> 9.9, 32000x4096 24.0 -> 21.3; W8 4096x4096 7.6 -> 6.1, 2 x 14336x4096 28.0 -> 22.8, 4096x14336 18.1 -> 13.5.
+    u32x4_t xp8[FEW ? HC / 2 : 1];
+    const auto products_few = [&](float* sums, uint32_t words, uint32_t records) {
+        constexpr int PAIRS = HC / 2;
+        constexpr int STEP = INTZ && (QUADS == 1 || BITS == 8) ? 4 : 2;       // pairs under way together (registers)
+        const uint32_t upto = (2u << r) - 1u, own = 1u << r;
+        const uint32_t before = (words >> 16) * RB + (records - (word_of(words, 0) >> 16) * RB - RB + (PAIRED8 ? 12u * (j & 1) : 0u));
+        const uint32_t to_codes = 8u * (j & 1);             // 4-bit: codes, scale | zero, codes
+        uint32_t code[PAIRS][BITS / 4], sz[PAIRS];
+        bool present[PAIRS];
+        for_each_index<PAIRS>([&](auto index) {
+            constexpr int i = decltype(index)::value;
+            // the header word and the byte offset of lane i of the lane's 16: its column's
+            const uint32_t mask = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(words), 0x150 + i, 0xF, 0xF, true)) & upto;
+            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(before), 0x150 + i, 0xF, 0xF, true)) +
+                                static_cast<uint32_t>(__builtin_popcount(mask)) * RB;
+            present[i] = mask >= own;
+            if constexpr (PAIRED8) {
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(staged + at);
+                code[i][0] = w[0];
+                sz[i] = w[1];
+                code[i][1] = w[2];
+            } else {
+                code[i][0] = *reinterpret_cast<const uint32_t*>(staged + (at + to_codes));
+                sz[i] = *reinterpret_cast<const uint32_t*>(staged + (at + 4));
+            }
+        });
+#pragma unroll
+        for (int i0 = 0; i0 < PAIRS; i0 += STEP) {
+            float4_t d[STEP], e[STEP];
+#pragma unroll
+            for (int i = 0; i < STEP; ++i) {
+                half2_t off_lo = k1024, off_hi = k64;
+                if constexpr (INTZ) {
+                    const half2_t both = __builtin_bit_cast(half2_t, sz[i0 + i]);
+                    const half2_t zz = {both.y, both.y};
+                    off_lo = k1024 + zz;
+                    off_hi = k64 + zz;
+                }
+                half2_t q[4];
+                if constexpr (BITS == 4) {
+                    // (bytes e0 | e2 << 4, e1 | e3 << 4, e4 | e6 << 4, e5 | e7 << 4: pairs (e0, e4), (e2, e6), (e1, e5), (e3, e7); the activations follow suit)
+                    const uint32_t w = code[i0 + i][0], v = w >> 8;
+                    q[0] = __builtin_bit_cast(half2_t, (w & dk.nib_lo) | dk.splice) - off_lo;
+                    q[1] = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, (w & dk.nib_hi) | dk.splice), dk.sixteenth, -off_hi);
+                    q[2] = __builtin_bit_cast(half2_t, (v & dk.nib_lo) | dk.splice) - off_lo;
+                    q[3] = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, (v & dk.nib_hi) | dk.splice), dk.sixteenth, -off_hi);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        q[2 * t] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(code[i0 + i][t * (BITS / 4 - 1)], dk.splice, 0x01050104u)) - off_lo;
+                        q[2 * t + 1] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(code[i0 + i][t * (BITS / 4 - 1)], dk.splice, 0x01070106u)) - off_lo;
+                    }
+                }
+                const half8_t a = __builtin_bit_cast(half8_t, xp8[FEW ? i0 + i : 0]);
+                const half8_t b = {q[0].x, q[0].y, q[1].x, q[1].y, q[2].x, q[2].y, q[3].x, q[3].y};
+                d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, zero4, 0, 0, 0);
+                if constexpr (!INTZ) {
+                    const half8_t ones8 = {ones.x, ones.x, ones.x, ones.x, ones.x, ones.x, ones.x, ones.x};
+                    e[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ones8, zero4, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < STEP; ++i) {
+                float sc = half_bits_to_float(sz[i0 + i] & 0xFFFFu);
+                asm volatile("" : "+v"(sc));
+                if (present[i0 + i]) {
+                    if constexpr (INTZ) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sums[v] = __builtin_fmaf(sc, d[i][v], sums[v]);
+                    } else {
+                        const float z = half_bits_to_float(sz[i0 + i] >> 16);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) sums[v] = __builtin_fmaf(sc, __builtin_fmaf(-z, e[i][v], d[i][v]), sums[v]);
+                    }
+                }
+            }
+        }
+    };
+
+    const auto turn_x = [&]() {
+        uint2* flat = &xa[0][0];
+        if constexpr (!TURNED) {
+#pragma unroll
+            for (int i = 0; i < XL; ++i) {
+                const auto s0 = __builtin_amdgcn_permlane32_swap(xw[i].x, xw[i].z, false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(xw[i].y, xw[i].w, false, false);
+                flat[2 * i] = uint2{s0[0], s1[0]};
+                flat[2 * i + 1] = uint2{s0[1], s1[1]};
+            }
+            return;
         }
 #pragma unroll
-        for (int quad = 0; quad < QUADS; ++quad) {
-            int mat[kPanelsPerQuad], pan[kPanelsPerQuad];
-            bool live[kPanelsPerQuad];
+        for (int i = 0; i < XL; ++i) {
+            // (a wavefront's LDS accesses complete in order: one area serves all of its loads)
+            *turn_in = xw[i];
+            asm volatile("" ::: "memory");
+            if constexpr (FEW) {
 #pragma unroll
-            for (int pp = 0; pp < kPanelsPerQuad; ++pp) live[pp] = locate(quad * kPanelsPerQuad + pp, mat[pp], pan[pp]);
-            if (quad > 0 && !live[0]) break;                // (the same for the whole workgroup)
-            // the headers of four panels at once (scalar loads; a panel beyond the
-            // last one stands in as the last one and is not computed)
-            // (where 4 x HC words do not fit the scalar registers -- AGAIN -- only the first and the
-            // last column's word of each panel are read here, and all of a panel's words a second
-            // time, from the scalar cache, when its products start)
-            constexpr bool AGAIN = kPanelsPerQuad * HC > 32;
-            uint32_t hh_all[AGAIN ? 1 : kPanelsPerQuad][AGAIN ? 1 : HC];
-            uint32_t header_at[kPanelsPerQuad];        // byte offset of the unit's first word in the panel's matrix's headers
-            uint32_t h_first[kPanelsPerQuad], h_last[kPanelsPerQuad], where[kPanelsPerQuad];
-#pragma unroll
-            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
-                // (the choice is made here, at the load: a header is read with scalar loads only if the
-                // compiler can trace its address to a read-only argument)
-                const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
-                const uint32_t* header = reinterpret_cast<const uint32_t*>(
-                    headers + static_cast<size_t>(pan[pp] * n_slices + s) * kPanelHeaderBytes);
-                header_at[pp] = static_cast<uint32_t>((pan[pp] * n_slices + s) * kPanelHeaderBytes + sub * HC * 4);
-                if constexpr (!AGAIN) {
-#pragma unroll
-                    for (int c = 0; c < HC; ++c) hh_all[pp][c] = header[sub * HC + c];
+                for (int t = 0; t < 2; ++t) {
+                    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(turn_out + 64 * t);
+                    if constexpr (BITS == 4)
+                        xp8[2 * i + t] = u32x4_t{__builtin_amdgcn_perm(w.z, w.x, 0x05040100u), __builtin_amdgcn_perm(w.w, w.y, 0x05040100u),
+                                                 __builtin_amdgcn_perm(w.z, w.x, 0x07060302u), __builtin_amdgcn_perm(w.w, w.y, 0x07060302u)};
+                    else
+                        xp8[2 * i + t] = w;
                 }
-                h_first[pp] = header[sub * HC];
-                h_last[pp] = header[sub * HC + HC - 1];
-                where[pp] = header[32];
+            } else {
+                flat[2 * i] = *reinterpret_cast<const uint2*>(turn_out);
+                flat[2 * i + 1] = *reinterpret_cast<const uint2*>(turn_out + 32);
             }
-            // Where each panel's records of this unit lie (they are contiguous: first group of the
-            // first column .. last group of the last column) and where they go in the wavefront's
-            // staging area: one after the other, each rounded up to 16 bytes plus room for one more
-            // record (a lane without a group may read the one behind the last).  All four panels are
-            // staged at once when they fit, else two and two.
-            constexpr uint32_t kSpare = (RB + 15u) & ~15u;
-            static_assert(2 * (kMaxUnitBytes + kSpare) <= kWaveLds, "two panels' worth must fit a wavefront's staging area");
-            uint32_t first[kPanelsPerQuad], bytes[kPanelsPerQuad], room[kPanelsPerQuad], slot[kPanelsPerQuad];
+            asm volatile("" ::: "memory");
+        }
+    };
+    if constexpr (FEW) {
+        constexpr bool kAhead = QUADS == 1;          // a unit's header is loaded during the one before it
+        Header h_next{};
+        if (kAhead && wl < n_units) h_next = load_header(wl);
+        for (int unit = wl; unit < n_units; unit += WAVES) {
+            const Header h = kAhead ? h_next : load_header(unit);
 #pragma unroll
-            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
-                const uint32_t last = h_last[pp];
-                first[pp] = h_first[pp] >> 16;
-                bytes[pp] = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first[pp]) * RB;     // <= kMaxUnitBytes
-                room[pp] = ((bytes[pp] + 15u) & ~15u) + kSpare;
-            }
-            const bool two_and_two = room[0] + room[1] + room[2] + room[3] > static_cast<uint32_t>(kWaveLds);
-            slot[0] = 0;
-            slot[1] = room[0];
-            slot[2] = two_and_two ? 0 : room[0] + room[1];
-            slot[3] = slot[2] + room[2];
-#pragma unroll
-            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
-                if (pp == 0 || (pp == 2 && two_and_two)) {
-                    // The records go where others lay: panels 0 and 1, the quad before, the unit before.  A lane's
-                    // reads of those must be back first -- the loads into LDS are not ordered against
-                    // them, and the compiler waits for a value where it is used, which may be further down
-                    // (in 8 of the 56 compiled forms it was).
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
-                    // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
-#pragma unroll
-                    for (int q = pp; q < kPanelsPerQuad; ++q) {
-                        if (live[q] && (q < pp + 2 || !two_and_two)) {
-                            const uint8_t* data = !MULTI || mat[q] == 0 ? data0 : mat[q] == 1 ? data1 : mat[q] == 2 ? data2 : data3;
-                            const uint8_t* from = data + static_cast<size_t>(where[q]) * 16 + first[q] * RB;
-#pragma unroll
-                            for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
-                                const uint32_t o = 16u * lane + 1024u * i;
-                                if (o < bytes[q])
-                                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
-                                                                     (__attribute__((address_space(3))) void*)(mine + slot[q] + 1024u * i),
-                                                                     16, 0, 0);
-                            }
-                        }
-                    }
-                    if (pp == 0 && quad == 0) {
-                        uint2* flat = &xa[0][0];
-#pragma unroll
-                        for (int pr = 0; pr < XCH / 2; ++pr) {
-                            const auto s0 = __builtin_amdgcn_permlane32_swap(xw[pr].x, xw[pr].z, false, false);
-                            const auto s1 = __builtin_amdgcn_permlane32_swap(xw[pr].y, xw[pr].w, false, false);
-                            flat[2 * pr] = uint2{s0[0], s1[0]};
-                            flat[2 * pr + 1] = uint2{s0[1], s1[1]};
-                        }
-                    }
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
+            for (int quad = 0; quad < QUADS; ++quad) {
+                if (quad > 0 && !is_live(quad * kPanelsPerQuad)) break;
+                int end = stage(h, quad, 0, kSpare);        // (a lane without a group may read the record before)
+                if (quad == 0) {
+                    load_x(unit);
+                    if (kAhead && unit + WAVES < n_units) h_next = load_header(unit + WAVES);
+                    turn_x();
                 }
-                if (live[pp]) {                             // (the same for the whole workgroup)
-                    const uint8_t* records = mine + slot[pp];           // in LDS
-                    const uint32_t before0 = first[pp];
-                    uint32_t hh[HC];
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
+#pragma unroll
+                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                    if (!is_live(quad * kPanelsPerQuad + pp)) break;
+                    if (pp >= 2 && pp == end) {                 // (two always fit)
+                        end = stage(h, quad, pp, kSpare);
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    }
+                    products_few(acc[quad * kPanelsPerQuad + pp], h.words[quad * kPanelsPerQuad + pp], wl * kWaveLds + slot[pp]);
+                }
+            }
+        }
+    } else {
+        for (int unit = wl; unit < n_units; unit += WAVES) {
+            const int s = unit / UPS;
+            const int sub = unit % UPS;
+            load_x(unit);       // (ahead of everything; turned once the records' loads have been issued too)
+#pragma unroll
+            for (int quad = 0; quad < QUADS; ++quad) {
+                int mat[kPanelsPerQuad], pan[kPanelsPerQuad];
+                bool live[kPanelsPerQuad];
+#pragma unroll
+                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                    live[pp] = is_live(quad * kPanelsPerQuad + pp);
+                    locate(quad * kPanelsPerQuad + pp, mat[pp], pan[pp]);
+                }
+                if (quad > 0 && !live[0]) break;                // (the same for the whole workgroup)
+                // the headers of four panels at once (scalar loads; a panel beyond the
+                // last one stands in as the last one and is not computed)
+                // (where 4 x HC words do not fit the scalar registers -- AGAIN -- only the first and the
+                // last column's word of each panel are read here, and all of a panel's words a second
+                // time, from the scalar cache, when its products start)
+                constexpr bool AGAIN = kPanelsPerQuad * HC > 32;
+                uint32_t hh_all[AGAIN ? 1 : kPanelsPerQuad][AGAIN ? 1 : HC];
+                uint32_t header_at[kPanelsPerQuad];        // byte offset of the unit's first word in the panel's matrix's headers
+                uint32_t h_first[kPanelsPerQuad], h_last[kPanelsPerQuad], where[kPanelsPerQuad];
+#pragma unroll
+                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                    // (the choice is made here, at the load: a header is read with scalar loads only if the
+                    // compiler can trace its address to a read-only argument)
+                    const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
+                    const uint32_t* header = reinterpret_cast<const uint32_t*>(
+                        headers + static_cast<size_t>(pan[pp] * n_slices + s) * kPanelHeaderBytes);
+                    header_at[pp] = static_cast<uint32_t>((pan[pp] * n_slices + s) * kPanelHeaderBytes + sub * HC * 4);
                     if constexpr (!AGAIN) {
 #pragma unroll
-                        for (int c = 0; c < HC; ++c) hh[c] = hh_all[pp][c];
-                    } else {
-                        uint32_t at = header_at[pp];
-                        asm volatile("" : "+s"(at));            // (a read of its own, not the values kept from above)
-                        const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
-                        const uint32_t* again = reinterpret_cast<const uint32_t*>(headers + at);
-#pragma unroll
-                        for (int c = 0; c < HC; ++c) hh[c] = again[c];
+                        for (int c = 0; c < HC; ++c) hh_all[pp][c] = header[sub * HC + c];
                     }
-                    // (sums of eight panels leave registers for the records of eight columns at a time, of four where a column takes two sums)
-                    constexpr int HL = QUADS == 1 || BITS == 8 ? HC : HC > 8 ? 8 : !INTZ && HC > 4 ? 4 : HC;
+                    h_first[pp] = header[sub * HC];
+                    h_last[pp] = header[sub * HC + HC - 1];
+                    where[pp] = header[32];
+                }
+                // Where each panel's records of this unit lie (they are contiguous: first group of the
+                // first column .. last group of the last column) and where they go in the wavefront's
+                // staging area: one after the other, each rounded up to 16 bytes plus room for one more
+                // record (a lane without a group may read the one behind the last).  All four panels are
+                // staged at once when they fit, else two and two.
+                uint32_t first[kPanelsPerQuad], bytes[kPanelsPerQuad], room[kPanelsPerQuad], slot[kPanelsPerQuad];
 #pragma unroll
-                    for (int c0 = 0; c0 < HC; c0 += HL) {
-                        if (c0 > 0) asm volatile("" ::: "memory");
-                        uint32_t code[HL][(PAIRED || PAIRED8) ? 2 : QW], sz[HL];
-                        constexpr bool TRI = PAIRED || PAIRED8;     // three words, the middle one is scale | zero as it is: the whole 12-byte
-                                                                    // record, or the half of the 24-byte one that holds the lane's quarter
+                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                    const uint32_t last = h_last[pp];
+                    first[pp] = h_first[pp] >> 16;
+                    bytes[pp] = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first[pp]) * RB;     // <= kMaxUnitBytes
+                    room[pp] = ((bytes[pp] + 15u) & ~15u) + kSpare;
+                }
+                const bool two_and_two = room[0] + room[1] + room[2] + room[3] > kWaveLds;
+                slot[0] = 0;
+                slot[1] = room[0];
+                slot[2] = two_and_two ? 0 : room[0] + room[1];
+                slot[3] = slot[2] + room[2];
 #pragma unroll
-                        for (int c = 0; c < HL; ++c) {
-                            const uint32_t h = hh[c0 + c];
-                            const uint32_t idx = ((h >> 16) - before0) + __builtin_popcount(h & 0xFFFFu & below);
-                            if constexpr (TRI) {
-                                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + (PAIRED8 ? half_of_record : 0u)));
-                                code[c][0] = w[0];
-                                sz[c] = w[1];
-                                code[c][1] = w[2];
-                            } else {
-                                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + code_lane));
+                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                    if (pp == 0 || (pp == 2 && two_and_two)) {
+                        // The records go where others lay: panels 0 and 1, the quad before, the unit before.  A lane's
+                        // reads of those must be back first -- the loads into LDS are not ordered against
+                        // them, and the compiler waits for a value where it is used, which may be further down
+                        // (in 8 of the 56 compiled forms it was).
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
+                        // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
 #pragma unroll
-                                for (int t = 0; t < QW; ++t) code[c][t] = w[t];
-                                sz[c] = *reinterpret_cast<const uint32_t*>(records + (idx * RB + CB / 2));
-                            }
-                        }
-                        // four columns at a time: the products of the later ones are under way while the
-                        // first one's sums are scaled.  Which lanes have a group in a column is a lane
-                        // mask made from the header word with scalar arithmetic (bit r -> lanes r, r + 16, ...)
+                        for (int q = pp; q < kPanelsPerQuad; ++q) {
+                            if (live[q] && (q < pp + 2 || !two_and_two)) {
+                                const uint8_t* data = !MULTI || mat[q] == 0 ? data0 : mat[q] == 1 ? data1 : mat[q] == 2 ? data2 : data3;
+                                const uint8_t* from = data + static_cast<size_t>(where[q]) * 16 + first[q] * RB;
 #pragma unroll
-                        for (int c = 0; c < HL; c += FLY) {
-                            float4_t d[FLY], e[FLY];
-                            uint32_t sz_word[FLY];
-#pragma unroll
-                            for (int i = 0; i < FLY; ++i) {
-                                sz_word[i] = sz[c + i];
-                                half2_t off_lo = k1024, off_hi = k64;
-                                if constexpr (INTZ) {
-                                    const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
-                                    const half2_t zz = {both.y, both.y};
-                                    off_lo = k1024 + zz;
-                                    off_hi = k64 + zz;
-                                }
-                                d[i] = zero4;
-                                e[i] = zero4;
-#pragma unroll
-                                for (int k = 0; k < M; ++k) {
-                                    const half4_t a = __builtin_bit_cast(half4_t, xa[c0 + c + i][k]);
-                                    half4_t q;
-                                    if constexpr (PAIRED8) {
-                                        q = decode4_w8(code[c + i][1], code[c + i][0], sel_codes, dk, off_lo);
-                                    } else if constexpr (PAIRED) {
-                                        q = decode4_w4(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off_lo, off_hi);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
-                                    } else if constexpr (BITS == 4) {     // chunk k: two bytes, the lower or the upper half of a word
-                                        q = decode4_w4(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off_lo, off_hi);
-                                    } else {
-                                        q = decode4_w8(0u, code[c + i][k], 0x0c010c00u, dk, off_lo);
-                                    }
-                                    d[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, q, d[i], 0, 0, 0);      // sum_j q_j x_j, or sum_j (q_j - z) x_j
-                                    if constexpr (!INTZ) e[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, e[i], 0, 0, 0);   // sum_j x_j
-                                }
-                            }
-#pragma unroll
-                            for (int i = 0; i < FLY; ++i) {
-                                const unsigned long long lanes = static_cast<unsigned long long>(hh[c0 + c + i] & 0xFFFFu) * 0x0001000100010001ull;
-                                if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
-                                    const float sc = half_bits_to_float(sz_word[i] & 0xFFFFu);
-                                    if constexpr (INTZ) {
-#pragma unroll
-                                        for (int v = 0; v < 4; ++v) acc[quad * kPanelsPerQuad + pp][v] = __builtin_fmaf(sc, d[i][v], acc[quad * kPanelsPerQuad + pp][v]);
-                                    } else {
-                                        const float z = half_bits_to_float(sz_word[i] >> 16);
-#pragma unroll
-                                        for (int v = 0; v < 4; ++v)
-                                            acc[quad * kPanelsPerQuad + pp][v] = __builtin_fmaf(sc, __builtin_fmaf(-z, e[i][v], d[i][v]), acc[quad * kPanelsPerQuad + pp][v]);
-                                    }
+                                for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
+                                    const uint32_t o = 16u * lane + 1024u * i;
+                                    if (o < bytes[q])
+                                        __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
+                                                                         (__attribute__((address_space(3))) void*)(mine + slot[q] + 1024u * i),
+                                                                         16, 0, 0);
                                 }
                             }
                         }
+                        if (pp == 0 && quad == 0) turn_x();
+                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
+                    }
+                    if (live[pp]) {                             // (the same for the whole workgroup)
+                        const uint8_t* records = mine + slot[pp];           // in LDS
+                        const uint32_t before0 = first[pp];
+                        uint32_t hh[HC];
+                        if constexpr (!AGAIN) {
+#pragma unroll
+                            for (int c = 0; c < HC; ++c) hh[c] = hh_all[pp][c];
+                        } else {
+                            uint32_t at = header_at[pp];
+                            asm volatile("" : "+s"(at));            // (a read of its own, not the values kept from above)
+                            const uint8_t* headers = !MULTI || mat[pp] == 0 ? headers0 : mat[pp] == 1 ? headers1 : mat[pp] == 2 ? headers2 : headers3;
+                            const uint32_t* again = reinterpret_cast<const uint32_t*>(headers + at);
+#pragma unroll
+                            for (int c = 0; c < HC; ++c) hh[c] = again[c];
+                        }
+                        products(acc[quad * kPanelsPerQuad + pp], hh, before0, records);
                     }
                 }
             }
         }
     }
 
+    // few: the sums of the first columns are in the lanes j < 2, of the second ones in the lanes 32 further on, for the
+    // activation rows 4 (j & 1) .. + 3: added up, both have the rows' sums
+    if constexpr (FEW) {
+#pragma unroll
+        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const uint32_t sum = __builtin_bit_cast(uint32_t, acc[pp][v]);
+                const auto both = __builtin_amdgcn_permlane32_swap(sum, sum, false, false);
+                const uint32_t first = both[0], second = both[1];
+                acc[pp][v] = __builtin_bit_cast(float, first) + __builtin_bit_cast(float, second);
+            }
+    }
+
     // The wavefronts' sums meet in LDS (the staging areas, once every wavefront is done with its
     // own): all panels' at once, then the wavefronts share out the (panel, accumulator register)
     // pairs: pair t = the activation rows 4 j + (t % 4) of panel t / 4, whose contributions are
     // added in wavefront order and stored.
-    static_assert(kPanelsPerWorkgroup * WAVES * 4 * kLanes * sizeof(float) <= sizeof(staged), "the sums must fit the staging areas");
+    static_assert(kPanelsPerWorkgroup * WAVES * 4u * kLanes * sizeof(float) <= sizeof(staged), "the sums must fit the staging areas");
     __syncthreads();
 #pragma unroll
     for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-        if (blockIdx.x + pp * gridDim.x >= static_cast<unsigned>(tgt.total)) break;     // (the same for the whole workgroup)
+        if (!is_live(pp)) break;
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[((pp * 4 + v) * WAVES + wl) * kLanes + lane] = acc[pp][v];
     }
@@ -428,7 +707,8 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
     for (int t = wl; t < 4 * kPanelsPerWorkgroup; t += WAVES) {      // t = (panel, accumulator register)
         const int pp = t >> 2, v = t & 3;
         int m, p;
-        if (locate(pp, m, p)) {
+        if (is_live(pp)) {
+            locate(pp, m, p);
             float sum = 0.0f;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) sum += part[(t * WAVES + w) * kLanes + lane];
@@ -439,6 +719,30 @@ __global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
             if (b < batch && row < n) y[static_cast<size_t>(b) * n + row] = float_to_half_bits(sum);
         }
     }
+}
+
+// One matrix: the leading parameters, which its first loads depend on, are in scalar registers when a wavefront starts (the file is
+// compiled with kernel-argument preloading: 4096x4096 at 8 and 16 rows 6.15 / 7.55 -> 5.9 / 7.3 us).
+template <int BITS, int M, bool INTZ, int WAVES, int QUADS, Rows ROWS>
+__global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_kernel(
+    const uint16_t* __restrict__ x, const uint8_t* __restrict__ headers, const uint8_t* __restrict__ data,
+    int K, int n_slices, int batch, int stride, int total, const PanelTargets tgt)
+{
+    panel_products<BITS, M, INTZ, false, WAVES, QUADS, ROWS>(x, headers, data, K, n_slices, batch, stride, total, nullptr, nullptr, nullptr,
+                                                            nullptr, nullptr, nullptr, tgt);
+}
+
+// Several: the scalar registers are short, so nothing is preloaded (the structure comes first).
+template <int BITS, int M, bool INTZ, int WAVES, int QUADS, Rows ROWS>
+__global__ __launch_bounds__(WAVES * kLanes, 4) void gqsa_panel_multi_kernel(
+    const PanelTargets tgt, const uint16_t* __restrict__ x,
+    const uint8_t* __restrict__ headers0, const uint8_t* __restrict__ headers1,
+    const uint8_t* __restrict__ headers2, const uint8_t* __restrict__ headers3,
+    const uint8_t* __restrict__ data0, const uint8_t* __restrict__ data1,
+    const uint8_t* __restrict__ data2, const uint8_t* __restrict__ data3, int K, int n_slices, int batch, int stride)
+{
+    panel_products<BITS, M, INTZ, true, WAVES, QUADS, ROWS>(x, headers0, data0, K, n_slices, batch, stride, tgt.total, headers1, headers2, headers3,
+                                                           data1, data2, data3, tgt);
 }
 
 }  // namespace
@@ -520,42 +824,66 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     const int64_t per_wg = many ? 2 * kPanelsPerQuad : kPanelsPerQuad;
     const int64_t wgs = std::min<int64_t>(total, std::max<int64_t>((halves ? 2 : 1) * kMaxDefaultWorkgroups,
                                                                    (total + per_wg - 1) / per_wg));
+    // (see the kernel: what more than 8 rows take, by the panels of a workgroup)
+    const Rows rows = batch <= 8 && m->G == 16 ? Rows::few : total <= kMaxDefaultWorkgroups ? Rows::turned : Rows::direct;
     const dim3 grid(static_cast<unsigned>(wgs)), block((halves ? kPanelWaves / 2 : kPanelWaves) * kLanes);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, static_cast<const uint16_t*>(x), headers[0], headers[1], headers[2],
-                           headers[3], data[0], data[1], data[2], data[3], tgt, static_cast<int>(m->K),
-                           static_cast<int>(m->n_slices), batch);
-    };
-    const auto pick = [&](auto multi, auto waves, auto quads) {
-        constexpr bool kMulti = decltype(multi)::value;
-        constexpr int kWaves = decltype(waves)::value;
-        constexpr int kQuads = decltype(quads)::value;
-        switch (m->bits * 1000 + m->G + (m->panel_integer_zeros ? 500 : 0)) {
-            case 4016: launch(gqsa_panel_kernel<4, 1, false, kMulti, kWaves, kQuads>); break;
-            case 4032: launch(gqsa_panel_kernel<4, 2, false, kMulti, kWaves, kQuads>); break;
-            case 4064: launch(gqsa_panel_kernel<4, 4, false, kMulti, kWaves, kQuads>); break;
-            case 4128: launch(gqsa_panel_kernel<4, 8, false, kMulti, kWaves, kQuads>); break;
-            case 8016: launch(gqsa_panel_kernel<8, 1, false, kMulti, kWaves, kQuads>); break;
-            case 8032: launch(gqsa_panel_kernel<8, 2, false, kMulti, kWaves, kQuads>); break;
-            case 8064: launch(gqsa_panel_kernel<8, 4, false, kMulti, kWaves, kQuads>); break;
-            case 4516: launch(gqsa_panel_kernel<4, 1, true, kMulti, kWaves, kQuads>); break;
-            case 4532: launch(gqsa_panel_kernel<4, 2, true, kMulti, kWaves, kQuads>); break;
-            case 4564: launch(gqsa_panel_kernel<4, 4, true, kMulti, kWaves, kQuads>); break;
-            case 4628: launch(gqsa_panel_kernel<4, 8, true, kMulti, kWaves, kQuads>); break;
-            case 8516: launch(gqsa_panel_kernel<8, 1, true, kMulti, kWaves, kQuads>); break;
-            case 8532: launch(gqsa_panel_kernel<8, 2, true, kMulti, kWaves, kQuads>); break;
-            case 8564: launch(gqsa_panel_kernel<8, 4, true, kMulti, kWaves, kQuads>); break;
+    // run(bits, chunks per group, integer zeros) for the format at hand
+    const auto pick = [&](auto run) {
+        using std::integral_constant;
+        const auto with = [&](auto bits, auto chunks) {
+            if (m->panel_integer_zeros) run(bits, chunks, std::true_type{});
+            else run(bits, chunks, std::false_type{});
+        };
+        const integral_constant<int, 4> four{};
+        const integral_constant<int, 8> eight{};
+        switch (m->bits * 1000 + m->G) {
+            case 4016: with(four, integral_constant<int, 1>{}); break;
+            case 4032: with(four, integral_constant<int, 2>{}); break;
+            case 4064: with(four, integral_constant<int, 4>{}); break;
+            case 4128: with(four, integral_constant<int, 8>{}); break;
+            case 8016: with(eight, integral_constant<int, 1>{}); break;
+            case 8032: with(eight, integral_constant<int, 2>{}); break;
+            case 8064: with(eight, integral_constant<int, 4>{}); break;
             default: return false;
         }
         return true;
+    };
+    const auto launch = [&](auto multi, auto waves, auto quads, auto more_rows) {
+        constexpr int kWaves = decltype(waves)::value, kQuads = decltype(quads)::value;
+        return pick([&](auto bits, auto chunks, auto integer_zeros) {
+            constexpr int kBits = decltype(bits)::value, kChunks = decltype(chunks)::value;
+            constexpr bool kInteger = decltype(integer_zeros)::value;
+            const auto go = [&](auto how) {
+                constexpr Rows kRows = decltype(how)::value;
+                if constexpr (decltype(multi)::value)
+                    hipLaunchKernelGGL((gqsa_panel_multi_kernel<kBits, kChunks, kInteger, kWaves, kQuads, kRows>), grid, block, 0, s, tgt,
+                                       static_cast<const uint16_t*>(x), headers[0], headers[1], headers[2], headers[3], data[0], data[1],
+                                       data[2], data[3], static_cast<int>(m->K), static_cast<int>(m->n_slices), batch, static_cast<int>(wgs));
+                else
+                    hipLaunchKernelGGL((gqsa_panel_kernel<kBits, kChunks, kInteger, kWaves, kQuads, kRows>), grid, block, 0, s,
+                                       static_cast<const uint16_t*>(x), headers[0], data[0], static_cast<int>(m->K),
+                                       static_cast<int>(m->n_slices), batch, static_cast<int>(wgs), tgt.total, tgt);
+            };
+            if constexpr (kChunks == 1) {
+                if (rows == Rows::few) {
+                    go(std::integral_constant<Rows, Rows::few>{});
+                    return;
+                }
+            }
+            go(more_rows);
+        });
     };
     using Whole = std::integral_constant<int, kPanelWaves>;
     using Half = std::integral_constant<int, kPanelWaves / 2>;
     using One = std::integral_constant<int, 1>;
     using Two = std::integral_constant<int, 2>;
-    const bool ok = n > 1 ? (many ? pick(std::true_type{}, Whole{}, Two{}) : pick(std::true_type{}, Whole{}, One{}))
-                          : (many ? pick(std::false_type{}, Half{}, Two{}) : pick(std::false_type{}, Whole{}, One{}));
+    using Direct = std::integral_constant<Rows, Rows::direct>;
+    using Turned = std::integral_constant<Rows, Rows::turned>;
+    const bool ok = n > 1 ? (many ? launch(std::true_type{}, Whole{}, Two{}, Direct{}) : launch(std::true_type{}, Whole{}, One{}, Direct{}))
+                  : many ? launch(std::false_type{}, Half{}, Two{}, Direct{})
+                  : rows == Rows::turned ? launch(std::false_type{}, Whole{}, One{}, Turned{})
+                                         : launch(std::false_type{}, Whole{}, One{}, Direct{});
     if (!ok) return GQSA_ERR_UNSUPPORTED;
     GQSA_HIP(hipGetLastError());
     return GQSA_OK;

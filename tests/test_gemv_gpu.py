@@ -915,6 +915,64 @@ def test_panel_kernel_ragged(torch_cuda, bits, G, batch):
     check(torch_cuda, h, c, gi.activations(batch, K, seed=11 + batch), panels=True)
 
 
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("integer_zeros", [True, False])
+def test_panel_kernel_up_to_eight_rows(torch_cuda, bits, integer_zeros):
+    """At most 8 activation rows (two columns a product): odd and even counts of columns around a pair, a unit (16 or 8
+    columns) and a slice (32), one panel and several, pruned rows next to full ones, and 9 rows beside them."""
+    rng = np.random.default_rng(17)
+    for N, columns in ((3, 1), (16, 2), (17, 7), (40, 8), (100, 9), (33, 16), (5000, 17), (20, 31), (4500, 33), (70, 127)):
+        K = 16 * columns
+        W = gi.dense_weight(N, K, seed=columns)
+        keep = rng.integers(0, columns + 1, N).astype(np.int32)
+        keep[::5] = columns
+        keep[N // 2] = 0
+        c = oracle.pack(W, 16, bits, keep_per_row=keep)
+        if not integer_zeros:
+            c.zeros = (c.zeros.view(np.float16) + rng.standard_normal(c.nnzg).astype(np.float16)).view(np.uint16)
+        h = gq.gqsa_import(c.rowIndex, c.groups, c.values, c.scales, c.zeros, N, K, 16, bits)
+        gq.gqsa_build_panels(h)
+        x = gi.activations(9, K, seed=columns + 1)
+        y8, _ = check(torch_cuda, h, c, x[:8], panels=True)
+        check(torch_cuda, h, c, x, panels=True)
+        for batch in (1, 5, 7):
+            y, _ = check(torch_cuda, h, c, x[:batch], panels=True)
+            assert np.array_equal(y.view(np.uint16), y8[:batch].view(np.uint16)), (N, columns, batch)
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("batch", [8, 16])
+def test_panel_kernel_infinite_activations_stay_in_their_column(torch_cuda, bits, batch):
+    """An infinite or undefined activation reaches the rows that store a group of its column, and no others: rows of even
+    columns, rows of odd ones, rows of all; the two columns of a pair share a product, absent groups read a neighbour's."""
+    N, columns = 48, 37
+    K = 16 * columns
+    W = gi.dense_weight(N, K, seed=3)
+    for r in range(N):
+        W.reshape(N, columns, 16)[r, (1 - r % 3) % 2::2] *= 1e-3 if r % 3 < 2 else 1.0    # r % 3: even columns, odd columns, all of them
+    keep = np.array([(columns + 1) // 2 if r % 3 == 0 else columns // 2 if r % 3 == 1 else columns for r in range(N)], np.int32)
+    c = oracle.pack(W, 16, bits, keep_per_row=keep)
+    stored = np.zeros((N, columns), bool)
+    for r in range(N):
+        stored[r, c.groups[c.rowIndex[r]:c.rowIndex[r + 1]]] = True
+    h = gq.gqsa_pack_rows(W, keep, 16, bits)
+    gq.gqsa_build_panels(h)
+    x = gi.activations(batch, K, seed=4)
+    plain, _ = check(torch_cuda, h, c, x, panels=True)
+    for row, column, value in ((0, 4, np.inf), (2, 5, -np.inf), (batch - 1, 36, np.nan)):
+        bad = x.copy()
+        bad[row, 16 * column + 3] = value
+        y = run_gemv(torch_cuda, h, bad, panels=True)
+        others = np.arange(batch) != row
+        assert np.array_equal(y[others].view(np.uint16), plain[others].view(np.uint16))
+        reached = stored[:, column]
+        assert not np.isfinite(y[row, reached]).any()
+        assert np.isfinite(y[row, ~reached]).all()
+        bad[row, 16 * column + 3] = 0
+        zero = run_gemv(torch_cuda, h, bad, panels=True)
+        assert np.array_equal(y[row, ~reached].view(np.uint16), zero[row, ~reached].view(np.uint16))
+
+
 def test_panel_kernel_unit_vectors_are_bit_exact(torch_cuda):
     """x = e_k in 16 activation rows: y[b] is column k_b of W^, and (q - z) s is exact in fp32, so
     every output is fp16((q - z) s) to the bit -- operand layout of the products, decode, scale
