@@ -338,6 +338,22 @@ struct Fmt {
     static constexpr int LOADS = UMAX * (PLANES + 2);    // load instructions per tile
 };
 
+// Where row b's activations begin in LDS, and its sums.  One or two rows: every row has both to itself, the sums 32 KGP bytes on.
+// Four or eight: the sums of four rows lie side by side, 16 bytes a slot at the place of the slot's activations (in what 48 bytes a
+// slot leave over behind the first of the four rows, or behind the fourth), so that a group's are one read at the address of
+// its activations where they were four with an address of their own: LDS bounds these kernels, and with pruned columns a
+// 16-byte read of the wavefront takes 12 cycles of a compute unit's LDS, four 4-byte reads 27.  4 / 8 rows, W4 S = 50 %:
+// 2 x 11008x4096 16.9 / 35.9 -> 16.1 / 34.3 us, 8192x8192 14.9 / 23.6 -> 14.1 / 22.1, 4096x14336 14.2 / 26.5 -> 13.5 / 25.0, 4096x4096 5.64 /
+// 9.23 -> 5.55 / 8.89; G = 64 5003x4160 8.35 / 13.55 -> 8.21 / 13.34.  (8 rows of 8-bit codes in the format's own tiles keep the
+// former places: the registers are not there, 14336x4096 26.9 -> 27.9.)
+template <typename F, int KGP, int NB>
+struct RowPlace {
+    static constexpr int kRow = row_bytes(KGP, NB, F::HALF);
+    static constexpr bool kSideBySide = NB >= 4 && !F::HALF && !(NB == 8 && F::BITS == 8 && F::M == 1 && !F::FLEX), kTight = kRow < 48 * KGP;
+    __host__ __device__ static constexpr int row(int b) { return kSideBySide && kTight ? (b / 4) * 4 * kRow + (b % 4) * 32 * KGP : b * kRow; }
+    __host__ __device__ static constexpr int sums(int b) { return kSideBySide ? (b / 4) * 4 * kRow + (kTight ? 128 : 32) * KGP : b * kRow + 32 * KGP; }
+};
+
 // The compressed groups of a tile, as loaded (one group per lane per block).
 template <typename F>
 struct Tile {
@@ -456,10 +472,10 @@ __device__ __forceinline__ void decode_chunk(const Tile<F>& t, int u, int i, Cod
 
 // x in LDS, per activation row: elements 0..7 of every group-column in 16-byte slots, elements
 // 8..15 in a second array of 16-byte slots 16*KGP bytes further on, and the fp32 sum of the 16
-// as a dense array of floats at 32*KGP (4 bytes per column: a wavefront's 64 reads of it spread
+// as a dense array of floats at 32*KGP (four rows and more: RowPlace; 4 bytes per column: a wavefront's 64 reads of it spread
 // over all banks instead of a quarter of them; with one 16-byte slot per sum the three reads of
 // a group would share an address and save a shift, but the kernels for several activation rows,
-// which LDS bounds, took 5 % longer).  Row b starts at b * row_bytes.  (G = 8: the same
+// which LDS bounds, took 5 % longer).  Row b starts at RowPlace::row(b).  (G = 8: the same
 // two arrays -- a group's 8 activations are one slot of the first or of the second -- and a sum
 // per half-slot, 8 bytes per column.)
 //
@@ -649,12 +665,20 @@ __device__ __forceinline__ void compute_tile(const MatArgs& m, const Tile<F>& t,
                 Codes c;
                 decode_chunk<F>(t, u, i, c);
                 const uint32_t sloti = kPlaced ? slot0 ^ (16u * i) : slot0 + 16u * i;
+                using Place = RowPlace<F, KGP, NB>;
+                uint4 four_sums{};
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const uint32_t xb = x0 + sloti + b * row_bytes(KGP, NB, F::HALF);
+                    const uint32_t xb = x0 + sloti + Place::row(b);
                     const uint4 xl = lds_read16(xb);
                     const uint4 xh = lds_read16(xb + 16 * KGP);
-                    const float xs = lds_read_float(x0 + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + (kPlaced ? sum0 ^ (4u * i) : sum0 + 4u * i));
+                    float xs;
+                    if constexpr (Place::kSideBySide) {
+                        if (b % 4 == 0) four_sums = lds_read16(x0 + sloti + Place::sums(b));
+                        xs = __builtin_bit_cast(float, b % 4 == 0 ? four_sums.x : b % 4 == 1 ? four_sums.y : b % 4 == 2 ? four_sums.z : four_sums.w);
+                    } else {
+                        xs = lds_read_float(x0 + Place::sums(b) + (kPlaced ? sum0 ^ (4u * i) : sum0 + 4u * i));
+                    }
                     const float d = __builtin_fmaf(-z, xs, dot16<F::BITS>(c, xl, xh));
                     dotz[b] = i == 0 ? d : dotz[b] + d;
                 }
@@ -968,7 +992,8 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
         // (where the slot and its sum lie: see compute_tile)
         const int at = column ^ ((column >> 4) & static_cast<int>(F::slot_mask(NB)));
         const int sum_at = column ^ ((column >> 6) & static_cast<int>(F::sum_mask(NB)));
-        uint8_t* slot = xlds + b * row_bytes(KGP, NB, F::HALF) + at * 16;
+        using Place = RowPlace<F, KGP, NB>;
+        uint8_t* slot = xlds + Place::row(b) + at * 16;
         *reinterpret_cast<uint4*>(slot) = lo;
         *reinterpret_cast<uint4*>(slot + 16 * KGP) = hi;
         const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -985,7 +1010,7 @@ __global__ __launch_bounds__(kWavesPerWorkgroup * kLanes) void gqsa_gemv_kernel(
             float s = 0.0f;      // sum of the slot's 16 activations, fp32: a pair per instruction
 #pragma unroll
             for (int i = 0; i < 8; ++i) s = __builtin_amdgcn_fdot2(as_half2(w[i]), ones, s, false);
-            *reinterpret_cast<float*>(xlds + b * row_bytes(KGP, NB, F::HALF) + 32 * KGP + sum_at * 4) = s;
+            *reinterpret_cast<float*>(xlds + Place::sums(b) + (Place::kSideBySide ? at * 16 + (b % 4) * 4 : sum_at * 4)) = s;
         }
     };
     // x into LDS (the loads of the tiles are already out), then the workgroup meets
