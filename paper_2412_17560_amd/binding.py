@@ -259,11 +259,11 @@ def gqsa_info(h: GqsaHandle) -> dict:
 def gqsa_export(h: GqsaHandle) -> dict:
     info = gqsa_info(h)
     nnz = info["nnz_groups"]
-    ri = np.zeros(info["N"] + 1, dtype=np.int32)
-    gr = np.zeros(nnz, dtype=np.int32)
-    va = np.zeros(info["values_bytes"], dtype=np.uint8)
-    sc = np.zeros(nnz, dtype=np.uint16)
-    ze = np.zeros(nnz, dtype=np.uint16)
+    ri = np.empty(info["N"] + 1, dtype=np.int32)        # (written in full by the call)
+    gr = np.empty(nnz, dtype=np.int32)
+    va = np.empty(info["values_bytes"], dtype=np.uint8)
+    sc = np.empty(nnz, dtype=np.uint16)
+    ze = np.empty(nnz, dtype=np.uint16)
     _check(_lib().gqsa_export(h.ptr, _np_ptr(ri), _np_ptr(gr) if nnz else None,
                               _np_ptr(va) if nnz else None, _np_ptr(sc) if nnz else None,
                               _np_ptr(ze) if nnz else None), "gqsa_export")
