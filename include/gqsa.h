@@ -239,7 +239,8 @@ gqsa_status_t gqsa_set_partition_rows(gqsa_handle_t h, int tile_blocks, int tile
 gqsa_status_t gqsa_build_panels(gqsa_handle_t h);
 
 /* gqsa_gemv from the second image whatever the batch (1..16): same arguments, same checks;
- * GQSA_ERR_UNSUPPORTED if the handle has no such image. */
+ * GQSA_ERR_UNSUPPORTED if the handle has no such image.  A row has the same bits in every batch of up to 8 rows, and
+ * in every batch of 9 to 16; with G = 16 the two add a row's products in different orders. */
 gqsa_status_t gqsa_gemv_panels(gqsa_handle_t h, const void* x_dev, void* y_dev, int batch, void* hip_stream);
 
 /* Copy the exact bytes of that second image into host_buf; bytes >= panel_bytes of gqsa_info.
