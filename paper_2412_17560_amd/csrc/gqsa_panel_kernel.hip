@@ -230,7 +230,7 @@ __device__ __forceinline__ void panel_products(
     // of their own, and x arrives at 16 bytes a cycle and compute unit: 3.5 us for 16 rows of 4096.
     // turned: a lane loads 16 bytes of row lane / 4, four lanes next to each other in memory -- 1.2 us for the same rows -- and
     // what it needs of them comes out of a turn through LDS, rows 80 bytes apart there so that the lanes' accesses spread
-    // over the banks.  Only where a workgroup has one panel: with more of them the wavefronts whose activations
+    // over the banks.  Only from 10 or 12 rows on (see panels_gemm) and where a workgroup has one panel: with more of them the wavefronts whose activations
     // arrive first multiply while the others' are on their way, and the turn is one thing more to do.  (direct / turned, 16 rows, W4 S = 50 %:
     // 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; but 3 x 4096x4096
     // in one launch 13.6 / 13.9, 8192x11008 19.4 / 20.1.)
@@ -824,8 +824,17 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     const int64_t per_wg = many ? 2 * kPanelsPerQuad : kPanelsPerQuad;
     const int64_t wgs = std::min<int64_t>(total, std::max<int64_t>((halves ? 2 : 1) * kMaxDefaultWorkgroups,
                                                                    (total + per_wg - 1) / per_wg));
-    // (see the kernel: what more than 8 rows take, by the panels of a workgroup)
-    const Rows rows = batch <= 8 && m->G == 16 ? Rows::few : total <= kMaxDefaultWorkgroups ? Rows::turned : Rows::direct;
+    // What the forms are for: see the kernel.  turned takes the same time whatever the rows, direct less with fewer of them (the copies of
+    // the last one are one request), so it is the rows that decide.  direct / turned, one matrix of at most 256 panels, S = 50 %:
+    //   4-bit codes, G > 16, 3, 8, 9, 10, 12, 16 rows of 4096x11008 G = 64: 10.0, 11.1, 11.2, 12.2, 13.6, 15.8 against 12.3, 12.1, 12.2, 12.2, 12.3, 12.7 us
+    //     (25 sizes, mean of turned / direct: 1.14, 1.01, 1.01, 0.97, 0.92, 0.85);
+    //   8-bit codes, G > 16, 3, 8, 10, 12, 14, 16 rows of 4096x11008 G = 64: 11.2, 11.4, 12.0, 12.9, 13.8, 15.5 against 12.3, 12.3, 12.4, 12.5, 12.7, 12.7
+    //     (16 sizes: 1.08, 1.05, 1.04, 0.985, 0.955, 0.89);
+    //   G = 16, 9, 10, 12, 16 rows of 4096x4096 W4: 6.7, 6.7, 6.9, 7.5 against 7.0, 6.8, 6.8, 6.9 (8 sizes: 1.05, 1.04, 0.99, 0.91; W8 1.05, 1.03, 1.01, 0.96).
+    // Several matrices always take direct: no joint launch of one panel a workgroup has been compiled or measured in the turned form.
+    const int turned_from = m->bits == 4 && m->G > 16 ? 10 : 12;
+    const Rows rows = batch <= 8 && m->G == 16 ? Rows::few
+                    : n == 1 && total <= kMaxDefaultWorkgroups && batch >= turned_from ? Rows::turned : Rows::direct;
     const dim3 grid(static_cast<unsigned>(wgs)), block((halves ? kPanelWaves / 2 : kPanelWaves) * kLanes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // run(bits, chunks per group, integer zeros) for the format at hand
