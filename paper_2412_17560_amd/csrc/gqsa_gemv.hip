@@ -344,12 +344,17 @@ struct Fmt {
 // its activations where they were four with an address of their own: LDS bounds these kernels, and with pruned columns a
 // 16-byte read of the wavefront takes 12 cycles of a compute unit's LDS, four 4-byte reads 27.  4 / 8 rows, W4 S = 50 %:
 // 2 x 11008x4096 16.9 / 35.9 -> 16.1 / 34.3 us, 8192x8192 14.9 / 23.6 -> 14.1 / 22.1, 4096x14336 14.2 / 26.5 -> 13.5 / 25.0, 4096x4096 5.64 /
-// 9.23 -> 5.55 / 8.89; G = 64 5003x4160 8.35 / 13.55 -> 8.21 / 13.34.  (8 rows of 8-bit codes in the format's own tiles keep the
-// former places: the registers are not there, 14336x4096 26.9 -> 27.9.)
+// 9.23 -> 5.55 / 8.89; G = 64 5003x4160 8.35 / 13.55 -> 8.21 / 13.34.
+// kApart: 8-bit codes in the format's own tiles, the form with the fewest registers to spare, keep every row's sums to themselves where
+// that is faster.  8 rows: 14336x4096 26.9 us, side by side 27.9.  4 rows beyond K = 8192, apart / side by side: 2500x16384 S = 0
+// 19.5 / 21.4, 4096x14336 23.0 / 24.7, 4096x11008 S = 10 % 18.8 / 20.4, 8192x11008 28.2 / 28.5, only 1000x14336 S = 30 % 10.1 / 9.8 (mean of 60
+// matrices 1.007); unpruned from K > 4096 on: 14336x8192 34.5 / 36.0.  Pruned ones of 4096 < K <= 8192 are 1 % ahead side by
+// side in the mean of 29, those with one tile a worker (1500x8192 S = 30 % 9.15 / 8.7), not those with several (4096x8192 13.2 / 14.1).
 template <typename F, int KGP, int NB>
 struct RowPlace {
     static constexpr int kRow = row_bytes(KGP, NB, F::HALF);
-    static constexpr bool kSideBySide = NB >= 4 && !F::HALF && !(NB == 8 && F::BITS == 8 && F::M == 1 && !F::FLEX), kTight = kRow < 48 * KGP;
+    static constexpr bool kApart = F::BITS == 8 && F::M == 1 && !F::FLEX && (NB == 8 || KGP >= (F::SPREAD ? 512 : 768));
+    static constexpr bool kSideBySide = NB >= 4 && !F::HALF && !kApart, kTight = kRow < 48 * KGP;
     __host__ __device__ static constexpr int row(int b) { return kSideBySide && kTight ? (b / 4) * 4 * kRow + (b % 4) * 32 * KGP : b * kRow; }
     __host__ __device__ static constexpr int sums(int b) { return kSideBySide ? (b / 4) * 4 * kRow + (kTight ? 128 : 32) * KGP : b * kRow + 32 * KGP; }
 };

@@ -108,6 +108,20 @@ def test_panel_kernels_wait_for_their_lds_reads_before_staging_over_them(code_ob
     assert not found
 
 
+def test_sums_of_8_bit_codes_lie_apart_where_that_is_faster(code_objects):
+    """A kernel for 4 or 8 rows reads four rows' sums of a slot at once (16 bytes) unless every row keeps its own (4 bytes each): with
+    8-bit codes in the format's own tiles 8 rows do, and 4 rows of K > 8192, unpruned of K > 4096: 4096x11008 took 20.4 us, not 18.8."""
+    apart = set()
+    for f in code_objects:
+        for name, code in _kernels(f, "gqsa_gemv_kernel"):
+            form = re.search(r"FmtILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EEELi(\d+)ELi(\d+)E", name)
+            bits, chunks, blocks, spread, slots, rows = map(int, form.groups())
+            if rows >= 4 and chunks >= 1 and any(c[1].startswith(("ds_read_b32", "ds_read2")) for c in code):
+                apart.add((bits, chunks, blocks, spread, slots, rows))
+    assert apart == ({(8, 1, 0, spread, slots, 8) for spread in (0, 1) for slots in (256, 512)}
+                     | {(8, 1, 0, spread, slots, 4) for spread in (0, 1) for slots in (768, 1024)} | {(8, 1, 0, 1, 512, 4)})
+
+
 def test_gemv_kernels_keep_their_registers(code_objects):
     """A GEMV kernel that runs out of registers waits for its own spills between the loads of x and those of the tile:
     with 24 of them 8 rows of 4096x8192 W8 took longer in one launch than in two of 4 rows.  Four words a lane at most."""
