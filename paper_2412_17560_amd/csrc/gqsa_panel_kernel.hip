@@ -433,16 +433,22 @@ __device__ __forceinline__ void panel_products(
     const auto products_few = [&](float* sums, uint32_t words, uint32_t records) {
         constexpr int PAIRS = HC / 2;
         constexpr int STEP = INTZ && (QUADS == 1 || BITS == 8) ? 4 : 2;       // pairs under way together (registers)
+        // (pairs whose records are held together: with the sums of eight panels and two sums a pair there are registers for half of them;
+        // all of them, 39 spilled, took 3 to 17 % longer: W4, any zeros, 8 rows of 20000x4096 S = 50 % 16.8 -> 15.6 us, 2 x 11008x4096 21.2 -> 19.5, 32000x2048 S = 30 % 17.2 -> 14.7)
+        constexpr int HELD = FEW && !INTZ && QUADS == 2 && BITS == 4 ? PAIRS / 2 : PAIRS;
         const uint32_t upto = (2u << r) - 1u, own = 1u << r;
         const uint32_t before = (words >> 16) * RB + (records - (word_of(words, 0) >> 16) * RB - RB + (PAIRED8 ? 12u * (j & 1) : 0u));
         const uint32_t to_codes = 8u * (j & 1);             // 4-bit: codes, scale | zero, codes
-        uint32_t code[PAIRS][BITS / 4], sz[PAIRS];
-        bool present[PAIRS];
-        for_each_index<PAIRS>([&](auto index) {
+        for_each_index<PAIRS / HELD>([&](auto part) {
+        constexpr int p0 = decltype(part)::value * HELD;
+        if (p0 > 0) asm volatile("" ::: "memory");
+        uint32_t code[HELD][BITS / 4], sz[HELD];
+        bool present[HELD];
+        for_each_index<HELD>([&](auto index) {
             constexpr int i = decltype(index)::value;
             // the header word and the byte offset of lane i of the lane's 16: its column's
-            const uint32_t mask = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(words), 0x150 + i, 0xF, 0xF, true)) & upto;
-            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(before), 0x150 + i, 0xF, 0xF, true)) +
+            const uint32_t mask = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(words), 0x150 + p0 + i, 0xF, 0xF, true)) & upto;
+            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(before), 0x150 + p0 + i, 0xF, 0xF, true)) +
                                 static_cast<uint32_t>(__builtin_popcount(mask)) * RB;
             present[i] = mask >= own;
             if constexpr (PAIRED8) {
@@ -456,7 +462,7 @@ __device__ __forceinline__ void panel_products(
             }
         });
 #pragma unroll
-        for (int i0 = 0; i0 < PAIRS; i0 += STEP) {
+        for (int i0 = 0; i0 < HELD; i0 += STEP) {
             float4_t d[STEP], e[STEP];
 #pragma unroll
             for (int i = 0; i < STEP; ++i) {
@@ -482,7 +488,7 @@ __device__ __forceinline__ void panel_products(
                         q[2 * t + 1] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(code[i0 + i][t * (BITS / 4 - 1)], dk.splice, 0x01070106u)) - off_lo;
                     }
                 }
-                const half8_t a = __builtin_bit_cast(half8_t, xp8[FEW ? i0 + i : 0]);
+                const half8_t a = __builtin_bit_cast(half8_t, xp8[FEW ? p0 + i0 + i : 0]);
                 const half8_t b = {q[0].x, q[0].y, q[1].x, q[1].y, q[2].x, q[2].y, q[3].x, q[3].y};
                 d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, zero4, 0, 0, 0);
                 if constexpr (!INTZ) {
@@ -506,6 +512,7 @@ __device__ __forceinline__ void panel_products(
                 }
             }
         }
+        });
     };
 
     const auto turn_x = [&]() {
