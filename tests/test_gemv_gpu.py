@@ -1020,6 +1020,24 @@ def test_panel_kernel_up_to_eight_rows(torch_cuda, bits, integer_zeros):
             assert np.array_equal(y.view(np.uint16), y8[:batch].view(np.uint16)), (N, columns, batch)
 
 
+@pytest.mark.parametrize("integer_zeros", [True, False])
+@pytest.mark.parametrize("bits,G", [(4, 16), (4, 32), (4, 64), (4, 128), (8, 16), (8, 32), (8, 64)])
+def test_panel_kernel_rows_have_the_same_bits_in_other_batches(torch_cuda, bits, G, integer_zeros):
+    """A row has the same bits in every batch of up to 8 rows and in every batch of 9 to 16, and with G > 16 in all of them, whichever
+    way the activations are loaded (one matrix of at most 256 panels: another way from 10 or 12 rows on; more panels: one way)."""
+    for N, K in ((70, 35 * G), (4112, 16 * G)):
+        c = oracle.pack(gi.dense_weight(N, K, seed=51), G, bits, sparsity=0.4)
+        if not integer_zeros:
+            c.zeros = (c.zeros.view(np.float16) + np.float16(0.375)).view(np.uint16)
+        h = gq.gqsa_import(c.rowIndex, c.groups, c.values, c.scales, c.zeros, N, K, G, bits)
+        gq.gqsa_build_panels(h)
+        x = gi.activations(16, K, seed=52)
+        y = {batch: check(torch_cuda, h, c, x[:batch], panels=True)[0].view(np.uint16) for batch in (1, 3, 8, 9, 10, 11, 12, 13, 16)}
+        for batch, rows in y.items():
+            same = y[8] if batch <= 8 and G == 16 else y[16]
+            assert np.array_equal(rows, same[:batch]), (N, batch)
+
+
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("batch", [8, 16])
 def test_panel_kernel_infinite_activations_stay_in_their_column(torch_cuda, bits, batch):
@@ -1053,23 +1071,26 @@ def test_panel_kernel_infinite_activations_stay_in_their_column(torch_cuda, bits
         assert np.array_equal(y[row, ~reached].view(np.uint16), zero[row, ~reached].view(np.uint16))
 
 
-def test_panel_kernel_unit_vectors_are_bit_exact(torch_cuda):
+@pytest.mark.parametrize("bits", [4, 8])
+def test_panel_kernel_unit_vectors_are_bit_exact(torch_cuda, bits):
     """x = e_k in 16 activation rows: y[b] is column k_b of W^, and (q - z) s is exact in fp32, so
     every output is fp16((q - z) s) to the bit -- operand layout of the products, decode, scale
-    and zero with no tolerance."""
+    and zero with no tolerance.  8 of them at a time as well: two columns a product, every place in a
+    column and columns on both sides of a pair."""
     N, K = 100, 1024
     W = gi.dense_weight(N, K, seed=95)
-    c = oracle.pack(W, 16, 4, sparsity=0.5)
-    h = gq.gqsa_pack(W, 16, 4, 0.5)
+    c = oracle.pack(W, 16, bits, sparsity=0.5)
+    h = gq.gqsa_pack(W, 16, bits, 0.5)
     gq.gqsa_build_panels(h)
     ks = [0, 1, 15, 16, 17, 255, 256, 511, 512, 513, 777, 1000, 1008, 1022, 1023, 300]
-    x = np.zeros((16, K), dtype=np.float16)
-    for b, k in enumerate(ks):
-        x[b, k] = 1.0
-    y = run_gemv(torch_cuda, h, x)        # 16 rows: gqsa_gemv itself takes the panel image
     Wd = oracle.densify(c)
-    ref = Wd[:, ks].T.astype(np.float32).astype(np.float16)
-    assert np.array_equal(y.view(np.uint16), ref.view(np.uint16))
+    for group in (ks, ks[:8], ks[8:], *(range(k, k + 8) for k in (0, 8, 16, 24, 992, 1000, 1008, 1016))):
+        x = np.zeros((len(group), K), dtype=np.float16)
+        for b, k in enumerate(group):
+            x[b, k] = 1.0
+        y = run_gemv(torch_cuda, h, x)        # from 5 rows on gqsa_gemv itself takes the panel image
+        ref = Wd[:, list(group)].T.astype(np.float32).astype(np.float16)
+        assert np.array_equal(y.view(np.uint16), ref.view(np.uint16))
 
 
 def test_panel_kernel_only_from_five_rows(torch_cuda):
@@ -1210,7 +1231,9 @@ def test_panel_kernel_dense_panels(torch_cuda, bits, G, sparsity):
     c = oracle.pack(W, G, bits, sparsity=sparsity)
     h = gq.gqsa_pack(W, G, bits, sparsity)
     gq.gqsa_build_panels(h)
-    check(torch_cuda, h, c, gi.activations(16, K, seed=16), panels=True)
+    x = gi.activations(16, K, seed=16)
+    check(torch_cuda, h, c, x, panels=True)
+    check(torch_cuda, h, c, x[:8], panels=True)
 
 
 @pytest.mark.parametrize("bits,G", [(4, 16), (8, 16), (4, 64), (8, 32)])
@@ -1239,7 +1262,9 @@ def test_panel_kernel_any_zero(torch_cuda, bits, G, zeros):
     h = gq.gqsa_import(c.rowIndex, c.groups, c.values, c.scales, c.zeros, N, K, G, bits)
     gq.gqsa_build_panels(h)
     assert gq.gqsa_info(h)["panel_integer_zeros"] == (1 if zeros == "extreme_integers" else 0)
-    check(torch_cuda, h, c, gi.activations(16, K, seed=15), panels=True)
+    x = gi.activations(16, K, seed=15)
+    check(torch_cuda, h, c, x, panels=True)
+    check(torch_cuda, h, c, x[:8], panels=True)
 
 
 @pytest.mark.parametrize("bits,shape_idx", [(4, 0), (8, 1)])

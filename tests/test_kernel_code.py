@@ -94,17 +94,17 @@ def test_the_check_itself_sees_a_missing_wait():
 
 
 def test_panel_kernels_wait_for_their_lds_reads_before_staging_over_them(code_objects):
-    """The panel kernel stages a unit's records by loads from global memory straight into LDS, over the records of
-    the panels, quad or unit before.  In no compiled form may such a load be reached while reads of those
-    are outstanding."""
-    checked, found = 0, {}
+    """The panel kernels (of one matrix and of several: gqsa_panel_kernel, gqsa_panel_multi_kernel) stage a unit's records by
+    loads from global memory straight into LDS, over the records of the panels, quad or unit before.  In no
+    compiled form may such a load be reached while reads of those are outstanding."""
+    checked, found = set(), {}
     for f in code_objects:
-        for name, code in _kernels(f, "gqsa_panel_kernel"):
+        for name, code in _kernels(f, "gqsa_panel_"):
             assert any("load_lds" in c[1] for c in code), name
-            checked += 1
+            checked.add(re.search(r"gqsa_panel\w*?kernelI\w*?ELNS0_4RowsE\d", name)[0])
             if late := _loads_into_lds_with_reads_outstanding(code):
                 found[name] = len(late)
-    assert checked >= 28
+    assert len(checked) == 86 and sum("multi" in name for name in checked) == 36
     assert not found
 
 
