@@ -71,17 +71,18 @@ gqsa_status_t upload(gqsa_matrix* m)
 }
 
 // Calls with this many activation rows or more go to the matrix-core kernel if the handle has a
-// panel image.  Its time hardly depends on the row count (16 rows' worth of products either way) and little on
-// the pruning; the wavefront kernel's grows with the rows and with the stored groups.  With G = 16 and K up to 8192 they
-// cross between 4 and 5 rows, with 4-bit codes in larger groups between 2 and 3 (4096x4096 at S = 50 %, 4 rows: G = 32 6.1
-// against 5.3 us; 4096x11008 13.9 against 9.5), and so with 8-bit codes in larger groups beyond K = 8192 (4096x11008, 3 and 4 rows: 13.0
-// against 11.0).  In the two classes between, whether 3 and 4 rows take them depends on the share of the groups that is stored:
-//   G = 16 beyond K = 8192, 4 rows of 4096x11008 W4 / W8 at S = 0: 22.5 / 21.8 against 11.5 / 15.1 us; 30 % 12.5 / 17.9 against 11.2 / 14.3;
-//     50 % 10.3 / 14.4 against 11.3 / 13.6; 70 % 8.2 / 8.0 against 10.8 / 13.0 (16 sizes, 12 with 8-bit codes, mean of the quotients: W4 1.32, 1.08, 0.87,
-//     0.70, at 40 % 1.00; W8 1.14, 1.04, 0.86, 0.64, at 40 % 1.03);
-//   8-bit codes in larger groups up to K = 8192, 4 rows of 4096x4096 G = 32 at S = 0, 30, 45, 50, 70 %: 6.9, 8.5, 8.5, 5.3, 5.6 against
-//     6.2, 5.9, 6.0, 6.0, 5.9 us (26 sizes, mean of the quotients: 1.04, 1.35, 1.19, 0.89, 0.87).
-// (All of one matrix again and again, so from the caches on both sides.)
+// panel image.  Its time depends little on the rows -- up to 8 rows of G = 16 two columns share a product, so the same work whatever
+// the rows, 9 to 16 rows take the next form; with G > 16 16 rows' worth of products at every batch -- and little on the pruning;
+// the wavefront kernel's grows with the rows and with the stored groups.  Where the two cross, wavefront / panel kernel, 3 and 4 rows
+// alike (4 given), every matrix from memory, mean of the quotients (11 sizes with G = 16, 6 with G > 16):
+//   G = 16, K <= 8192 at S = 0, 30, 50, 70 %: W4 1.25, 1.04, 0.92, 0.81; W8 0.99, 1.02, 0.91, 0.77 (single sizes 0.6 to 2.2 either side);
+//   G = 16, K > 8192: W4 1.48, 1.14, 1.09, 0.83; W8 1.01, 0.95, 0.96, 0.74 (from the caches 1.13, 1.06, 1.08, 0.73);
+//   G > 16, K <= 8192: W4 1.18, 2.14, 1.12, 1.12; W8 0.89, 1.32, 0.85, 0.90;
+//   G > 16, K > 8192: W4 1.61, 1.21, 1.24, 0.96; W8 1.28, 1.11, 0.99, 0.85.
+// So 3 rows with 4-bit codes in larger groups, with 8-bit codes in larger groups beyond K = 8192; in the two classes between
+// by the share of the groups that is stored; 5 rows with G = 16 up to K = 8192, where the mean over all prunings is 1.  (The line
+// of 52 % is from matrices timed from the caches and, with G = 16, from before two columns shared a product: 50 % pruned 4-bit ones of
+// K > 8192 and unpruned 4-bit ones up to there would now be better off with the panel kernel, 8-bit ones would not.)
 // The share and not the size, though a matrix of few rows would be better off with the other kernel: the matrices of
 // one call (q/k/v) differ in size but are pruned alike, and they must choose alike to go out together.
 int panel_min_batch(const gqsa_matrix* m)
