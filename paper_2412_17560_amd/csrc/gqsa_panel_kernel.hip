@@ -117,9 +117,12 @@ struct PanelTargets {
 // column at hand) follows from the header with a masked population count.  Fetching 8 bytes per
 // lane from global memory instead kept 1.5 KB per wavefront under way where this keeps 6 KB.
 // No lane reads conditionally: one whose row has no group in a column reads a neighbouring
-// record (or the bytes behind the last one), and what it computes from it stays in its own
-// column of the product, which it then leaves out.  Likewise the activation rows beyond `batch`
-// are copies of the last one: they only reach result rows that are never stored.
+// record.  More than 8 rows, or G > 16: the next one or the bytes behind the last; whatever it computes from them stays
+// in its own column of the product, which it then leaves out.  Two columns a product (few): the record before, or the
+// zeros ahead of the first one.  What it decodes from that also enters the sums that another lane of the same output row
+// keeps, times the zeros that the activations hold there -- so it has to be finite, which decoded codes always are and
+// the zeros are.  The activation rows beyond `batch` are copies of the last one: they only reach result rows
+// that are never stored.
 // Operands of v_mfma_f32_16x16x16_f16 in a wavefront: lane l holds A[l % 16][4 (l / 16) .. + 3],
 // B[4 (l / 16) .. + 3][l % 16] and receives D[4 (l / 16) .. + 3][l % 16].  Here A = the
 // activations (row = activation row, 16 elements of one group-column), B = the codes (column =
@@ -299,8 +302,8 @@ __device__ __forceinline__ void panel_products(
     uint32_t slot[kPanelsPerQuad];      // where a panel's records begin in the staging area
     // few: stages a unit's records of the panels from pp on of a quad, from byte `at` of the area on, as many as fit: returns
     // one past the last.  The records of a panel in a unit are contiguous (first group of the first column .. last group of
-    // the last column); they go one panel's after the other's, each rounded up to 16 bytes plus room for one more record (a
-    // lane without a group may read the one behind the last).  Every lane copies 16 bytes per KiB of them, global memory ->
+    // the last column); they go one panel's after the other's, each rounded up to 16 bytes with room for one more record ahead of it (a
+    // lane without a group reads the one before, and before the first one there are zeros).  Every lane copies 16 bytes per KiB of them, global memory ->
     // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers.
     const auto stage = [&](const Header& h, int quad, int from_panel, uint32_t at) {
         // The records go where others lay.  A lane's reads of those must be back first -- the loads into LDS are not
@@ -564,7 +567,7 @@ __device__ __forceinline__ void panel_products(
 #pragma unroll
             for (int quad = 0; quad < QUADS; ++quad) {
                 if (quad > 0 && !is_live(quad * kPanelsPerQuad)) break;
-                int end = stage(h, quad, 0, kSpare);        // (a lane without a group may read the record before)
+                int end = stage(h, quad, 0, kSpare);        // (room ahead of the first record: see stage)
                 if (quad == 0) {
                     load_x(unit);
                     if (kAhead && unit + WAVES < n_units) h_next = load_header(unit + WAVES);
@@ -646,7 +649,7 @@ __device__ __forceinline__ void panel_products(
                         // The records go where others lay: panels 0 and 1, the quad before, the unit before.  A lane's
                         // reads of those must be back first -- the loads into LDS are not ordered against
                         // them, and the compiler waits for a value where it is used, which may be further down
-                        // (in 8 of the 56 compiled forms it was).
+                        // (and is, in some of the compiled forms).
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                         // stage: every lane copies 16 bytes per KiB of a panel's records, global memory ->
                         // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers
