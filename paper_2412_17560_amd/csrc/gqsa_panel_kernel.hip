@@ -48,33 +48,38 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float v)
     return __builtin_bit_cast(uint16_t, static_cast<_Float16>(v));     // round to nearest even
 }
 
-// Four codes -> four fp16 numbers, exactly: 0x6400 | q is the fp16 number 1024 + q (q < 1024), and
-// 0x6400 | q << 4 is 1024 + 16 q, which one fused multiply-add turns into q (x 1/16, - 64: both
-// steps exact).  `splice` = 0x64006400.  What is subtracted comes from the caller: 1024 and 64
-// for the plain codes, 1024 + z and 64 + z for codes minus zero (exact for an integer z of at most
-// 1024 in magnitude: every intermediate and the result are integers below 2048).
-// 4-bit: `pair` holds the two bytes (e0 | e2 << 4), (e1 | e3 << 4) in bits 0..7 and 16..23;
-// `nib` = 0x000F000F and `nib << 4`, kept in vector registers so that AND and OR are one instruction.
+// Four codes -> four fp16 numbers in units of 2^-9, exactly: a code in the low bits of an empty 16-bit half is the fp16 subnormal
+// q 2^-24, at bits 4..7 it is q 2^-20, and one fused multiply-add by 2^15 or 2^11 turns either into (q - z) 2^-9 (`off` = -z 2^-9, twice;
+// an integer z of at most 1024 in magnitude: every intermediate and the result are integers below 2048 in that unit, so each
+// step is exact) -- or, without a zero, into q 2^-9.  The unit travels with the sums and comes off the results, a power of two: the same bits as
+// with the plain integers.  (A splice with 1024 in front of the codes, taken off again, took one instruction more for the zero and an AND-OR
+// -- 5.3 cycles -- where an AND -- 3 -- is enough.)
+// 4-bit: `pair` holds the two bytes (e0 | e2 << 4), (e1 | e3 << 4) in bits 0..7 and 16..23.
+constexpr float kUnitInverse = 512.0f;
 struct DecodeConstants {
-    uint32_t splice, nib_lo, nib_hi;
-    half2_t sixteenth;
+    uint32_t nib_lo, nib_hi;      // 0x000F000F and << 4
+    half2_t low, high;            // 2^15 for codes in the low bits, 2^11 at bits 4..7
 };
-__device__ __forceinline__ half4_t decode4_w4(uint32_t pair, const DecodeConstants& k, half2_t off_lo, half2_t off_hi)
+template <bool INTZ>
+__device__ __forceinline__ half2_t to_unit(uint32_t codes, half2_t times, half2_t off)
 {
-    const uint32_t lo = (pair & k.nib_lo) | k.splice;            // 1024 + e0, 1024 + e1
-    const uint32_t hi = (pair & k.nib_hi) | k.splice;            // 1024 + 16 e2, 1024 + 16 e3
-    const half2_t a = __builtin_bit_cast(half2_t, lo) - off_lo;
-    const half2_t b = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, hi), k.sixteenth, -off_hi);
+    const half2_t q = __builtin_bit_cast(half2_t, codes);
+    return INTZ ? __builtin_elementwise_fma(q, times, off) : q * times;
+}
+template <bool INTZ>
+__device__ __forceinline__ half4_t decode4_w4(uint32_t pair, const DecodeConstants& k, half2_t off)
+{
+    const half2_t a = to_unit<INTZ>(pair & k.nib_lo, k.low, off);
+    const half2_t b = to_unit<INTZ>(pair & k.nib_hi, k.high, off);
     return half4_t{a.x, a.y, b.x, b.y};
 }
 // 8-bit: four bytes, one per element, in the word of the pair (upper, lower) that `sel` names:
 // sel = 0x0c010c00 for the lower word, 0x0c050c04 for the upper one.
-__device__ __forceinline__ half4_t decode4_w8(uint32_t upper, uint32_t lower, uint32_t sel, const DecodeConstants& k, half2_t off_lo)
+template <bool INTZ>
+__device__ __forceinline__ half4_t decode4_w8(uint32_t upper, uint32_t lower, uint32_t sel, const DecodeConstants& k, half2_t off)
 {
-    const uint32_t lo = __builtin_amdgcn_perm(upper, lower, sel) | k.splice;                  // bytes 0, 1
-    const uint32_t hi = __builtin_amdgcn_perm(upper, lower, sel + 0x00020002u) | k.splice;    // bytes 2, 3
-    const half2_t a = __builtin_bit_cast(half2_t, lo) - off_lo;
-    const half2_t b = __builtin_bit_cast(half2_t, hi) - off_lo;
+    const half2_t a = to_unit<INTZ>(__builtin_amdgcn_perm(upper, lower, sel), k.low, off);                  // bytes 0, 1
+    const half2_t b = to_unit<INTZ>(__builtin_amdgcn_perm(upper, lower, sel + 0x00020002u), k.low, off);    // bytes 2, 3
     return half4_t{a.x, a.y, b.x, b.y};
 }
 
@@ -271,15 +276,15 @@ __device__ __forceinline__ void panel_products(
     };
 
     const uint32_t below = (1u << r) - 1u;
-    DecodeConstants dk;       // (kept out of the compiler's sight as constants: it would split the AND-OR)
-    asm volatile("s_mov_b32 %0, 0x64006400" : "=s"(dk.splice));
-    asm volatile("v_mov_b32 %0, 0x000F000F" : "=v"(dk.nib_lo));
-    asm volatile("v_mov_b32 %0, 0x00F000F0" : "=v"(dk.nib_hi));
-    dk.sixteenth = half2_t{(_Float16)0.0625f, (_Float16)0.0625f};
-    const half2_t k1024 = {(_Float16)1024.0f, (_Float16)1024.0f};
-    const half2_t k64 = {(_Float16)64.0f, (_Float16)64.0f};
+    DecodeConstants dk;
+    dk.nib_lo = 0x000F000Fu;
+    dk.nib_hi = 0x00F000F0u;
+    dk.low = half2_t{(_Float16)32768.0f, (_Float16)32768.0f};
+    dk.high = half2_t{(_Float16)2048.0f, (_Float16)2048.0f};
+    constexpr _Float16 zero_unit = (_Float16)(-1.0f / kUnitInverse);
     const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    const half4_t ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
+    constexpr _Float16 kOne = (_Float16)(1.0f / kUnitInverse);
+    const half4_t ones = {kOne, kOne, kOne, kOne};
     // a lane supplies elements 0-3, 8-11, 4-7, 12-15 of every chunk for j = 0..3: quarters 0, 2, 1, 3
     const uint32_t quarter = 2u * (j & 1) + (j >> 1);
     const uint32_t code_lane = quarter * QB + (quarter >= 2 ? 4u : 0u);     // where its codes start in a record
@@ -383,13 +388,9 @@ __device__ __forceinline__ void panel_products(
 #pragma unroll
             for (int i = 0; i < FLY; ++i) {
                 sz_word[i] = sz[c + i];
-                half2_t off_lo = k1024, off_hi = k64;
-                if constexpr (INTZ) {
-                    const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
-                    const half2_t zz = {both.y, both.y};
-                    off_lo = k1024 + zz;
-                    off_hi = k64 + zz;
-                }
+                const half2_t both = __builtin_bit_cast(half2_t, sz_word[i]);
+                const _Float16 minus_z = both.y * zero_unit;
+                const half2_t off = {minus_z, minus_z};
                 d[i] = zero4;
                 e[i] = zero4;
 #pragma unroll
@@ -397,13 +398,13 @@ __device__ __forceinline__ void panel_products(
                     const half4_t a = __builtin_bit_cast(half4_t, xa[c0 + c + i][k]);
                     half4_t q;
                     if constexpr (PAIRED8) {
-                        q = decode4_w8(code[c + i][1], code[c + i][0], sel_codes, dk, off_lo);
+                        q = decode4_w8<INTZ>(code[c + i][1], code[c + i][0], sel_codes, dk, off);
                     } else if constexpr (PAIRED) {
-                        q = decode4_w4(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off_lo, off_hi);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
+                        q = decode4_w4<INTZ>(__builtin_amdgcn_perm(code[c + i][1], code[c + i][0], sel_codes), dk, off);   // (same selectors: bytes 0..3 = word 0, 4..7 = word 2)
                     } else if constexpr (BITS == 4) {     // chunk k: two bytes, the lower or the upper half of a word
-                        q = decode4_w4(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off_lo, off_hi);
+                        q = decode4_w4<INTZ>(__builtin_amdgcn_perm(0u, code[c + i][k / 2], (k & 1) ? 0x0c030c02u : 0x0c010c00u), dk, off);
                     } else {
-                        q = decode4_w8(0u, code[c + i][k], 0x0c010c00u, dk, off_lo);
+                        q = decode4_w8<INTZ>(0u, code[c + i][k], 0x0c010c00u, dk, off);
                     }
                     d[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, q, d[i], 0, 0, 0);      // sum_j q_j x_j, or sum_j (q_j - z) x_j
                     if constexpr (!INTZ) e[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, e[i], 0, 0, 0);   // sum_j x_j
@@ -475,26 +476,22 @@ __device__ __forceinline__ void panel_products(
             float4_t d[STEP], e[STEP];
 #pragma unroll
             for (int i = 0; i < STEP; ++i) {
-                half2_t off_lo = k1024, off_hi = k64;
-                if constexpr (INTZ) {
-                    const half2_t both = __builtin_bit_cast(half2_t, sz[i0 + i]);
-                    const half2_t zz = {both.y, both.y};
-                    off_lo = k1024 + zz;
-                    off_hi = k64 + zz;
-                }
+                const half2_t both = __builtin_bit_cast(half2_t, sz[i0 + i]);
+                const _Float16 minus_z = both.y * zero_unit;
+                const half2_t off = {minus_z, minus_z};
                 half2_t q[4];
                 if constexpr (BITS == 4) {
                     // (bytes e0 | e2 << 4, e1 | e3 << 4, e4 | e6 << 4, e5 | e7 << 4: pairs (e0, e4), (e2, e6), (e1, e5), (e3, e7); the activations follow suit)
                     const uint32_t w = code[i0 + i][0], v = w >> 8;
-                    q[0] = __builtin_bit_cast(half2_t, (w & dk.nib_lo) | dk.splice) - off_lo;
-                    q[1] = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, (w & dk.nib_hi) | dk.splice), dk.sixteenth, -off_hi);
-                    q[2] = __builtin_bit_cast(half2_t, (v & dk.nib_lo) | dk.splice) - off_lo;
-                    q[3] = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, (v & dk.nib_hi) | dk.splice), dk.sixteenth, -off_hi);
+                    q[0] = to_unit<INTZ>(w & dk.nib_lo, dk.low, off);
+                    q[1] = to_unit<INTZ>(w & dk.nib_hi, dk.high, off);
+                    q[2] = to_unit<INTZ>(v & dk.nib_lo, dk.low, off);
+                    q[3] = to_unit<INTZ>(v & dk.nib_hi, dk.high, off);
                 } else {
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        q[2 * t] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(code[i0 + i][t * (BITS / 4 - 1)], dk.splice, 0x01050104u)) - off_lo;
-                        q[2 * t + 1] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(code[i0 + i][t * (BITS / 4 - 1)], dk.splice, 0x01070106u)) - off_lo;
+                        q[2 * t] = to_unit<INTZ>(__builtin_amdgcn_perm(0u, code[i0 + i][t * (BITS / 4 - 1)], 0x0c010c00u), dk.low, off);
+                        q[2 * t + 1] = to_unit<INTZ>(__builtin_amdgcn_perm(0u, code[i0 + i][t * (BITS / 4 - 1)], 0x0c030c02u), dk.low, off);
                     }
                 }
                 const half8_t a = __builtin_bit_cast(half8_t, xp8[FEW ? p0 + i0 + i : 0]);
@@ -732,7 +729,7 @@ __device__ __forceinline__ void panel_products(
             const int row = p * kPanelRows + r;         // output row
             const int n = !MULTI || m == 0 ? tgt.N[0] : m == 1 ? tgt.N[1] : m == 2 ? tgt.N[2] : tgt.N[3];
             uint16_t* y = !MULTI || m == 0 ? tgt.y[0] : m == 1 ? tgt.y[1] : m == 2 ? tgt.y[2] : tgt.y[3];
-            if (b < batch && row < n) y[static_cast<size_t>(b) * n + row] = float_to_half_bits(sum);
+            if (b < batch && row < n) y[static_cast<size_t>(b) * n + row] = float_to_half_bits(sum * kUnitInverse);
         }
     }
 }
