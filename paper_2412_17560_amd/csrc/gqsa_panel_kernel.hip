@@ -117,7 +117,7 @@ struct PanelTargets {
 // panels.  A block's header is the same for all lanes and is read with scalar loads (few rows: see products_few).  The records
 // of a panel in a unit are contiguous in the image; the wavefront copies them from global memory
 // straight into its own part of LDS, 1 KiB per instruction with nothing passing through
-// registers (all of its panels at once when they fit, else two and two), and every lane then
+// registers (direct: all of its panels at once when they fit, else two and two; turned and few: panel after panel, a few ahead), and every lane then
 // reads its group's codes, scale and zero from there: which group is a lane's (its row's, in the
 // column at hand) follows from the header with a masked population count.  Fetching 8 bytes per
 // lane from global memory instead kept 1.5 KB per wavefront under way where this keeps 6 KB.
@@ -207,27 +207,55 @@ __device__ __forceinline__ void panel_products(
         }
     };
     const auto is_live = [&](int pp) { return wg + pp * stride < total; };     // (the same for the whole workgroup)
+    int n_live = 0;
+#pragma unroll
+    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) n_live += is_live(pp) ? 1 : 0;
     const uint32_t panel_headers = static_cast<uint32_t>(n_slices) * kPanelHeaderBytes;
+    // What staging asks of a panel is worked out for all panels at once, lanes 4 pp .. 4 pp + 3 for panel pp (with scalar instructions, panel after
+    // panel and with a branch at every choice of a matrix, it was 300 of the 500 instructions ahead of the first load), and read out of lane 4 pp.
+    static_assert(4 * kPanelsPerWorkgroup <= kLanes, "four lanes a panel");
+    uint64_t headers_at = 0, data_at = 0;
+    if constexpr (ROWS != Rows::direct) {
+        int m, p;
+        locate((lane >> 2) & (kPanelsPerWorkgroup - 1), m, p);
+        uint64_t h = reinterpret_cast<uint64_t>(headers0), d = reinterpret_cast<uint64_t>(data0);
+        if constexpr (MULTI) {
+            uint64_t hs[3] = {reinterpret_cast<uint64_t>(headers1), reinterpret_cast<uint64_t>(headers2), reinterpret_cast<uint64_t>(headers3)};
+            uint64_t ds[3] = {reinterpret_cast<uint64_t>(data1), reinterpret_cast<uint64_t>(data2), reinterpret_cast<uint64_t>(data3)};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                asm volatile("" : "+s"(hs[i]), "+s"(ds[i]));       // (read with the first ones, not inside a branch)
+                if (m > i) h = hs[i];
+                if (m > i) d = ds[i];
+            }
+        }
+        headers_at = h + static_cast<uint64_t>(static_cast<uint32_t>(p)) * panel_headers;
+        data_at = d;
+    }
+    const auto of_lane = [&](uint64_t v, int at) {
+        return static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), at))) |
+               static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), at))) << 32;
+    };
+    typedef const __attribute__((address_space(1))) uint8_t* global_bytes;
+    typedef const __attribute__((address_space(1))) uint32_t* global_words;
+    const auto headers_of = [&](int pp) {
+        return MULTI ? of_lane(headers_at, 4 * pp)
+                     : reinterpret_cast<uint64_t>(headers0) + static_cast<uint64_t>(static_cast<uint32_t>(min(wg + pp * stride, total - 1))) * panel_headers;
+    };
     const int r = lane & 15;                        // activation row (A), output row of the panel (B, D)
     const int j = lane >> 4;                        // which four of a group's 16 elements (FEW: which eight of two groups')
-    // few: a unit's header words, a vector load per panel (scalar ones, a panel after the other, arrived up to 3500 cycles later with
-    // 16 wavefronts asking): of every 16 lanes lane i takes column 2 i (the lanes 0..31) or 2 i + 1
-    // (32..63), and lane 15 the word that says where the block's data start.
-    struct Header { uint32_t words[kPanelsPerWorkgroup]; };
-    static_assert(!FEW || HC / 2 < 16, "lane 15 takes the block's place");
-    const auto load_header = [&](int unit) {
-        const uint32_t block = static_cast<uint32_t>(unit / UPS) * kPanelHeaderBytes;
-        const uint32_t lane_at = r == 15 ? kSliceColumns * 4u : (unit % UPS) * (HC * 4u) + 4u * (2 * min(r, HC / 2 - 1) + (j >> 1));
-        Header h{};
-#pragma unroll
-        for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
-            if (!is_live(pp)) break;
-            int m, p;
-            locate(pp, m, p);
-            const uint8_t* base = !MULTI || m == 0 ? headers0 : m == 1 ? headers1 : m == 2 ? headers2 : headers3;
-            h.words[pp] = *reinterpret_cast<const uint32_t*>(base + (static_cast<uint64_t>(static_cast<uint32_t>(p)) * panel_headers + block) + lane_at);
-        }
-        return h;
+    // A unit's header words.  `ends`: of a panel's four lanes the first takes the word of the unit's first column, the second that of the last one,
+    // the others the word that says where the block's data start.  Few: also the words of all columns, a vector load per panel (scalar
+    // ones arrived up to 3500 cycles later with 16 wavefronts asking): of every 16 lanes lane i takes column 2 i (the lanes 0..31) or 2 i + 1 (32..63).
+    const uint32_t ends_lane = (lane & 2) ? kSliceColumns * 4u : (lane & 1) * (HC * 4u - 4u), ends_columns = (lane & 2) ? 0u : ~0u;
+    const uint32_t words_lane = 4u * (2 * min(r, HC / 2 - 1) + (j >> 1));
+    const auto load_ends = [&](int unit) {
+        const uint32_t at = static_cast<uint32_t>(unit / UPS) * kPanelHeaderBytes + ends_lane + ((unit % UPS) * (HC * 4u) & ends_columns);
+        return *reinterpret_cast<global_words>(headers_at + at);
+    };
+    const auto load_words = [&](int pp, int unit) {
+        const uint32_t columns = static_cast<uint32_t>(unit / UPS) * kPanelHeaderBytes + (unit % UPS) * (HC * 4u);
+        return *reinterpret_cast<global_words>(reinterpret_cast<global_bytes>(headers_of(pp)) + (columns + words_lane));
     };
 
     // The activations under a unit, once for all panels of the workgroup.
@@ -238,10 +266,10 @@ __device__ __forceinline__ void panel_products(
     // of their own, and x arrives at 16 bytes a cycle and compute unit: 3.5 us for 16 rows of 4096.
     // turned: a lane loads 16 bytes of row lane / 4, four lanes next to each other in memory -- 1.2 us for the same rows -- and
     // what it needs of them comes out of a turn through LDS, rows 80 bytes apart there so that the lanes' accesses spread
-    // over the banks.  Only from 10 or 12 rows on (see panels_gemm) and where a workgroup has one panel: with more of them the wavefronts whose activations
-    // arrive first multiply while the others' are on their way, and the turn is one thing more to do.  (direct / turned, 16 rows, W4 S = 50 %:
-    // 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; but 3 x 4096x4096
-    // in one launch 13.6 / 13.9, 8192x11008 19.4 / 20.1.)
+    // over the banks.  One matrix of one panel a workgroup from 10 or 12 rows on, and joint launches with G = 16 (see panels_gemm).  (direct / turned, 16 rows,
+    // W4 S = 50 %: 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; one matrix of
+    // two panels a workgroup and more is ahead with direct, 8192x11008 19.4 / 20.1: there the wavefronts whose activations arrive first
+    // multiply while the others' are on their way.)
     // few (at most 8 activation rows): likewise with eight lanes to a row; elements 8 (j & 1) .. + 7 of row r & 7, of the first column of a
     // pair for j < 2 and r < 8, of the second for j >= 2 and r >= 8, and nothing -- 16 zero bytes -- else.
     constexpr int kRowLanes = FEW ? 8 : 4, kRowStride = FEW ? 144 : 80;
@@ -304,58 +332,84 @@ __device__ __forceinline__ void panel_products(
         for (int v = 0; v < 4; ++v) acc[pp][v] = 0.0f;
 
     const auto word_of = [&](uint32_t h, int at) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), at)); };
-    uint32_t slot[kPanelsPerQuad];      // where a panel's records begin in the staging area
-    // few: stages a unit's records of the panels from pp on of a quad, from byte `at` of the area on, as many as fit: returns
-    // one past the last.  The records of a panel in a unit are contiguous (first group of the first column .. last group of
-    // the last column); they go one panel's after the other's, each rounded up to 16 bytes with room for one more record ahead of it (a
-    // lane without a group reads the one before, and before the first one there are zeros).  Every lane copies 16 bytes per KiB of them, global memory ->
-    // LDS directly (lane l's bytes land at the given LDS address + 16 l), no registers.
-    const auto stage = [&](const Header& h, int quad, int from_panel, uint32_t at) {
-        // The records go where others lay.  A lane's reads of those must be back first -- the loads into LDS are not
-        // ordered against them, and the compiler waits for a value where it is used, which may be further down.
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        int end = kPanelsPerQuad;
+    // The records of a panel in a unit are contiguous (first group of the first column .. last group of the last column).  Every
+    // lane copies 16 bytes per KiB of them, global memory -> LDS directly (lane l's bytes land at the given LDS address + 16 l), no
+    // registers.  The panels' records have slots of the staging area in turn, each with room for one more record: few ahead of
+    // the first (a lane without a group reads the one before, and before the first one there are zeros), else behind the last.
+    // All panels of a unit take as many loads, `pieces`: loads return in the order of issue, so "all but the n newest" says that a panel's
+    // records are there while those of the panels behind it are on their way. 
+    uint32_t span = 0;                  // lane 4 pp: bytes of panel pp's records | where they start in the block << 16,
+    uint64_t records_from = 0;          // and where that is
+    int pieces = 0, n_slots = 1;
+    uint32_t slot_bytes = 0;
+    const uint32_t mine_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)mine));
+    const auto slot_of = [&](int pp) { return static_cast<uint32_t>(pp & (n_slots - 1)) * slot_bytes + (FEW ? kSpare : 0u); };
+    // Piece i of `bytes` bytes.  Lanes past the end are switched off (they would take their cycles) but the first, so that every piece is
+    // a load that counts; its address stays inside (the image ends with 256 zero bytes).  (The wait state is for m0.)
+    const auto copy = [&](uint32_t to, int i, uint32_t bytes, uint64_t from) {
+        const uint32_t o = 16u * lane + 1024u * i;
+        const unsigned long long lanes = __ballot(o < bytes || o == 1024u * i);
+        unsigned long long all;
+        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
+                     : "=&s"(all) : "{m0}"(to + 1024u * i), "v"(min(o, (max(bytes, 1u) - 1u) & ~15u)), "s"(from), "s"(lanes) : "memory");
+    };
+    const auto issue = [&](int pp) {
+        const uint64_t from = of_lane(records_from, 4 * pp);
+        const uint32_t bytes = word_of(span, 4 * pp) & 0xFFFFu, to = mine_at + slot_of(pp);
 #pragma unroll
-        for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
-            if (pp < from_panel || pp >= end) continue;
-            if (!is_live(quad * kPanelsPerQuad + pp)) { end = pp; continue; }
-            const uint32_t words = h.words[quad * kPanelsPerQuad + pp];
-            const uint32_t last = word_of(words, 32 + HC / 2 - 1), first = word_of(words, 0) >> 16, place = word_of(words, 15);
-            const uint32_t bytes = ((last >> 16) + __builtin_popcount(last & 0xFFFFu) - first) * RB;     // <= kMaxUnitBytes
-            const uint32_t next = at + ((bytes + 15u) & ~15u) + kSpare;
-            if (next > kWaveLds) { end = pp; continue; }
-            // Four panels of which three would fit (panels pruned alike take alike: the first stands for them) go two and two where they are
-            // all a workgroup has: the fourth's loads alone have one panel's products before them and after. 32000x2048 at 8 rows: W4, any zeros,
-            // S = 10 / 20 % 16.7 / 15.5 -> 14.7 / 14.1 us, W8 18.7 / 17.6 -> 17.5 / 16.5; 16000x4096 W4 1.05 and W8 1.08 times as fast.  With a second quad
-            // three and one is ahead (60000x2048 W8 by 3 %).
-            if (pp == 0 && quad == 0 && from_panel == 0 && is_live(kPanelsPerQuad - 1) && !is_live(kPanelsPerQuad) &&
-                kSpare + 4 * (next - at) > kWaveLds) end = 2;
-            int m, p;
-            locate(quad * kPanelsPerQuad + pp, m, p);
-            const uint8_t* data = !MULTI || m == 0 ? data0 : m == 1 ? data1 : m == 2 ? data2 : data3;
-            const uint8_t* from = data + (static_cast<uint64_t>(place) * 16u + first * RB);
-            slot[pp] = at;
+        for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
+            if (i >= pieces) break;
+            copy(to, i, bytes, from);
+        }
+    };
+    // what a unit's headers say, and the loads of its first panels
+    const auto begin_unit = [&](uint32_t ends) {
+        const auto of_quad = [&](auto ctrl) { return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(ends), decltype(ctrl)::value, 0xF, 0xF, true)); };
+        const uint32_t first = (of_quad(std::integral_constant<int, 0x00>{}) >> 16) * RB, last = of_quad(std::integral_constant<int, 0x55>{});
+        const uint32_t bytes = (lane >> 2) < n_live ? ((last >> 16) + __builtin_popcount(last & 0xFFFFu)) * RB - first : 0u;     // <= kMaxUnitBytes
+        span = bytes | first << 16;
+        records_from = data_at + (static_cast<uint64_t>(of_quad(std::integral_constant<int, 0xAA>{})) * 16u + first);
+        pieces = (__any(bytes > 0) ? 1 : 0) + (__any(bytes > 1024) ? 1 : 0) + (__any(bytes > 2048) ? 1 : 0);
+        slot_bytes = static_cast<uint32_t>(pieces) * 1024u + kSpare;
+        n_slots = pieces <= 1 ? 8 : pieces == 2 ? 4 : 2;
+        static_assert(8 * (1024 + kSpare) <= kWaveLds && 4 * (2048 + kSpare) <= kWaveLds && 2 * (3072 + kSpare) <= kWaveLds && kMaxUnitBytes == 3072,
+                      "the slots must fit a wavefront's staging area");
+        // The records go where others lay.  A lane's reads of those must be back first -- the loads into LDS are not
+        // ordered against them.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        for (int pp = 0; pp < min(n_live, n_slots); ++pp) issue(pp);
+        if constexpr (FEW) {
             // What a lane without a group multiplies meets the zeros of the other column's activations, so it has to be finite:
             // the record before the first one is zero.
-            if (lane < static_cast<int>(kSpare / 16)) *reinterpret_cast<u32x4_t*>(mine + (at - kSpare) + 16 * lane) = u32x4_t{0, 0, 0, 0};
+            if (lane < n_slots)
 #pragma unroll
-            for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
-                if (i > 0 && bytes <= 1024u * i) continue;
-                const uint32_t o = 16u * lane + 1024u * i;
-                if (o < bytes)
-                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(from + o),
-                                                     (__attribute__((address_space(3))) void*)(mine + (at + 1024u * i)), 16, 0, 0);
-            }
-            at = next;
+                for (uint32_t i = 0; i < kSpare / 16; ++i) *reinterpret_cast<u32x4_t*>(mine + lane * slot_bytes + 16 * i) = u32x4_t{0, 0, 0, 0};
         }
-        return end;
+    };
+    // waits until the records of panel pp are in LDS
+    const auto wait_for = [&](int pp) {
+        const int newer = (min(n_live, n_slots + pp) - 1 - pp) * pieces;
+        if (newer >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else if (newer >= 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else if (newer == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+        else if (newer == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+        else if (newer == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    // once all of panel pp's records have been read: its slot takes the next panel's
+    const auto pass_on = [&](int pp) {
+        if (pp + n_slots < n_live) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue(pp + n_slots);
+        }
     };
 
     uint2 xa[HC][M];
+    typedef const __attribute__((address_space(3))) uint32_t* lds_words;
     // The products of one panel of a step: its records in LDS, its header words in 16 lanes of h.
-    const auto products = [&](float* sums, const uint32_t (&hh)[HC], uint32_t before0, const uint8_t* records) {
+    const auto products = [&](float* sums, const uint32_t (&hh)[HC], uint32_t records, auto whole, auto&& all_read) {
         // (sums of eight panels leave registers for the records of eight columns at a time, of four where a column takes two sums)
-        constexpr int HL = QUADS == 1 || BITS == 8 ? HC : HC > 8 ? 8 : !INTZ && HC > 4 ? 4 : HC;
+        constexpr int HL = decltype(whole)::value || BITS == 8 ? HC : HC > 8 ? 8 : !INTZ && HC > 4 ? 4 : HC;
 #pragma unroll
         for (int c0 = 0; c0 < HC; c0 += HL) {
         if (c0 > 0) asm volatile("" ::: "memory");
@@ -365,17 +419,17 @@ __device__ __forceinline__ void panel_products(
 #pragma unroll
         for (int c = 0; c < HL; ++c) {
             const uint32_t h = hh[c0 + c];
-            const uint32_t idx = ((h >> 16) - before0) + __builtin_popcount(h & 0xFFFFu & below);
+            const uint32_t at = ((h >> 16) + __builtin_popcount(h & 0xFFFFu & below)) * RB + records;
             if constexpr (TRI) {
-                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + (PAIRED8 ? half_of_record : 0u)));
+                const lds_words w = reinterpret_cast<lds_words>(at);
                 code[c][0] = w[0];
                 sz[c] = w[1];
                 code[c][1] = w[2];
             } else {
-                const uint32_t* w = reinterpret_cast<const uint32_t*>(records + (idx * RB + code_lane));
+                const lds_words w = reinterpret_cast<lds_words>(at + code_lane);
 #pragma unroll
                 for (int t = 0; t < QW; ++t) code[c][t] = w[t];
-                sz[c] = *reinterpret_cast<const uint32_t*>(records + (idx * RB + CB / 2));
+                sz[c] = *reinterpret_cast<lds_words>(at + CB / 2);
             }
         }
         // four columns at a time: the products of the later ones are under way while the
@@ -426,6 +480,7 @@ __device__ __forceinline__ void panel_products(
                     }
                 }
             }
+            if (c == 0 && c0 + HL == HC) all_read();
         }
         }
     };
@@ -440,14 +495,14 @@ __device__ __forceinline__ void panel_products(
     // ones.  At 8 rows, W4 S = 50 %: 4096x4096 6.9 -> 5.7 us, 3 x 4096x4096 in one launch 13.3 -> 11.3, 2 x 11008x4096 21.2 -> 18.1,
     // 4096x11008 12.4 -> 9.9, 32000x4096 24.0 -> 21.3; W8 4096x4096 7.6 -> 6.1, 2 x 14336x4096 28.0 -> 22.8, 4096x14336 18.1 -> 13.5.
     u32x4_t xp8[FEW ? HC / 2 : 1];
-    const auto products_few = [&](float* sums, uint32_t words, uint32_t records) {
+    const auto products_few = [&](float* sums, uint32_t words, uint32_t records, auto whole, auto&& all_read) {
         constexpr int PAIRS = HC / 2;
         constexpr int STEP = INTZ && (QUADS == 1 || BITS == 8) ? 4 : 2;       // pairs under way together (registers)
         // (pairs whose records are held together: with the sums of eight panels and two sums a pair there are registers for half of them;
         // all of them, 39 spilled, took 3 to 17 % longer: W4, any zeros, 8 rows of 20000x4096 S = 50 % 16.8 -> 15.6 us, 2 x 11008x4096 21.2 -> 19.5, 32000x2048 S = 30 % 17.2 -> 14.7)
-        constexpr int HELD = FEW && !INTZ && QUADS == 2 && BITS == 4 ? PAIRS / 2 : PAIRS;
+        constexpr int HELD = decltype(whole)::value ? PAIRS : PAIRS / 2;
         const uint32_t upto = (2u << r) - 1u, own = 1u << r;
-        const uint32_t before = (words >> 16) * RB + (records - (word_of(words, 0) >> 16) * RB - RB + (PAIRED8 ? 12u * (j & 1) : 0u));
+        const uint32_t before = (words >> 16) * RB + (records - RB + (PAIRED8 ? 12u * (j & 1) : 0u));
         const uint32_t to_codes = 8u * (j & 1);             // 4-bit: codes, scale | zero, codes
         for_each_index<PAIRS / HELD>([&](auto part) {
         constexpr int p0 = decltype(part)::value * HELD;
@@ -517,6 +572,7 @@ __device__ __forceinline__ void panel_products(
                     }
                 }
             }
+            if (i0 == 0 && p0 + HELD == PAIRS) all_read();
         }
         });
     };
@@ -555,34 +611,41 @@ __device__ __forceinline__ void panel_products(
             asm volatile("" ::: "memory");
         }
     };
-    if constexpr (FEW) {
-        constexpr bool kAhead = QUADS == 1;          // a unit's header is loaded during the one before it
-        Header h_next{};
-        if (kAhead && wl < n_units) h_next = load_header(wl);
-        for (int unit = wl; unit < n_units; unit += WAVES) {
-            const Header h = kAhead ? h_next : load_header(unit);
+    // 9 rows and more, G > 16: the header words of the panels' columns, scalar loads -- of a quad's panels at once where they fit the scalar
+    // registers, else a panel's when its products start (one latency a panel; asked for ahead of that they are slower yet: while a
+    // scalar load is under way every wait for LDS waits for it as well).
+    constexpr bool kQuadWords = !FEW && kPanelsPerQuad * HC <= 32;
+    uint32_t hh[kQuadWords ? kPanelsPerQuad : 1][FEW ? 1 : HC] = {};
+    const auto load_columns = [&](int at, int pp, int unit) {
+        const auto from = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(
+            headers_of(pp) + (static_cast<uint32_t>(unit / UPS) * kPanelHeaderBytes + (unit % UPS) * (HC * 4u)));
 #pragma unroll
-            for (int quad = 0; quad < QUADS; ++quad) {
-                if (quad > 0 && !is_live(quad * kPanelsPerQuad)) break;
-                int end = stage(h, quad, 0, kSpare);        // (room ahead of the first record: see stage)
-                if (quad == 0) {
-                    load_x(unit);
-                    if (kAhead && unit + WAVES < n_units) h_next = load_header(unit + WAVES);
-                    turn_x();
-                }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
+        for (int c = 0; c < HC; ++c) hh[at][c] = from[c];
+    };
+    const auto load_quad = [&](int quad, int unit) {
+        if constexpr (kQuadWords) {
 #pragma unroll
-                for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
-                    if (!is_live(quad * kPanelsPerQuad + pp)) break;
-                    if (pp >= 2 && pp == end) {                 // (two always fit)
-                        end = stage(h, quad, pp, kSpare);
-                        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    }
-                    products_few(acc[quad * kPanelsPerQuad + pp], h.words[quad * kPanelsPerQuad + pp], wl * kWaveLds + slot[pp]);
-                }
+            for (int pp = 0; pp < kPanelsPerQuad; ++pp) {
+                if (quad * kPanelsPerQuad + pp >= n_live) break;
+                load_columns(pp, quad * kPanelsPerQuad + pp, unit);
             }
         }
-    } else {
+    };
+    // the products of a panel whose records are in LDS, `records` past the place of the block's first one
+    const auto multiply = [&](int pp, int unit, uint32_t words, uint32_t records, auto whole, auto&& arrived, auto&& all_read) {
+        if constexpr (FEW) {
+            arrived();
+            products_few(acc[pp], words, wl * kWaveLds + records, whole, all_read);
+        } else {
+            if constexpr (!kQuadWords) load_columns(0, pp, unit);
+            else if (pp > 0 && pp % kPanelsPerQuad == 0) load_quad(pp / kPanelsPerQuad, unit);
+            arrived();
+            products(acc[pp], hh[kQuadWords ? pp % kPanelsPerQuad : 0], mine_at + records + (PAIRED8 ? half_of_record : 0u), whole, all_read);
+        }
+    };
+    if constexpr (ROWS == Rows::direct) {
+        // direct: the records of a quad (or of two of its panels) are requested and awaited together.  Panel by panel, as below, took up to
+        // 14 % longer in this form (4822x4096 G = 128 7.4 -> 8.5 us, 32000x4096 at 16 rows 23.1 -> 23.9).
         for (int unit = wl; unit < n_units; unit += WAVES) {
             const int s = unit / UPS;
             const int sub = unit % UPS;
@@ -669,8 +732,6 @@ __device__ __forceinline__ void panel_products(
                         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the records are in LDS before any lane reads them
                     }
                     if (live[pp]) {                             // (the same for the whole workgroup)
-                        const uint8_t* records = mine + slot[pp];           // in LDS
-                        const uint32_t before0 = first[pp];
                         uint32_t hh[HC];
                         if constexpr (!AGAIN) {
 #pragma unroll
@@ -683,9 +744,128 @@ __device__ __forceinline__ void panel_products(
 #pragma unroll
                             for (int c = 0; c < HC; ++c) hh[c] = again[c];
                         }
-                        products(acc[quad * kPanelsPerQuad + pp], hh, before0, records);
+                        products(acc[quad * kPanelsPerQuad + pp], hh, mine_at + slot[pp] - first[pp] * RB + (PAIRED8 ? half_of_record : 0u),
+                                 std::bool_constant<QUADS == 1>{}, []() {});
                     }
                 }
+            }
+        }
+    } else {
+        bool single = false;
+        if constexpr (QUADS == 1) single = n_live == 1;
+        if (single) {
+            // One panel: while a unit's products are computed, the next one's records and (where there are registers for them) activations
+            // are on their way, and the headers of the one behind it, which say where its records are.
+            constexpr bool kXAhead = XL <= 4;
+            if constexpr (FEW) {        // (the zeros ahead of the first record, see begin_unit)
+                if (lane < static_cast<int>(kSpare / 16)) *reinterpret_cast<u32x4_t*>(mine + 16 * lane) = u32x4_t{0, 0, 0, 0};
+            }
+            constexpr uint32_t kSlot = FEW ? kSpare : 0u;
+            const uint64_t data_from = MULTI ? of_lane(data_at, 0) : reinterpret_cast<uint64_t>(data0);
+            uint32_t first = 0;
+            const auto begin = [&](uint32_t ends) {
+                const uint32_t last = word_of(ends, 1);
+                first = (word_of(ends, 0) >> 16) * RB;
+                const uint32_t bytes = ((last >> 16) + __builtin_popcount(last & 0xFFFFu)) * RB - first;
+                const uint64_t from = data_from + (static_cast<uint64_t>(word_of(ends, 2)) * 16u + first);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (as in begin_unit)
+#pragma unroll
+                for (int i = 0; i < kMaxUnitBytes / 1024; ++i) {
+                    if (bytes <= 1024u * i) break;
+                    copy(mine_at + kSlot, i, bytes, from);
+                }
+            };
+            int unit = wl;
+            uint32_t words = 0, ends_next = 0, words_next = 0;
+            const auto of_unit = [&](int u) { return min(u, n_units - 1); };
+            if (unit < n_units) {
+                const uint32_t ends = load_ends(unit);
+                if constexpr (FEW) words = load_words(0, unit);
+                load_quad(0, unit);
+                __builtin_amdgcn_sched_barrier(0);
+                load_x(unit);
+                __builtin_amdgcn_sched_barrier(0);
+                ends_next = load_ends(of_unit(unit + WAVES));
+                if constexpr (FEW) words_next = load_words(0, of_unit(unit + WAVES));
+                begin(ends);
+                turn_x();
+            }
+            while (unit < n_units) {
+                const bool more = unit + WAVES < n_units;
+                uint32_t ends_after = 0, words_after = 0;
+                multiply(0, unit, words, kSlot - first, std::bool_constant<!FEW || BITS == 8>{}, [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }, [&]() {
+                    if (!more) return;
+                    ends_after = load_ends(of_unit(unit + 2 * WAVES));
+                    if constexpr (FEW) words_after = load_words(0, of_unit(unit + 2 * WAVES));
+                    if (kXAhead) load_x(unit + WAVES);
+                    begin(ends_next);
+                });
+                if (!more) break;
+                unit += WAVES;
+                load_quad(0, unit);
+                if (!kXAhead) load_x(unit);
+                words = words_next;
+                ends_next = ends_after;
+                words_next = words_after;
+                turn_x();
+            }
+        } else {
+            // Several: the records of the first panels are on their way while the activations are turned, and those of the later ones while
+            // the first ones' products are computed.  (The activations are requested ahead of the headers, so they are there when the
+            // headers are, and the records' loads, which the headers place, come next: a wait for the activations behind those would be one for the
+            // records of all panels.)  Before, all of a quad's panels were awaited together: at 16 rows the products of 2 x 11008x4096 began when three
+            // quarters of the image had arrived.
+            constexpr bool kEndsAhead = INTZ || QUADS == 1;
+            const bool x_first = n_live > 2;
+            int unit = wl;
+            uint32_t words[FEW ? kPanelsPerWorkgroup : 1] = {}, ends_next = 0;
+            const auto load_all_words = [&](int u) {
+                if constexpr (FEW) {
+#pragma unroll
+                    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
+                        if (pp >= n_live) break;
+                        words[pp] = load_words(pp, u);
+                    }
+                }
+            };
+            if (unit < n_units) {
+                // (two copies, as behind a common end there would be one wait for both)
+                if (x_first) {
+                    load_x(unit);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const uint32_t ends = load_ends(unit);
+                    if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
+                    load_all_words(unit);
+                    load_quad(0, unit);
+                    begin_unit(ends);
+                    turn_x();
+                } else {
+                    const uint32_t ends = load_ends(unit);
+                    load_all_words(unit);
+                    load_quad(0, unit);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_x(unit);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
+                    begin_unit(ends);
+                    turn_x();
+                }
+            }
+            while (unit < n_units) {
+#pragma unroll
+                for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) {
+                    if (pp >= n_live) break;
+                    multiply(pp, unit, words[FEW ? pp : 0], slot_of(pp) - (word_of(span, 4 * pp) >> 16), std::bool_constant<FEW ? BITS == 8 || QUADS == 1 : BITS == 8>{}, [&]() { wait_for(pp); }, [&]() { pass_on(pp); });
+                }
+                unit += WAVES;
+                if (unit >= n_units) break;
+                load_quad(0, unit);
+                load_x(unit);
+                load_all_words(unit);
+                const uint32_t ends = kEndsAhead ? ends_next : load_ends(unit);
+                if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
+                begin_unit(ends);
+                turn_x();
             }
         }
     }
@@ -844,7 +1024,9 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     //   8-bit codes, G > 16, 3, 8, 10, 12, 14, 16 rows of 4096x11008 G = 64: 11.2, 11.4, 12.0, 12.9, 13.8, 15.5 against 12.3, 12.3, 12.4, 12.5, 12.7, 12.7
     //     (16 sizes: 1.08, 1.05, 1.04, 0.985, 0.955, 0.89);
     //   G = 16, 9, 10, 12, 16 rows of 4096x4096 W4: 6.7, 6.7, 6.9, 7.5 against 7.0, 6.8, 6.8, 6.9 (8 sizes: 1.05, 1.04, 0.99, 0.91; W8 1.05, 1.03, 1.01, 0.96).
-    // Several matrices always take direct: no joint launch of one panel a workgroup has been compiled or measured in the turned form.
+    // Several matrices of G = 16 with 9 rows and more take turned, whatever the panels of a workgroup (direct, the records of a quad awaited together, against
+    // turned, panel by panel, 16 rows: 2 x 1629x8192 S = 30 % 12.9 / 10.4 us, 3 x 327x4096 W8 8.4 / 6.6, 3 x 4096x4096 13.1 / 12.4, 2 x 11008x4096 21.0 / 19.6;
+    // 10 rows of 3 x 1133x5120 8.1 / 7.6), of larger groups direct (not compiled in the other form).
     const int turned_from = m->bits == 4 && m->G > 16 ? 10 : 12;
     const Rows rows = batch <= 8 && m->G == 16 ? Rows::few
                     : n == 1 && total <= kMaxDefaultWorkgroups && batch >= turned_from ? Rows::turned : Rows::direct;
@@ -893,7 +1075,8 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
                     return;
                 }
             }
-            go(more_rows);
+            if constexpr (kChunks == 1 && decltype(multi)::value) go(std::integral_constant<Rows, Rows::turned>{});
+            else go(more_rows);
         });
     };
     using Whole = std::integral_constant<int, kPanelWaves>;

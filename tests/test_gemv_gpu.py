@@ -867,6 +867,52 @@ def test_panel_kernel_staging_area_used_again(torch_cuda, bits, G, integer_zeros
             assert np.array_equal(y[b].view(np.uint16), np.tile(y[b][:period], times)[:N].view(np.uint16))
 
 
+@pytest.mark.parametrize("bits,G", [(4, 16), (8, 16), (4, 64), (8, 32)])
+@pytest.mark.parametrize("integer_zeros", [True, False])
+@pytest.mark.parametrize("panels", [(37,), (300, 301), (611, 690), (1100,)])
+def test_panel_kernel_panels_of_very_different_lengths(torch_cuda, bits, G, integer_zeros, panels):
+    """A workgroup's panels (one, two or three, six, two to three) take none, one, two or three loads for their records in a unit: the slots
+    of the staging area go by the longest, an empty panel's load counts all the same.  One unit for some wavefronts and two for
+    others, the last slice short; 16, 9 and up to 8 rows; the rows repeat a pattern whose products the oracle has."""
+    rng = np.random.default_rng(bits * 100 + G)
+    units = {4: 16, 8: 8}[bits] * 16
+    K = 20 * units + G if G == 16 else 20 * units
+    columns = K // G
+    # (panels of 16 rows: dense, empty, a single group in one row, half, ragged)
+    keep = np.concatenate([np.full(16, columns), np.zeros(16), np.eye(1, 16, 5)[0], np.full(16, columns // 2),
+                           gi.imbalanced_keep_counts(16, columns, seed=3)]).astype(np.int64)
+    c = oracle.pack(gi.dense_weight(80, K, seed=61), G, bits, keep_per_row=keep)
+    if not integer_zeros:
+        c.zeros = (c.zeros.view(np.float16) + rng.standard_normal(c.nnzg).astype(np.float16)).view(np.uint16)
+    x = gi.activations(16, K, seed=62)
+    ref = oracle.gemv(c, x, threads=8)
+
+    def repeated_rows(n):
+        times = -(-n // 80)
+        lengths = np.tile(np.diff(c.rowIndex), times)[:n]
+        row_index = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+        arrays = (np.tile(a, times)[:int(row_index[-1]) * (len(a) // c.nnzg)] for a in (c.groups, c.values, c.scales, c.zeros))
+        h = gq.gqsa_import(row_index, *arrays, n, K, G, bits)
+        gq.gqsa_build_panels(h)
+        return h
+
+    handles = [repeated_rows(16 * p - 3) for p in panels]
+    for rows in (16, 9, 8, 5):
+        xd = torch_cuda.from_numpy(x[:rows].copy()).cuda()
+        ys = [torch_cuda.full((rows, 16 * p - 3), float("nan"), dtype=torch_cuda.float16, device="cuda") for p in panels]
+        for _ in range(2):
+            if len(panels) > 1:
+                gq.gqsa_gemv_multi(handles, xd, ys)
+            else:
+                gq.gqsa_gemv(handles[0], xd, ys[0])
+        torch_cuda.cuda.synchronize()
+        for y, p in zip(ys, panels):
+            y, n = y.cpu().numpy(), 16 * p - 3
+            for b in range(rows):
+                assert oracle.rel_error(y[b][:80], ref[b]) <= TOL
+                assert np.array_equal(y[b].view(np.uint16), np.tile(y[b][:80], -(-n // 80))[:n].view(np.uint16))
+
+
 @pytest.mark.parametrize("bits,G,K,first", [(4, 16, 4096, (5, 5)), (8, 16, 4096, (5, 5)), (4, 16, 8320, (5, 3)), (8, 16, 8320, (5, 3)), (8, 32, 4096, (5, 3)),
                                             (8, 64, 1024, (5, 3)), (4, 32, 4096, (3, 3)), (8, 64, 8320, (3, 3))])
 def test_batch_from_which_the_second_image_is_used(torch_cuda, bits, G, K, first):
