@@ -266,7 +266,7 @@ __device__ __forceinline__ void panel_products(
     // of their own, and x arrives at 16 bytes a cycle and compute unit: 3.5 us for 16 rows of 4096.
     // turned: a lane loads 16 bytes of row lane / 4, four lanes next to each other in memory -- 1.2 us for the same rows -- and
     // what it needs of them comes out of a turn through LDS, rows 80 bytes apart there so that the lanes' accesses spread
-    // over the banks.  One matrix of one panel a workgroup from 10 or 12 rows on, and joint launches with G = 16 (see panels_gemm).  (direct / turned, 16 rows,
+    // over the banks.  One matrix of one panel a workgroup from 9 to 12 rows on, and joint launches with G = 16 (see panels_gemm).  (direct / turned, 16 rows,
     // W4 S = 50 %: 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; one matrix of
     // two panels a workgroup and more is ahead with direct, 8192x11008 19.4 / 20.1: there the wavefronts whose activations arrive first
     // multiply while the others' are on their way.)
@@ -1018,16 +1018,17 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     const int64_t wgs = std::min<int64_t>(total, std::max<int64_t>((halves ? 2 : 1) * kMaxDefaultWorkgroups,
                                                                    (total + per_wg - 1) / per_wg));
     // What the forms are for: see the kernel.  turned takes the same time whatever the rows, direct less with fewer of them (the copies of
-    // the last one are one request), so it is the rows that decide.  direct / turned, one matrix of at most 256 panels, S = 50 %:
-    //   4-bit codes, G > 16, 3, 8, 9, 10, 12, 16 rows of 4096x11008 G = 64: 10.0, 11.1, 11.2, 12.2, 13.6, 15.8 against 12.3, 12.1, 12.2, 12.2, 12.3, 12.7 us
-    //     (25 sizes, mean of turned / direct: 1.14, 1.01, 1.01, 0.97, 0.92, 0.85);
-    //   8-bit codes, G > 16, 3, 8, 10, 12, 14, 16 rows of 4096x11008 G = 64: 11.2, 11.4, 12.0, 12.9, 13.8, 15.5 against 12.3, 12.3, 12.4, 12.5, 12.7, 12.7
-    //     (16 sizes: 1.08, 1.05, 1.04, 0.985, 0.955, 0.89);
-    //   G = 16, 9, 10, 12, 16 rows of 4096x4096 W4: 6.7, 6.7, 6.9, 7.5 against 7.0, 6.8, 6.8, 6.9 (8 sizes: 1.05, 1.04, 0.99, 0.91; W8 1.05, 1.03, 1.01, 0.96).
+    // the last one are one request), so it is the rows that decide.  direct against turned, one matrix of at most 256 panels, S = 50 %, 4096x4096,
+    // 4096x11008, 1024x4096 and 2000x8192 (us of 4096x11008, mean of direct / turned over the four):
+    //   4-bit codes, G > 16: 3 and 8 rows of G = 64 10.0 and 11.1 (turned, before its records came panel by panel, 12.3 and 12.1); 9 rows
+    //     11.4 / 11.0 and 10.9 / 10.7 (G = 64, 32), 1.04 and 1.02; 10 and 11 rows 1.00;
+    //   8-bit codes, G > 16: 9, 10, 11 rows of G = 32 11.5 / 12.1, 11.8 / 12.0, 12.0 / 12.1; G = 32 and 64 0.97, 1.00, 1.04;
+    //   G = 16, 4-bit codes: 11.7 / 12.1, 11.8 / 12.3, 12.2 / 12.3; 0.97, 0.985, 1.025; 8-bit codes: 13.3 / 13.2, 13.4 / 13.2, 13.4 / 13.2; 0.98, 0.99, 1.00
+    //     (1024x4096 5.9 / 6.15, 5.95 / 6.1, 6.0 / 6.1).
     // Several matrices of G = 16 with 9 rows and more take turned, whatever the panels of a workgroup (direct, the records of a quad awaited together, against
     // turned, panel by panel, 16 rows: 2 x 1629x8192 S = 30 % 12.9 / 10.4 us, 3 x 327x4096 W8 8.4 / 6.6, 3 x 4096x4096 13.1 / 12.4, 2 x 11008x4096 21.0 / 19.6;
     // 10 rows of 3 x 1133x5120 8.1 / 7.6), of larger groups direct (not compiled in the other form).
-    const int turned_from = m->bits == 4 && m->G > 16 ? 10 : 12;
+    const int turned_from = m->bits == 4 && m->G > 16 ? 9 : m->bits == 8 && m->G == 16 ? 12 : 11;
     const Rows rows = batch <= 8 && m->G == 16 ? Rows::few
                     : n == 1 && total <= kMaxDefaultWorkgroups && batch >= turned_from ? Rows::turned : Rows::direct;
     const dim3 grid(static_cast<unsigned>(wgs)), block((halves ? kPanelWaves / 2 : kPanelWaves) * kLanes);
