@@ -491,8 +491,8 @@ __device__ __forceinline__ void panel_products(
     // the second -- and each lane has read, decoded and scaled the group of its own column only.  The launches are bound by
     // vector instructions (5.3 cycles each with four wavefronts on a SIMD unit, 3 for a plain fp32 multiply-add): per pair of
     // columns 6 for address and presence (the header words stay in a vector register, lane i's is broadcast by the instruction that
-    // uses it), 11 (8-bit codes: 9) for the codes, 5 for the scale, where two columns by themselves take 6, 14 (12) and 8 slower
-    // ones.  At 8 rows, W4 S = 50 %: 4096x4096 6.9 -> 5.7 us, 3 x 4096x4096 in one launch 13.3 -> 11.3, 2 x 11008x4096 21.2 -> 18.1,
+    // uses it), 10 (8-bit codes: 9) for the codes, four of them ANDs at 3 cycles, 5 for the scale, where two columns by themselves take 6, 12 and 10.
+    // At 8 rows, W4 S = 50 %, when the form came: 4096x4096 6.9 -> 5.7 us, 3 x 4096x4096 in one launch 13.3 -> 11.3, 2 x 11008x4096 21.2 -> 18.1,
     // 4096x11008 12.4 -> 9.9, 32000x4096 24.0 -> 21.3; W8 4096x4096 7.6 -> 6.1, 2 x 14336x4096 28.0 -> 22.8, 4096x14336 18.1 -> 13.5.
     u32x4_t xp8[FEW ? HC / 2 : 1];
     const auto products_few = [&](float* sums, uint32_t words, uint32_t records, auto whole, auto&& all_read) {
