@@ -345,12 +345,14 @@ __device__ __forceinline__ void panel_products(
     const uint32_t mine_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)mine));
     const auto slot_of = [&](int pp) { return static_cast<uint32_t>(pp & (n_slots - 1)) * slot_bytes + (FEW ? kSpare : 0u); };
     // Piece i of `bytes` bytes.  Lanes past the end are switched off (they would take their cycles) but the first, so that every piece is
-    // a load that counts; its address stays inside (the image ends with 256 zero bytes).  (The wait state is for m0.)
+    // a load that counts; its address stays inside (the image ends with 256 zero bytes).  The scalar registers of the address may come
+    // straight from a v_readlane, and a vector-memory instruction may read those only five wait states later; the compiler sees to that for its
+    // own loads but not inside a statement of assembly, so the statement brings the five itself: one a move, three the s_nop (m0 takes one).
     const auto copy = [&](uint32_t to, int i, uint32_t bytes, uint64_t from) {
         const uint32_t o = 16u * lane + 1024u * i;
         const unsigned long long lanes = __ballot(o < bytes || o == 1024u * i);
         unsigned long long all;
-        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
+        asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
                      : "=&s"(all) : "{m0}"(to + 1024u * i), "v"(min(o, (max(bytes, 1u) - 1u) & ~15u)), "s"(from), "s"(lanes) : "memory");
     };
     const auto issue = [&](int pp) {

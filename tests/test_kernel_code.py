@@ -108,6 +108,44 @@ def test_panel_kernels_wait_for_their_lds_reads_before_staging_over_them(code_ob
     assert not found
 
 
+def _wait_states(op, args):
+    return int(args, 0) + 1 if op == "s_nop" else 1
+
+
+def _hand_issued_loads(code):
+    """(address, wait states that its own statement puts ahead of it) of every load into LDS that is issued under lanes switched by hand:
+    s_mov_b64 save, exec; s_mov_b64 exec, lanes; s_nop n; the load.  (The compiler switches lanes with s_and_saveexec_b64.)"""
+    for i, (address, op, args, _) in enumerate(code):
+        if "load_lds" not in op:
+            continue
+        first = i
+        while code[first - 1][1] == "s_nop" or (code[first - 1][1] == "s_mov_b64" and "exec" in code[first - 1][2]):
+            first -= 1
+        if any(c[1] == "s_mov_b64" and c[2].startswith("exec") for c in code[first:i]):
+            yield address, sum(_wait_states(c[1], c[2]) for c in code[first:i])
+
+
+def test_hand_issued_copies_bring_the_wait_states_of_their_address(code_objects):
+    """A vector-memory instruction may read scalar registers that a vector instruction (v_readlane) wrote only five wait states
+    later.  The compiler does not look inside a statement of assembly, so what it happens to put ahead of one says nothing
+    about the next build: the statement has to bring all five."""
+    def at(*ops):
+        return [(4 * i, op, args, "") for i, (op, args) in enumerate(ops)]
+    short = [("v_readlane_b32", "s4, v1, 0"), ("s_mov_b64", "s[8:9], exec"), ("s_mov_b64", "exec, s[10:11]"), ("global_load_lds_dwordx4", "v2, s[4:5]")]
+    assert list(_hand_issued_loads(at(*short))) == [(12, 2)]
+    assert list(_hand_issued_loads(at(*short[:3], ("s_nop", "2"), short[3]))) == [(16, 5)]
+    assert not list(_hand_issued_loads(at(("s_and_saveexec_b64", "s[8:9], vcc"), short[3])))
+    loads, late = 0, {}
+    for f in code_objects:
+        for name, code in _kernels(f, "gqsa_panel_"):
+            found = list(_hand_issued_loads(code))
+            loads += len(found)
+            if any(states < 5 for _, states in found):
+                late[name] = min(states for _, states in found)
+    assert loads > 0
+    assert not late
+
+
 def test_sums_of_8_bit_codes_lie_apart_where_that_is_faster(code_objects):
     """A kernel for 4 or 8 rows reads four rows' sums of a slot at once (16 bytes) unless every row keeps its own (4 bytes each): with
     8-bit codes in the format's own tiles 8 rows do, and 4 rows of K > 8192, unpruned of K > 4096: 4096x11008 took 20.4 us, not 18.8."""
