@@ -104,6 +104,33 @@ __device__ __forceinline__ void for_each_index(F&& f)
 // How a wavefront gets the activations (see the kernel).
 enum class Rows { direct, turned, few };
 
+// few and turned: the records of a unit's panels come in panel by panel, each panel with `pieces` loads (1 to 3), into slots of the staging area
+// in turn.  Loads return in the order of issue, so once all but the newest `newer_loads` have, panel pp's are there: those of the panels issued behind
+// it.  Two waits serve all cases: for all but three loads, and for all.  (One for every count from 0 to 6, chosen by comparisons, was ten scalar
+// instructions and up to six branches a panel for each of 16 wavefronts: 1629x8192 W8 at 8 rows and its like 2 % slower.)
+constexpr int slots_for(int pieces) { return pieces == 1 ? 8 : pieces == 2 ? 4 : 2; }
+constexpr int newer_loads(int pp, int n_live, int n_slots, int pieces) { return ((n_live < n_slots + pp ? n_live : n_slots + pp) - 1 - pp) * pieces; }
+constexpr int kStillOut = 3;
+constexpr int may_be_out(int newer) { return newer < kStillOut ? 0 : kStillOut; }
+// The schedule played through: the first panels' loads, then for every panel the wait, its records read, its slot passed on.
+constexpr bool records_there_when_read(int panels)
+{
+    for (int n_live = 1; n_live <= panels; ++n_live) {
+        for (int pieces = 1; pieces <= 3; ++pieces) {
+            const int n_slots = slots_for(pieces);
+            int requested = n_live < n_slots ? n_live : n_slots;        // panels
+            for (int pp = 0; pp < n_live; ++pp) {
+                const int returned = requested * pieces - may_be_out(newer_loads(pp, n_live, n_slots, pieces));
+                if (requested <= pp || returned < (pp + 1) * pieces) return false;
+                if (requested < n_live) ++requested;                    // into the slot of panel pp
+            }
+            if (requested != n_live) return false;
+        }
+    }
+    return true;
+}
+static_assert(records_there_when_read(8), "a panel's records would be read before they are there");
+
 struct PanelTargets {
     uint16_t* y[kMaxMatricesPerLaunch];
     int N[kMaxMatricesPerLaunch];
@@ -207,17 +234,19 @@ __device__ __forceinline__ void panel_products(
         }
     };
     const auto is_live = [&](int pp) { return wg + pp * stride < total; };     // (the same for the whole workgroup)
-    int n_live = 0;
+    int n_live = 1;             // (the grid has no workgroup without a panel)
 #pragma unroll
-    for (int pp = 0; pp < kPanelsPerWorkgroup; ++pp) n_live += is_live(pp) ? 1 : 0;
+    for (int pp = 1; pp < kPanelsPerWorkgroup; ++pp) n_live = is_live(pp) ? pp + 1 : n_live;
     const uint32_t panel_headers = static_cast<uint32_t>(n_slices) * kPanelHeaderBytes;
     // What staging asks of a panel is worked out for all panels at once, lanes 4 pp .. 4 pp + 3 for panel pp (with scalar instructions, panel after
     // panel and with a branch at every choice of a matrix, it was 300 of the 500 instructions ahead of the first load), and read out of lane 4 pp.
+    // The lanes of panels that the workgroup does not have follow its first one (all workgroups' on the launch's last panel are one line for everybody).
     static_assert(4 * kPanelsPerWorkgroup <= kLanes, "four lanes a panel");
     uint64_t headers_at = 0, data_at = 0;
     if constexpr (ROWS != Rows::direct) {
         int m, p;
-        locate((lane >> 2) & (kPanelsPerWorkgroup - 1), m, p);
+        const int pp = (lane >> 2) & (kPanelsPerWorkgroup - 1);
+        locate(pp < n_live ? pp : 0, m, p);
         uint64_t h = reinterpret_cast<uint64_t>(headers0), d = reinterpret_cast<uint64_t>(data0);
         if constexpr (MULTI) {
             uint64_t hs[3] = {reinterpret_cast<uint64_t>(headers1), reinterpret_cast<uint64_t>(headers2), reinterpret_cast<uint64_t>(headers3)};
@@ -238,9 +267,9 @@ __device__ __forceinline__ void panel_products(
     };
     typedef const __attribute__((address_space(1))) uint8_t* global_bytes;
     typedef const __attribute__((address_space(1))) uint32_t* global_words;
-    const auto headers_of = [&](int pp) {
+    const auto headers_of = [&](int pp) {         // (of a panel that the workgroup has)
         return MULTI ? of_lane(headers_at, 4 * pp)
-                     : reinterpret_cast<uint64_t>(headers0) + static_cast<uint64_t>(static_cast<uint32_t>(min(wg + pp * stride, total - 1))) * panel_headers;
+                     : reinterpret_cast<uint64_t>(headers0) + static_cast<uint64_t>(static_cast<uint32_t>(wg + pp * stride)) * panel_headers;
     };
     const int r = lane & 15;                        // activation row (A), output row of the panel (B, D)
     const int j = lane >> 4;                        // which four of a group's 16 elements (FEW: which eight of two groups')
@@ -336,8 +365,7 @@ __device__ __forceinline__ void panel_products(
     // lane copies 16 bytes per KiB of them, global memory -> LDS directly (lane l's bytes land at the given LDS address + 16 l), no
     // registers.  The panels' records have slots of the staging area in turn, each with room for one more record: few ahead of
     // the first (a lane without a group reads the one before, and before the first one there are zeros), else behind the last.
-    // All panels of a unit take as many loads, `pieces`: loads return in the order of issue, so "all but the n newest" says that a panel's
-    // records are there while those of the panels behind it are on their way. 
+    // All panels of a unit take as many loads, `pieces` (see records_there_when_read).
     uint32_t span = 0;                  // lane 4 pp: bytes of panel pp's records | where they start in the block << 16,
     uint64_t records_from = 0;          // and where that is
     int pieces = 0, n_slots = 1;
@@ -350,7 +378,7 @@ __device__ __forceinline__ void panel_products(
     // own loads but not inside a statement of assembly, so the statement brings the five itself: one a move, three the s_nop (m0 takes one).
     const auto copy = [&](uint32_t to, int i, uint32_t bytes, uint64_t from) {
         const uint32_t o = 16u * lane + 1024u * i;
-        const unsigned long long lanes = __ballot(o < bytes || o == 1024u * i);
+        const unsigned long long lanes = __builtin_amdgcn_ballot_w64(o < bytes || o == 1024u * i);     // (__ballot takes an int: a select and a second comparison)
         unsigned long long all;
         asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
                      : "=&s"(all) : "{m0}"(to + 1024u * i), "v"(min(o, (max(bytes, 1u) - 1u) & ~15u)), "s"(from), "s"(lanes) : "memory");
@@ -368,12 +396,12 @@ __device__ __forceinline__ void panel_products(
     const auto begin_unit = [&](uint32_t ends) {
         const auto of_quad = [&](auto ctrl) { return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(ends), decltype(ctrl)::value, 0xF, 0xF, true)); };
         const uint32_t first = (of_quad(std::integral_constant<int, 0x00>{}) >> 16) * RB, last = of_quad(std::integral_constant<int, 0x55>{});
-        const uint32_t bytes = (lane >> 2) < n_live ? ((last >> 16) + __builtin_popcount(last & 0xFFFFu)) * RB - first : 0u;     // <= kMaxUnitBytes
+        const uint32_t bytes = ((last >> 16) + __builtin_popcount(last & 0xFFFFu)) * RB - first;     // <= kMaxUnitBytes
         span = bytes | first << 16;
         records_from = data_at + (static_cast<uint64_t>(of_quad(std::integral_constant<int, 0xAA>{})) * 16u + first);
-        pieces = (__any(bytes > 0) ? 1 : 0) + (__any(bytes > 1024) ? 1 : 0) + (__any(bytes > 2048) ? 1 : 0);
+        pieces = __builtin_amdgcn_ballot_w64(bytes > 2048) ? 3 : __builtin_amdgcn_ballot_w64(bytes > 1024) ? 2 : 1;
         slot_bytes = static_cast<uint32_t>(pieces) * 1024u + kSpare;
-        n_slots = pieces <= 1 ? 8 : pieces == 2 ? 4 : 2;
+        n_slots = slots_for(pieces);
         static_assert(8 * (1024 + kSpare) <= kWaveLds && 4 * (2048 + kSpare) <= kWaveLds && 2 * (3072 + kSpare) <= kWaveLds && kMaxUnitBytes == 3072,
                       "the slots must fit a wavefront's staging area");
         // The records go where others lay.  A lane's reads of those must be back first -- the loads into LDS are not
@@ -390,13 +418,12 @@ __device__ __forceinline__ void panel_products(
     };
     // waits until the records of panel pp are in LDS
     const auto wait_for = [&](int pp) {
-        const int newer = (min(n_live, n_slots + pp) - 1 - pp) * pieces;
-        if (newer >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-        else if (newer >= 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else if (newer == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-        else if (newer == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-        else if (newer == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        static_assert(kStillOut == 3, "the wait below");
+        if (pp + 1 < kPanelsPerWorkgroup) {
+            asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+            if (may_be_out(newer_loads(pp, n_live, n_slots, pieces)) > 0) return;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
     // once all of panel pp's records have been read: its slot takes the next panel's
     const auto pass_on = [&](int pp) {
@@ -500,9 +527,10 @@ __device__ __forceinline__ void panel_products(
     const auto products_few = [&](float* sums, uint32_t words, uint32_t records, auto whole, auto&& all_read) {
         constexpr int PAIRS = HC / 2;
         constexpr int STEP = INTZ && (QUADS == 1 || BITS == 8) ? 4 : 2;       // pairs under way together (registers)
-        // (pairs whose records are held together: with the sums of eight panels and two sums a pair there are registers for half of them;
-        // all of them, 39 spilled, took 3 to 17 % longer: W4, any zeros, 8 rows of 20000x4096 S = 50 % 16.8 -> 15.6 us, 2 x 11008x4096 21.2 -> 19.5, 32000x2048 S = 30 % 17.2 -> 14.7)
-        constexpr int HELD = decltype(whole)::value ? PAIRS : PAIRS / 2;
+        // (pairs whose records are held together: with the sums of eight panels there are registers for half of them, with two sums a pair on top for a
+        // quarter.  W4, any zeros, 8 rows: all of them, 39 registers spilled among the products, took 3 to 17 % longer than half, and half, with the header words of the
+        // last panels spilled, 0 to 5 % longer than a quarter: 20000x4096 S = 30 % 17.2 -> 16.6 us, 2 x 11008x4096 S = 50 % 19.8 -> 19.4, 2 x 16384x4096 23.8 -> 23.2)
+        constexpr int HELD = decltype(whole)::value ? PAIRS : INTZ ? PAIRS / 2 : PAIRS / 4;
         const uint32_t upto = (2u << r) - 1u, own = 1u << r;
         const uint32_t before = (words >> 16) * RB + (records - RB + (PAIRED8 ? 12u * (j & 1) : 0u));
         const uint32_t to_codes = 8u * (j & 1);             // 4-bit: codes, scale | zero, codes
@@ -813,12 +841,12 @@ __device__ __forceinline__ void panel_products(
             }
         } else {
             // Several: the records of the first panels are on their way while the activations are turned, and those of the later ones while
-            // the first ones' products are computed.  (The activations are requested ahead of the headers, so they are there when the
+            // the first ones' products are computed.  The activations are requested ahead of the headers, so they are there when the
             // headers are, and the records' loads, which the headers place, come next: a wait for the activations behind those would be one for the
-            // records of all panels.)  Before, all of a quad's panels were awaited together: at 16 rows the products of 2 x 11008x4096 began when three
+            // records of all panels.  (For two panels the headers went first for a while, in a copy of their own: shorter by itself, but with both
+            // copies in the kernel W4 at 9 to 16 rows kept sums of the eighth panel in memory.)  Before, all of a quad's panels were awaited together: at 16 rows the products of 2 x 11008x4096 began when three
             // quarters of the image had arrived.
             constexpr bool kEndsAhead = INTZ || QUADS == 1;
-            const bool x_first = n_live > 2;
             int unit = wl;
             uint32_t words[FEW ? kPanelsPerWorkgroup : 1] = {}, ends_next = 0;
             const auto load_all_words = [&](int u) {
@@ -831,27 +859,14 @@ __device__ __forceinline__ void panel_products(
                 }
             };
             if (unit < n_units) {
-                // (two copies, as behind a common end there would be one wait for both)
-                if (x_first) {
-                    load_x(unit);
-                    __builtin_amdgcn_sched_barrier(0);
-                    const uint32_t ends = load_ends(unit);
-                    if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
-                    load_all_words(unit);
-                    load_quad(0, unit);
-                    begin_unit(ends);
-                    turn_x();
-                } else {
-                    const uint32_t ends = load_ends(unit);
-                    load_all_words(unit);
-                    load_quad(0, unit);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_x(unit);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
-                    begin_unit(ends);
-                    turn_x();
-                }
+                load_x(unit);
+                __builtin_amdgcn_sched_barrier(0);
+                const uint32_t ends = load_ends(unit);
+                if (kEndsAhead) ends_next = load_ends(min(unit + WAVES, n_units - 1));
+                load_all_words(unit);
+                load_quad(0, unit);
+                begin_unit(ends);
+                turn_x();
             }
             while (unit < n_units) {
 #pragma unroll
