@@ -295,7 +295,7 @@ __device__ __forceinline__ void panel_products(
     // of their own, and x arrives at 16 bytes a cycle and compute unit: 3.5 us for 16 rows of 4096.
     // turned: a lane loads 16 bytes of row lane / 4, four lanes next to each other in memory -- 1.2 us for the same rows -- and
     // what it needs of them comes out of a turn through LDS, rows 80 bytes apart there so that the lanes' accesses spread
-    // over the banks.  One matrix of one panel a workgroup from 9 to 12 rows on, and joint launches with G = 16 (see panels_gemm).  (direct / turned, 16 rows,
+    // over the banks.  One matrix of one panel a workgroup from 9 to 12 rows on, and most joint launches with G = 16 (see panels_gemm).  (direct / turned, 16 rows,
     // W4 S = 50 %: 1024x4096 7.0 / 6.1 us, 4096x4096 7.9 / 7.2, 2048x8192 12.1 / 10.0, 4096x11008 15.6 / 13.7, G = 64 4096x4096 7.3 / 6.0; one matrix of
     // two panels a workgroup and more is ahead with direct, 8192x11008 19.4 / 20.1: there the wavefronts whose activations arrive first
     // multiply while the others' are on their way.)
@@ -1042,12 +1042,33 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     //   8-bit codes, G > 16: 9, 10, 11 rows of G = 32 11.5 / 12.1, 11.8 / 12.0, 12.0 / 12.1; G = 32 and 64 0.97, 1.00, 1.04;
     //   G = 16, 4-bit codes: 11.7 / 12.1, 11.8 / 12.3, 12.2 / 12.3; 0.97, 0.985, 1.025; 8-bit codes: 13.3 / 13.2, 13.4 / 13.2, 13.4 / 13.2; 0.98, 0.99, 1.00
     //     (1024x4096 5.9 / 6.15, 5.95 / 6.1, 6.0 / 6.1).
-    // Several matrices of G = 16 with 9 rows and more take turned, whatever the panels of a workgroup (direct, the records of a quad awaited together, against
-    // turned, panel by panel, 16 rows: 2 x 1629x8192 S = 30 % 12.9 / 10.4 us, 3 x 327x4096 W8 8.4 / 6.6, 3 x 4096x4096 13.1 / 12.4, 2 x 11008x4096 21.0 / 19.6;
-    // 10 rows of 3 x 1133x5120 8.1 / 7.6), of larger groups direct (not compiled in the other form).
+    // Several matrices of G = 16, 9 rows and more.  Up to one panel a workgroup, and with more than four (direct awaits the records of a whole quad),
+    // turned is ahead whatever the rows, the codes and K; with two to four it is x that decides.  direct / turned at S = 50 %, by the units of 16 (8-bit codes:
+    // 8) columns that K has, 9 and 16 rows (two matrices, the wavefronts' share of x grows with K up to 16 units, one each):
+    //   panels a workgroup        0.3           1.5           3             6
+    //   4-bit, 8 units       1.02, 1.13    0.94, 1.01    0.95, 0.99    1.06, 1.09
+    //          16 units      1.06, 1.17    0.99, 1.05    1.01, 1.04    1.05, 1.06
+    //          24 units      1.01, 1.29    0.94, 1.01    0.95, 1.00    1.04, 1.06
+    //   8-bit, 8 units       1.08, 1.09    0.98, 0.99    0.98, 0.98    1.11, 1.09
+    //          16 units      1.19, 1.19    1.01, 1.04    1.00, 1.00    1.03, 1.04
+    //          24 units      1.16, 1.18    0.99, 1.04    1.04, 1.04    1.09, 1.07
+    // (10 to 16 units of 4-bit codes at 12 rows 1.01 to 1.04, 32 and 43 units at 12 and 14 rows 0.95 to 0.99, at 16 rows 0.98 to 1.04; any zeros
+    // alike.)  8-bit codes that are hardly pruned, where direct stages two and two because the records of a workgroup's panels do not all fit: 8, 12 and 16 units,
+    // four panels, S = 30 % 1.04, 1.15, 1.07, S = 0 1.06, 1.03, 1.02 (4-bit ones 0.96 to 1.04: no rule of their own).
+    // 848 launches of two to four panels a workgroup: by this rule 0.74 % faster than direct throughout, the worst 0.95 times as fast, turned throughout 0.17 % slower, the
+    // worst 0.93.  Several matrices of larger groups: direct (not compiled in the other form).
+    const int unit_columns = m->bits == 4 ? 16 : 8, units = static_cast<int>(m->n_slices) * (kSliceColumns / unit_columns);
+    int64_t stored = 0;
+    for (int i = 0; i < n; ++i) stored += ms[i]->nnzg();
+    // (mean bytes of a panel's records in a unit, G = 16: 12 bytes a 4-bit group, 24 an 8-bit one; nine tenths, as the panels differ)
+    const int64_t panel_bytes = stored * (m->bits * 3) * unit_columns / std::max<int64_t>(1, total * (m->K / m->G));
+    const bool apart = (total + kMaxDefaultWorkgroups - 1) / kMaxDefaultWorkgroups * panel_bytes * 10 > int64_t{kDirectArea} * 9;
+    const bool joint_turned = m->G == 16 && (total <= kMaxDefaultWorkgroups || many ||
+                                             (m->bits == 4 ? units > 8 && batch >= (units <= kPanelWaves ? 12 : 15)
+                                                           : units > kPanelWaves || (apart && units > 4)));
     const int turned_from = m->bits == 4 && m->G > 16 ? 9 : m->bits == 8 && m->G == 16 ? 12 : 11;
-    const Rows rows = batch <= 8 && m->G == 16 ? Rows::few
-                    : n == 1 && total <= kMaxDefaultWorkgroups && batch >= turned_from ? Rows::turned : Rows::direct;
+    const bool turns = n > 1 ? joint_turned : total <= kMaxDefaultWorkgroups && batch >= turned_from;
+    const Rows rows = batch <= 8 && m->G == 16 ? Rows::few : turns ? Rows::turned : Rows::direct;
     const dim3 grid(static_cast<unsigned>(wgs)), block((halves ? kPanelWaves / 2 : kPanelWaves) * kLanes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // run(bits, chunks per group, integer zeros) for the format at hand
@@ -1071,14 +1092,15 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
         }
         return true;
     };
-    const auto launch = [&](auto multi, auto waves, auto quads, auto more_rows) {
+    const auto launch = [&](auto multi, auto waves, auto quads) {
         constexpr int kWaves = decltype(waves)::value, kQuads = decltype(quads)::value;
+        constexpr bool kMulti = decltype(multi)::value;
         return pick([&](auto bits, auto chunks, auto integer_zeros) {
             constexpr int kBits = decltype(bits)::value, kChunks = decltype(chunks)::value;
             constexpr bool kInteger = decltype(integer_zeros)::value;
             const auto go = [&](auto how) {
                 constexpr Rows kRows = decltype(how)::value;
-                if constexpr (decltype(multi)::value)
+                if constexpr (kMulti)
                     hipLaunchKernelGGL((gqsa_panel_multi_kernel<kBits, kChunks, kInteger, kWaves, kQuads, kRows>), grid, block, 0, s, tgt,
                                        static_cast<const uint16_t*>(x), headers[0], headers[1], headers[2], headers[3], data[0], data[1],
                                        data[2], data[3], static_cast<int>(m->K), static_cast<int>(m->n_slices), batch, static_cast<int>(wgs));
@@ -1087,26 +1109,22 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
                                        static_cast<const uint16_t*>(x), headers[0], data[0], static_cast<int>(m->K),
                                        static_cast<int>(m->n_slices), batch, static_cast<int>(wgs), tgt.total, tgt);
             };
+            // (only the forms that `rows` can be are compiled)
             if constexpr (kChunks == 1) {
-                if (rows == Rows::few) {
-                    go(std::integral_constant<Rows, Rows::few>{});
-                    return;
-                }
+                if (rows == Rows::few) return go(std::integral_constant<Rows, Rows::few>{});
             }
-            if constexpr (kChunks == 1 && decltype(multi)::value) go(std::integral_constant<Rows, Rows::turned>{});
-            else go(more_rows);
+            if constexpr (kMulti ? kChunks == 1 : kQuads == 1) {
+                if (rows == Rows::turned) return go(std::integral_constant<Rows, Rows::turned>{});
+            }
+            if constexpr (!(kMulti && kChunks == 1 && kQuads == 2)) go(std::integral_constant<Rows, Rows::direct>{});
         });
     };
     using Whole = std::integral_constant<int, kPanelWaves>;
     using Half = std::integral_constant<int, kPanelWaves / 2>;
     using One = std::integral_constant<int, 1>;
     using Two = std::integral_constant<int, 2>;
-    using Direct = std::integral_constant<Rows, Rows::direct>;
-    using Turned = std::integral_constant<Rows, Rows::turned>;
-    const bool ok = n > 1 ? (many ? launch(std::true_type{}, Whole{}, Two{}, Direct{}) : launch(std::true_type{}, Whole{}, One{}, Direct{}))
-                  : many ? launch(std::false_type{}, Half{}, Two{}, Direct{})
-                  : rows == Rows::turned ? launch(std::false_type{}, Whole{}, One{}, Turned{})
-                                         : launch(std::false_type{}, Whole{}, One{}, Direct{});
+    const bool ok = n > 1 ? (many ? launch(std::true_type{}, Whole{}, Two{}) : launch(std::true_type{}, Whole{}, One{}))
+                          : (many ? launch(std::false_type{}, Half{}, Two{}) : launch(std::false_type{}, Whole{}, One{}));
     if (!ok) return GQSA_ERR_UNSUPPORTED;
     GQSA_HIP(hipGetLastError());
     return GQSA_OK;
