@@ -197,7 +197,10 @@ __device__ __forceinline__ void panel_products(
     constexpr int QB = (BITS / 2) * M;              // code bytes of a lane (one quarter of every chunk)
     constexpr int QW = (QB + 3) / 4;                // ... in registers
     constexpr bool PAIRED = QB == 2;                // 4-bit, G = 16: a 12-byte record, read whole
-    constexpr int kPanelsPerWorkgroup = QUADS * kPanelsPerQuad;     // at most
+    // (turned with one matrix: launches of at most as many panels as workgroups, see panels_gemm)
+    constexpr bool kOnePanel = !MULTI && ROWS == Rows::turned;
+    constexpr int kPanelsPerWorkgroup = kOnePanel ? 1 : QUADS * kPanelsPerQuad;     // at most
+    static_assert(!kOnePanel || QUADS == 1, "one panel is less than a quad");
     constexpr int HC = (BITS == 4 ? 16 : 8) / M;    // group-columns of a unit: 16 rows x HC columns x RB bytes <= kMaxUnitBytes
     static_assert(HC >= 1 && HC <= 16 && kPanelRows * HC * RB <= kMaxUnitBytes, "a unit's records must fit their staging area");
     constexpr int XCH = HC * M;                     // 16-element chunks of activations under a unit
@@ -781,8 +784,8 @@ __device__ __forceinline__ void panel_products(
             }
         }
     } else {
-        bool single = false;
-        if constexpr (QUADS == 1) single = n_live == 1;
+        bool single = kOnePanel;
+        if constexpr (!kOnePanel && QUADS == 1) single = n_live == 1;
         if (single) {
             // One panel: while a unit's products are computed, the next one's records and (where there are registers for them) activations
             // are on their way, and the headers of the one behind it, which say where its records are.
@@ -1037,11 +1040,14 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     // What the forms are for: see the kernel.  turned takes the same time whatever the rows, direct less with fewer of them (the copies of
     // the last one are one request), so it is the rows that decide.  direct against turned, one matrix of at most 256 panels, S = 50 %, 4096x4096,
     // 4096x11008, 1024x4096 and 2000x8192 (us of 4096x11008, mean of direct / turned over the four):
-    //   4-bit codes, G > 16: 3 and 8 rows of G = 64 10.0 and 11.1 (turned, before its records came panel by panel, 12.3 and 12.1); 9 rows
+    //   4-bit codes, G > 16: 3 and 8 rows of G = 64 9.5 / 11.0 and 11.5 / 11.0 (G = 32 9.4 / 11.0 and 11.0 / 11.1, G = 128 8.8 / 10.6 and 11.4 / 10.6); 9 rows
     //     11.4 / 11.0 and 10.9 / 10.7 (G = 64, 32), 1.04 and 1.02; 10 and 11 rows 1.00;
     //   8-bit codes, G > 16: 9, 10, 11 rows of G = 32 11.5 / 12.1, 11.8 / 12.0, 12.0 / 12.1; G = 32 and 64 0.97, 1.00, 1.04;
     //   G = 16, 4-bit codes: 11.7 / 12.1, 11.8 / 12.3, 12.2 / 12.3; 0.97, 0.985, 1.025; 8-bit codes: 13.3 / 13.2, 13.4 / 13.2, 13.4 / 13.2; 0.98, 0.99, 1.00
     //     (1024x4096 5.9 / 6.15, 5.95 / 6.1, 6.0 / 6.1).
+    // (The figures of 9 to 11 rows are from when turned was compiled for four panels.  With one it is 2 % faster, and the lines could come down: 8-bit codes of
+    // G = 16 at 9, 10, 11 rows 1.02, 1.035, 1.05, 4-bit ones of G = 64 and 128 at 8 rows 1.04 to 1.08.  250 random launches of 9 to 16 rows, G = 16 to 128, S = 0 to
+    // 80 %, lost nothing by these lines against direct throughout below 10 and 12 rows, 0.985 at worst.)
     // Several matrices of G = 16, 9 rows and more.  Up to one panel a workgroup, and with more than four (direct awaits the records of a whole quad),
     // turned is ahead whatever the rows, the codes and K; with two to four it is x that decides.  direct / turned at S = 50 %, by the units of 16 (8-bit codes:
     // 8) columns that K has, 9 and 16 rows (two matrices, the wavefronts' share of x grows with K up to 16 units, one each):

@@ -160,6 +160,20 @@ def test_sums_of_8_bit_codes_lie_apart_where_that_is_faster(code_objects):
                      | {(8, 1, 0, spread, slots, 4) for spread in (0, 1) for slots in (768, 1024)} | {(8, 1, 0, 1, 512, 4)})
 
 
+def test_form_for_one_panel_is_compiled_for_one(code_objects):
+    """The form that turns the activations takes one matrix of one panel a workgroup (its code is the 1 of the last parameter): 16 columns' products with
+    4-bit codes, 8 with 8-bit ones -- twice where the zeros are any -- and none for panels that never come."""
+    checked = 0
+    for f in code_objects:
+        for name, code in _kernels(f, "gqsa_panel_kernel"):
+            form = re.search(r"kernelILi(\d)ELi\dELb(\d)ELi16ELi1ELNS0_4RowsE1", name)
+            if form:
+                checked += 1
+                products = {"4": 16, "8": 8}[form[1]] * (1 if form[2] == "1" else 2)
+                assert sum(op.startswith("v_mfma") for _, op, *_ in code) == products, name
+    assert checked == 14
+
+
 def _spills_among_products(code):
     """Addresses of the accesses to private memory between a kernel's first and last matrix product."""
     products = [i for i, (_, op, *_) in enumerate(code) if op.startswith("v_mfma")]
