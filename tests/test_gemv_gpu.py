@@ -1014,10 +1014,41 @@ def repeated(period, times, N, K, G, bits, sparsity, integer_zeros, seed):
 
 @pytest.mark.parametrize("integer_zeros", [True, False])
 @pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("sparsity,loads", [(0.5, 2), (0.9, 1)])
+@pytest.mark.parametrize("panels,batches", [((640, 700), (16, 9, 8)), ((1024, 1020), (16, 8)), ((2600,), (8,)), ((3900,), (5,))])
+def test_panel_kernel_slots_of_the_staging_area_taken_over(torch_cuda, bits, integer_zeros, sparsity, loads, panels, batches):
+    """Five to eight panels to a workgroup (of 16 wavefronts, several matrices; of 8, one matrix), every panel's records of a unit two loads -- four slots,
+    which the fifth to eighth panel take over -- or one, eight slots.  More units than wavefronts, the last one short."""
+    wavefronts = 16 if len(panels) > 1 else 8
+    columns = {4: 16, 8: 8}[bits]                       # of a unit
+    period, K = 80, 16 * ((wavefronts + 3) * columns + 1)
+    x = gi.activations(16, K, seed=71)
+    made = [repeated(period, -(-(16 * p - 3) // period), 16 * p - 3, K, 16, bits, sparsity, integer_zeros, seed=72) for p in panels]
+    c = made[0][1]
+    row = np.repeat(np.arange(period), np.diff(c.rowIndex))
+    held = np.bincount(row // 16 * (wavefronts + 4) + c.groups // columns, minlength=period // 16 * (wavefronts + 4))
+    held = held.reshape(-1, wavefronts + 4)[:, :-1] * {4: 12, 8: 24}[bits]      # bytes of a panel's records in a full unit
+    longest = held.max(axis=0)                          # of a workgroup's panels, which have all of the pattern
+    assert longest.max() <= 1024 * loads and (loads == 1 or longest.min() > 1024 * (loads - 1))        # (one load also where there is nothing)
+    ref = oracle.gemv(c, x, threads=8)
+    for batch in batches:
+        xd = torch_cuda.from_numpy(x[:batch].copy()).cuda()
+        ys = [torch_cuda.full((batch, 16 * p - 3), float("nan"), dtype=torch_cuda.float16, device="cuda") for p in panels]
+        gq.gqsa_gemv_multi([h for h, _ in made], xd, ys)
+        torch_cuda.cuda.synchronize()
+        for y in ys:
+            y = y.cpu().numpy()
+            for b in range(batch):
+                assert oracle.rel_error(y[b][:period], ref[b]) <= TOL
+                assert np.array_equal(y[b].view(np.uint16), np.tile(y[b][:period], -(-y.shape[1] // period))[:y.shape[1]].view(np.uint16))
+
+
+@pytest.mark.parametrize("integer_zeros", [True, False])
+@pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("panels", [769, 1537, 2561])
 def test_panel_kernel_up_to_eight_rows_of_which_three_panels_fit(torch_cuda, bits, integer_zeros, panels):
-    """10 and 20 % pruned, up to 8 rows: three panels' records fit the staging area and the fourth's do not.  Four panels to a
-    workgroup of 16 or of 8 wavefronts (staged two and two), six (three and one, then the second quad), and fewer."""
+    """10 and 20 % pruned, up to 8 rows: three loads a panel, so that the staging area has two slots.  Four panels to a
+    workgroup of 16 or of 8 wavefronts, six, and fewer."""
     period, K = 80, (4096 if bits == 4 else 2048) + 16
     N = 16 * panels - 3
     times = -(-N // period)
@@ -1033,8 +1064,8 @@ def test_panel_kernel_up_to_eight_rows_of_which_three_panels_fit(torch_cuda, bit
 
 
 def test_panel_kernel_a_tenth_fewer_groups_take_no_longer(torch_cuda):
-    """32000x2048, trained zeros, 8 rows: with 10 % pruned three of a workgroup's four panels fit the staging area; staged
-    three and one they took 1.07 to 1.09 times as long as the unpruned ones, which go two and two (as these do: 1.00)."""
+    """32000x2048, trained zeros, 8 rows: with 10 % pruned three of a workgroup's four panels would fit the staging area; staged
+    three and one they took 1.07 to 1.09 times as long as the unpruned ones (panel by panel, in two slots: no longer)."""
     N, K, period = 32000, 2048, 80
     full, pruned = (repeated(period, N // period, N, K, 16, 4, s, False, seed=98)[0] for s in (0.0, 0.1))
     all_groups, fewer = replay_times(torch_cuda, ((full, 8), (pruned, 8)))
@@ -1070,7 +1101,7 @@ def test_panel_kernel_up_to_eight_rows(torch_cuda, bits, integer_zeros):
 @pytest.mark.parametrize("bits,G", [(4, 16), (4, 32), (4, 64), (4, 128), (8, 16), (8, 32), (8, 64)])
 def test_panel_kernel_rows_have_the_same_bits_in_other_batches(torch_cuda, bits, G, integer_zeros):
     """A row has the same bits in every batch of up to 8 rows and in every batch of 9 to 16, and with G > 16 in all of them, whichever
-    way the activations are loaded (one matrix of at most 256 panels: another way from 10 or 12 rows on; more panels: one way)."""
+    way the activations are loaded (one matrix of at most 256 panels: another way from 9, 11 or 12 rows on; more panels: one way)."""
     for N, K in ((70, 35 * G), (4112, 16 * G)):
         c = oracle.pack(gi.dense_weight(N, K, seed=51), G, bits, sparsity=0.4)
         if not integer_zeros:
