@@ -106,8 +106,8 @@ enum class Rows { direct, turned, few };
 
 // few and turned: the records of a unit's panels come in panel by panel, each panel with `pieces` loads (1 to 3), into slots of the staging area
 // in turn.  Loads return in the order of issue, so once all but the newest `newer_loads` have, panel pp's are there: those of the panels issued behind
-// it.  Two waits serve all cases: for all but three loads, and for all.  (One for every count from 0 to 6, chosen by comparisons, was ten scalar
-// instructions and up to six branches a panel for each of 16 wavefronts: 1629x8192 W8 at 8 rows and its like 2 % slower.)
+// it.  Two waits serve all cases: for all but three loads, and for all.  (With one for every count that occurs, chosen by comparisons,
+// 6318x1024 W8 at 8 rows took 3 % longer, 5916x2048 2 %.)
 constexpr int slots_for(int pieces) { return pieces == 1 ? 8 : pieces == 2 ? 4 : 2; }
 constexpr int newer_loads(int pp, int n_live, int n_slots, int pieces) { return ((n_live < n_slots + pp ? n_live : n_slots + pp) - 1 - pp) * pieces; }
 constexpr int kStillOut = 3;
@@ -141,7 +141,8 @@ struct PanelTargets {
 // A workgroup takes up to four panels (eight: QUADS) of 16 output rows (blockIdx.x, + gridDim.x, ...); wavefront
 // w takes the units w, w + 16, ... (a unit = a run of group-columns, half a slice or less) of
 // every one of them, so the activations under a unit are loaded once for all of the workgroup's
-// panels.  A block's header is the same for all lanes and is read with scalar loads (few rows: see products_few).  The records
+// panels.  A block's header is the same for all lanes and is read with scalar loads (turned: the words of the columns; what staging asks of
+// all panels comes with one vector load there, and few reads all words that way, see load_ends).  The records
 // of a panel in a unit are contiguous in the image; the wavefront copies them from global memory
 // straight into its own part of LDS, 1 KiB per instruction with nothing passing through
 // registers (direct: all of its panels at once when they fit, else two and two; turned and few: panel after panel, a few ahead), and every lane then
@@ -175,11 +176,11 @@ struct PanelTargets {
 // panels than four per compute unit -- 8 and two: the loads of one then run under the products
 // of the other (workgroups of 16 wavefronts can only follow one another, each loading, then
 // computing).  Either way four wavefronts per SIMD unit, 128 vector registers each.
-// QUADS: a workgroup takes its panels four at a time (a quad: their headers share the scalar registers,
-// their records the staging area), and up to QUADS quads under the activations of a unit, which are loaded
+// QUADS: a workgroup has up to four panels, or eight (direct takes them four at a time -- a quad: their headers share the scalar registers,
+// their records the staging area -- turned and few one by one), under the activations of a unit, which are loaded
 // once for all of them: every compute unit pulls all of x through its L1 (128 KB at 16 rows and K = 4096, direct at
 // about 16 bytes per cycle: 3.4 us, see Rows), so a second workgroup or launch for the panels beyond the fourth
-// pays that again.  Two quads against one, at 16 rows, K = 4096, W4 S = 50 %: gate/up of 2 x 11008 in one launch
+// pays that again.  Two quads against one when they came (direct), at 16 rows, K = 4096, W4 S = 50 %: gate/up of 2 x 11008 in one launch
 // instead of two 24.3 -> 22.6 us, 2 x 14336 29.0 -> 25.1 us (W8 33.5 -> 29.4), one matrix of 60000 rows 46.5 -> 43.4 us, 32000 rows
 // the same.  (One matrix of 1025 to 2048 panels has at most four for each of its 512 workgroups and never reaches a second quad; what
 // it gained, 20000 rows 25.0 -> 18.5 us, 28672x8192 45.4 -> 40.2, came from there being 512 of them where there were 313 and 448.)
@@ -523,7 +524,8 @@ __device__ __forceinline__ void panel_products(
     // the second -- and each lane has read, decoded and scaled the group of its own column only.  The launches are bound by
     // vector instructions (5.3 cycles each with four wavefronts on a SIMD unit, 3 for a plain fp32 multiply-add): per pair of
     // columns 6 for address and presence (the header words stay in a vector register, lane i's is broadcast by the instruction that
-    // uses it), 10 (8-bit codes: 9) for the codes, four of them ANDs at 3 cycles, 5 for the scale, where two columns by themselves take 6, 12 and 10.
+    // uses it), 10 (8-bit codes: 9) for the codes, four of them ANDs at 3 cycles, 5 for the scale, where two columns by themselves take 6, 12 and 10;
+    // counted over a panel of the compiled joint forms, the passing on of its slot included, 23.6 (8-bit codes 24.2) a pair, and 15.2 (15.5) a column in turned.
     // At 8 rows, W4 S = 50 %, when the form came: 4096x4096 6.9 -> 5.7 us, 3 x 4096x4096 in one launch 13.3 -> 11.3, 2 x 11008x4096 21.2 -> 18.1,
     // 4096x11008 12.4 -> 9.9, 32000x4096 24.0 -> 21.3; W8 4096x4096 7.6 -> 6.1, 2 x 14336x4096 28.0 -> 22.8, 4096x14336 18.1 -> 13.5.
     u32x4_t xp8[FEW ? HC / 2 : 1];
@@ -644,8 +646,8 @@ __device__ __forceinline__ void panel_products(
             asm volatile("" ::: "memory");
         }
     };
-    // 9 rows and more, G > 16: the header words of the panels' columns, scalar loads -- of a quad's panels at once where they fit the scalar
-    // registers, else a panel's when its products start (one latency a panel; asked for ahead of that they are slower yet: while a
+    // turned: the header words of the panels' columns, scalar loads -- of a quad's panels at once where they fit the scalar
+    // registers (8-bit codes, G > 16), else a panel's when its products start (one latency a panel; asked for ahead of that they are slower yet: while a
     // scalar load is under way every wait for LDS waits for it as well).
     constexpr bool kQuadWords = !FEW && kPanelsPerQuad * HC <= 32;
     uint32_t hh[kQuadWords ? kPanelsPerQuad : 1][FEW ? 1 : HC] = {};
@@ -1046,8 +1048,8 @@ gqsa_status_t panels_gemm(const gqsa_matrix* const* ms, int n, const void* x, vo
     //   G = 16, 4-bit codes: 11.7 / 12.1, 11.8 / 12.3, 12.2 / 12.3; 0.97, 0.985, 1.025; 8-bit codes: 13.3 / 13.2, 13.4 / 13.2, 13.4 / 13.2; 0.98, 0.99, 1.00
     //     (1024x4096 5.9 / 6.15, 5.95 / 6.1, 6.0 / 6.1).
     // (The figures of 9 to 11 rows are from when turned was compiled for four panels.  With one it is 2 % faster, and the lines could come down: 8-bit codes of
-    // G = 16 at 9, 10, 11 rows 1.02, 1.035, 1.05, 4-bit ones of G = 64 and 128 at 8 rows 1.04 to 1.08.  250 random launches of 9 to 16 rows, G = 16 to 128, S = 0 to
-    // 80 %, lost nothing by these lines against direct throughout below 10 and 12 rows, 0.985 at worst.)
+    // G = 16 at 9, 10, 11 rows 1.02, 1.035, 1.05, 4-bit ones of G = 64 and 128 at 8 rows 1.04 to 1.08.  100 random launches of 9 to 16 rows, G = 16 to 128, S = 0 to
+    // 80 %, against the lines of before, 10 and 12 rows: 1.06 times as fast, none slower.)
     // Several matrices of G = 16, 9 rows and more.  Up to one panel a workgroup, and with more than four (direct awaits the records of a whole quad),
     // turned is ahead whatever the rows, the codes and K; with two to four it is x that decides.  direct / turned at S = 50 %, by the units of 16 (8-bit codes:
     // 8) columns that K has, 9 and 16 rows (two matrices, the wavefronts' share of x grows with K up to 16 units, one each):
